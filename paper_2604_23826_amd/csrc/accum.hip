@@ -7,6 +7,21 @@
 
 namespace st {
 
+// Whether the columns are interleaved in one plane (row-major records): equal
+// strides, all columns of a row within one stride.  Then the elements of a few
+// rows are contiguous, which the kernel with a column per lane loads whole; a
+// row per lane (k_generic) touches a line per lane and element there, and is
+// kept for columns in separate planes, where it loads contiguous elements.
+static bool interleaved(const AccumLaunch& L) {
+  const char *lo = L.colbase[0], *hi = L.colbase[0];
+  for (int c = 1; c < L.p; ++c) {
+    if (L.colstride[c] != L.colstride[0]) return false;
+    lo = L.colbase[c] < lo ? L.colbase[c] : lo;
+    hi = L.colbase[c] > hi ? L.colbase[c] : hi;
+  }
+  return hi - lo < L.colstride[0];
+}
+
 int64_t launch_accum_small_p(const AccumLaunch& L, hipStream_t s) {
   const int p = L.p;
   if (p < 1 || p > 16) return -1;
@@ -54,6 +69,10 @@ int64_t launch_accum_small_p(const AccumLaunch& L, hipStream_t s) {
   a.nrows = L.nrows;
   a.R = L.block_rows;
   a.rec = L.rec;
+  if (kind == ACC_GENERIC && interleaved(L)) {
+    launch_rows(a, p, nblocks, s);
+    return nblocks;
+  }
   switch (p) {
 #define ST_CASE(PP) \
   case PP: launch_accum_p<PP>(a, kind, ni, nblocks, s); break;

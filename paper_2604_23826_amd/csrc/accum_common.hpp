@@ -219,4 +219,8 @@ __device__ inline double shift_of(const char* p) {
 }
 
 }  // namespace acc
+
+// The matrix-core kernel for interleaved columns of any type (rows_mfma.hip);
+// slots in column order.
+void launch_rows(const acc::Args& a, int p, int64_t nblocks, hipStream_t s);
 }  // namespace st

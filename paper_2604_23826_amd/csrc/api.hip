@@ -375,9 +375,12 @@ static bool aos_rows_layout(const stats_ctx* h, const void* const* planes, int R
   return true;
 }
 
-static int accumulate_aos_rows(stats_ctx* h, const void* const* planes, int64_t nrows, int64_t R, int RS) {
+// Uniform blocks of R rows on the record kernel of RS-byte rows, or (RS = 0,
+// p <= 32, any layout) on the kernel with a column per lane.
+int accumulate_rows(stats_ctx* h, const void* const* planes, int64_t nrows, int64_t R, int RS) {
   const int p = h->p;
-  const int pl = h->cols[0].plane;
+  int32_t dtypes[32];
+  for (int c = 0; c < p; ++c) dtypes[c] = h->cols[c].dtype;
   // slot table and queue word in aux3 (shared with the wide path,
   // accumulate_device_wide; one of them runs per launch, stream-ordered)
   const size_t slot_bytes = (sizeof(wide::SlotInfo) * (size_t)p + 255) / 256 * 256;
@@ -401,10 +404,10 @@ static int accumulate_aos_rows(stats_ctx* h, const void* const* planes, int64_t 
     for (int c = 0; c < p; ++c) {
       const stats_column& col = h->cols[c];
       wide::SlotInfo& sl = slots[c];
-      sl.stride = RS;
-      sl.base = (const char*)planes[pl] + 8 * c + done * RS;
+      sl.stride = h->row_stride[col.plane];
+      sl.base = (const char*)planes[col.plane] + col.byte_offset + done * sl.stride;
       sl.kind = col.dtype;
-      sl.chk = (col.flags & STATS_COL_INTEGER) ? 1 : 0;
+      sl.chk = (col.dtype == STATS_F32 || col.dtype == STATS_F64) && (col.flags & STATS_COL_INTEGER);
       sl.isint = h->intf[c];
       sl.pad[0] = sl.pad[1] = 0;
     }
@@ -425,7 +428,9 @@ static int accumulate_aos_rows(stats_ctx* h, const void* const* planes, int64_t 
     {
       Timer t;
       t.begin(h, STATS_K_ACCUM);
-      launch_seg_aos64(a, g, (int)std::min<int64_t>(nblocks, (int64_t)ncu * 8), h->stream, RS);
+      const int nwg = (int)std::min<int64_t>(nblocks, (int64_t)ncu * 8);
+      if (RS) launch_seg_aos64(a, g, nwg, h->stream, RS);
+      else launch_seg_rows(a, g, dtypes, nwg, h->stream);
       t.end();
     }
     e = hipGetLastError();
@@ -473,7 +478,7 @@ int64_t block_rows_for(const stats_ctx* h, int64_t nrows) {
 int accumulate_device_small(stats_ctx* h, const void* const* planes, int64_t nrows) {
   const int p = h->p;
   const int64_t R = block_rows_for(h, nrows);
-  if (p >= 11 && aos_rows_layout(h, planes, 128)) return accumulate_aos_rows(h, planes, nrows, R, 128);
+  if (p >= 11 && aos_rows_layout(h, planes, 128)) return accumulate_rows(h, planes, nrows, R, 128);
   const AccumLaunch a = accum_launch_of(h, planes);
   const int64_t W = rec_words(p);
   // at most 2^28 rows (and 16384 blocks) per launch: plane offsets stay 32-bit
@@ -516,7 +521,7 @@ int accumulate_device(stats_ctx* h, const void* const* planes, int64_t nrows) {
   if (h->flags & STATS_CFG_PAIRWISE) return accumulate_pairwise(h, planes, nrows);
   if (h->p <= 16) return accumulate_device_small(h, planes, nrows);
   if (h->p <= 32 && h->precision != STATS_PREC_SPLIT && aos_rows_layout(h, planes, 256))
-    return accumulate_aos_rows(h, planes, nrows, h->block_rows ? h->block_rows : auto_block_rows(nrows), 256);
+    return accumulate_rows(h, planes, nrows, h->block_rows ? h->block_rows : auto_block_rows(nrows), 256);
   return accumulate_device_wide(h, planes, nrows);
 }
 

@@ -92,6 +92,7 @@ int sync_handle(stats_ctx* h);
 void collect_timings(stats_ctx* h);
 int accumulate_device(stats_ctx* h, const void* const* planes, int64_t nrows);
 int accumulate_device_wide(stats_ctx* h, const void* const* planes, int64_t nrows);
+int accumulate_rows(stats_ctx* h, const void* const* planes, int64_t nrows, int64_t R, int RS);
 int accumulate_host_src(stats_ctx* h, const void* const* planes, int fd, int64_t file_off, int64_t nrows,
                         bool pinned);
 int pairwise_state_words(int p);

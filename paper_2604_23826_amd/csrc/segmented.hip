@@ -277,7 +277,7 @@ std::map<std::string, Tuned> g_tuned;
 // kernel (the 256-byte record kernel or the general one) and the layout of
 // every column (type, plane, byte offset, plane row stride).
 std::string tune_key(const stats_ctx* h, const char* arch, bool aos64) {
-  std::string k = std::string(arch) + ":p" + std::to_string(h->p) + (aos64 ? ":rec" : ":gen");
+  std::string k = std::string(arch) + ":p" + std::to_string(h->p) + (aos64 ? ":rec" : h->p <= 32 ? ":rows" : ":gen");
   for (const auto& c : h->cols)
     k += ":" + std::to_string(c.dtype) + "." + std::to_string(c.plane) + "." +
          std::to_string(c.byte_offset) + "." + std::to_string(h->row_stride[c.plane]);
@@ -441,10 +441,16 @@ static bool seg_aos64_layout(const stats_ctx* h, const void* const* planes) {
 }
 
 static void seg_launch(const stats_ctx* h, bool aos64, const wide::Args& a, const wide::SegArgs& g,
-                       int ST, int nwg, hipStream_t s) {
-  (void)h;
-  if (aos64) launch_seg_aos64(a, g, nwg, s);
-  else launch_seg(a, g, ST, nwg, s);
+                       int nwg, hipStream_t s) {
+  if (aos64) {
+    launch_seg_aos64(a, g, nwg, s);
+  } else if (h->p <= 32) {
+    int32_t dt[32];
+    for (int c = 0; c < h->p; ++c) dt[c] = h->cols[c].dtype;
+    launch_seg_rows(a, g, dt, nwg, s);
+  } else {
+    launch_seg(a, g, nwg, s);
+  }
 }
 
 static int num_cus(int device) {
@@ -501,9 +507,9 @@ static int autotune(stats_ctx* h, const void* const* planes, const int64_t* off,
     a.status = h->status_dev;
     wide::SegArgs s{B.rowtiles, B.nrt, B.counter};
     for (int W : cands_W) {
-      seg_launch(h, aos64, a, s, ST, ncu * W, h->stream);  // warm
+      seg_launch(h, aos64, a, s, ncu * W, h->stream);  // warm
       (void)hipEventRecord(e0, h->stream);
-      seg_launch(h, aos64, a, s, ST, ncu * W, h->stream);
+      seg_launch(h, aos64, a, s, ncu * W, h->stream);
       (void)hipEventRecord(e1, h->stream);
       e = hipEventSynchronize(e1);
       if (e != hipSuccess) {
@@ -652,7 +658,7 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
     }
     e = hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(h, e, "hipStreamBeginCapture");
-    seg_launch(h, aos64, a, sa, ST, nwg, h->cap_stream);
+    seg_launch(h, aos64, a, sa, nwg, h->cap_stream);
     hipLaunchKernelGGL(k_seg_part, dim3((unsigned)(num_cus(h->device) * 8)), dim3(kMergeThreads), 0,
                        h->cap_stream, h->rec, B.chunks, B.nch, p, h->intf_dev, h->seg_part, h->status_dev);
     const size_t shm = sizeof(double) * (size_t)(p + 1);

@@ -247,8 +247,8 @@ void launch_wide(const wide::Args& a, int st, int mode, hipStream_t s) {
     launch_wide_split(a, st, s);
     return;
   }
-  if (st == 32) hipLaunchKernelGGL(wide::k_wide_f64<32>, grid, block, 0, s, a);
-  else hipLaunchKernelGGL(wide::k_wide_f64<64>, grid, block, 0, s, a);
+  // FP64 tables and groups of p <= 32 columns run on rows_mfma.hip
+  hipLaunchKernelGGL(wide::k_wide_f64<64>, grid, block, 0, s, a);
 }
 
 void launch_wide_fixup(const wide::Args& a, int st, const int* ovf, hipStream_t s) {
@@ -258,10 +258,9 @@ void launch_wide_fixup(const wide::Args& a, int st, const int* ovf, hipStream_t 
   else hipLaunchKernelGGL(wide::k_wide_fixup<64>, grid, block, 0, s, a, ovf);
 }
 
-void launch_seg(const wide::Args& a, const wide::SegArgs& g, int st, int nwg, hipStream_t s) {
+void launch_seg(const wide::Args& a, const wide::SegArgs& g, int nwg, hipStream_t s) {
   hipLaunchKernelGGL(wide::k_zero_counter, dim3(1), dim3(1), 0, s, g.counter);
-  if (st == 32) hipLaunchKernelGGL(wide::k_seg_f64<32>, dim3(nwg), dim3(wide::kThreads), 0, s, a, g);
-  else hipLaunchKernelGGL(wide::k_seg_f64<64>, dim3(nwg), dim3(wide::kThreads), 0, s, a, g);
+  hipLaunchKernelGGL(wide::k_seg_f64<64>, dim3(nwg), dim3(wide::kThreads), 0, s, a, g);
 }
 
 }  // namespace st

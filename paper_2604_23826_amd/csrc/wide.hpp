@@ -87,10 +87,15 @@ void launch_syrk_split(const wide::SyrkArgs& a, hipStream_t s);
 // a.nblocks as for the launch that set them).
 void launch_wide_fixup(const wide::Args& a, int st, const int* ovf, hipStream_t s);
 
-// Persistent segmented launch (zeroes the queue first): nwg workgroups.
-void launch_seg(const wide::Args& a, const wide::SegArgs& g, int st, int nwg, hipStream_t s);
+// Persistent segmented launch of p > 32 columns (zeroes the queue first): nwg
+// workgroups.
+void launch_seg(const wide::Args& a, const wide::SegArgs& g, int nwg, hipStream_t s);
 // The same for FP64 records of 256 bytes, column c at byte 8c, p <= 32.
 void launch_seg_aos64(const wide::Args& a, const wide::SegArgs& g, int nwg, hipStream_t s, int row_bytes = 256);
+
+// Items of tables or groups of p <= 32 columns in any layout (rows_mfma.hip);
+// dtypes: the columns' STATS_* types.
+void launch_seg_rows(const wide::Args& a, const wide::SegArgs& g, const int32_t* dtypes, int nwg, hipStream_t s);
 
 // st = super-group width (32 or 64); mode = MODE_FP64 or MODE_SPLIT.
 void launch_wide(const wide::Args& a, int st, int mode, hipStream_t s);

@@ -207,6 +207,7 @@ int accumulate_device_wide(stats_ctx* h, const void* const* planes, int64_t nrow
   const int ST = p <= 32 ? 32 : 64;
   const int ng = (p + ST - 1) / ST;
   const int mode = h->precision == STATS_PREC_SPLIT ? wide::MODE_SPLIT : wide::MODE_FP64;
+  if (mode == wide::MODE_FP64 && p <= 32) return accumulate_rows(h, planes, nrows, wide_block_rows(h, nrows), 0);
   std::vector<int2> tiles;
   for (int A = 0; A < ng; ++A)
     for (int B = A; B < ng; ++B) tiles.push_back(make_int2(A, B));
