@@ -162,18 +162,45 @@ __host__ __device__ inline U256 u256_mul64(const U256& a, uint64_t m) {
   return r;
 }
 
+// Shifts by 0 <= s < 256 as two limb moves and one bit shift, without indexing
+// the limbs by a variable (which would put them in scratch memory on the GPU).
 __host__ __device__ inline U256 u256_shl(const U256& a, int s) {
   U256 r = {{0, 0, 0, 0}};
   if (s >= 256) return r;
-  const int q = s >> 6, b = s & 63;
-  for (int k = 3; k >= 0; --k) {
-    int src = k - q;
-    if (src < 0) continue;
-    uint64_t v = a.w[src] << b;
-    if (b && src - 1 >= 0) v |= a.w[src - 1] >> (64 - b);
-    r.w[k] = v;
+  uint64_t w0 = a.w[0], w1 = a.w[1], w2 = a.w[2], w3 = a.w[3];
+  if (s & 128) {
+    w3 = w1;
+    w2 = w0;
+    w1 = w0 = 0;
   }
+  if (s & 64) {
+    w3 = w2;
+    w2 = w1;
+    w1 = w0;
+    w0 = 0;
+  }
+  const int b = s & 63;
+  r.w[3] = (w3 << b) | (w2 >> 1 >> (63 - b));
+  r.w[2] = (w2 << b) | (w1 >> 1 >> (63 - b));
+  r.w[1] = (w1 << b) | (w0 >> 1 >> (63 - b));
+  r.w[0] = w0 << b;
   return r;
+}
+
+// Low 64 bits of a >> s.
+__host__ __device__ inline uint64_t u256_shr_low(const U256& a, int s) {
+  uint64_t w0 = a.w[0], w1 = a.w[1], w2 = a.w[2];
+  if (s & 128) {
+    w0 = a.w[2];
+    w1 = a.w[3];
+    w2 = 0;
+  }
+  if (s & 64) {
+    w0 = w1;
+    w1 = w2;
+  }
+  const int b = s & 63;
+  return (w0 >> b) | (w1 << 1 << (63 - b));
 }
 
 __host__ __device__ inline U256 u256_shr1(const U256& a) {
@@ -241,9 +268,8 @@ __host__ __device__ inline int u256_cmp_half(const U256& a, const U256& b, int e
 // Top 64 bits of a (bit length la > 0) times 2^(la - 64), as a double.
 __host__ __device__ inline double u256_approx(const U256& a, int la) {
   if (la <= 64) return (double)a.w[0];
-  const int sh = la - 64, q = sh >> 6, r = sh & 63;
-  uint64_t v = a.w[q] >> r;
-  if (r && q + 1 < 4) v |= a.w[q + 1] << (64 - r);
+  const int sh = la - 64;
+  const uint64_t v = u256_shr_low(a, sh);
   return ldexp((double)v, sh);
 }
 

@@ -14,11 +14,16 @@
 // Table 3: eigenvalues descending, variance %, cumulative %, loadings (one
 // row per component).
 //
+// (Correlation matrices up to 60 x 60 take Householder reduction and implicit QL
+// instead, see below.)
+//
 // One workgroup does the whole job.  The working matrices live in LDS when
 // they fit (q <= kLdsQ, every PCA of the narrow path), else in a global
 // scratch buffer that stays in L2; there each thread loads the 2 x 2 blocks
 // of several rotations before it writes any (the blocks of one round are
 // disjoint), so the L2 latency is paid once per batch.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace st {
@@ -42,14 +47,17 @@ struct Args {
   int want_vectors;
   double* out;
   double* scratch;
-  int lds_mat;  // A and V in dynamic LDS after the rotation tables
-  int phase;     // kAll, or kPre / kPost around the multi-kernel Jacobi
   unsigned* jc;  // kPre / kPost: [0] rotations of a sweep, [1] no decomposition (non-finite
                  // input, or n <= ddof),
                  // [2] pairs that would still rotate after the sweep
 };
 
-enum { kAll = 0, kPre = 1, kPost = 2 };
+// What one k_finalize launch does: everything with the matrices in LDS
+// (q <= kLdsQ; Householder and QL for a correlation matrix, Jacobi for a
+// covariance matrix), or the parts before and after the multi-kernel Jacobi.
+// A template parameter, so that LDS accesses are known to be that and the
+// small sizes fetch only the code they run.
+enum { kQl = 0, kLdsJacobi = 1, kPre = 2, kPost = 3 };
 
 // Round-robin schedule on m (even) players: player at position pos in round
 // r (0 <= pos < m, 0 <= r < m - 1).
@@ -225,7 +233,240 @@ __device__ inline bool converged(const double* A, int q, int tid, int nth, int* 
   return *cnt == 0;
 }
 
-__global__ __launch_bounds__(kThreads) void k_finalize(Args f) {
+// ---- correlation matrices up to 60 x 60: Householder + implicit QL -----------
+//
+// A correlation matrix has a unit diagonal, so a solver whose errors are small
+// against its norm loses nothing on its small eigenvalues that Jacobi would
+// keep (a covariance matrix may be graded, and stays with Jacobi).  The matrix
+// is reduced to tridiagonal form in LDS, the reflectors are multiplied out,
+// and implicit QL runs on one wave: every lane carries the scalar recurrence
+// (d and e live one element per lane and are read by index across lanes), and
+// lane r applies each rotation to component r of the two eigenvectors.  What
+// bounds it is the chain of one rotation (about 1.2 q^2 of them), one
+// reciprocal square root and a dozen dependent FMAs (360 cycles in all), where a
+// Jacobi round (about 5 q of them) is three divisions, three square roots and
+// two barriers.  Whole kernel, 9 x 9: 89 -> 38 us; 15 x 15: 168 -> 72 us.
+constexpr int kQlThreads = 256;
+
+// Ordering point between the lanes that share the work: the whole workgroup,
+// or (kWave) one wave, whose LDS accesses execute in order.
+template <bool kWave>
+__device__ inline void group_sync() {
+  if constexpr (kWave) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    __syncthreads();
+  }
+}
+
+__device__ inline double lane_value(double v, int lane) {  // lane wave-uniform
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
+}
+
+// Sum over the four lanes of a quad, in every lane of it.
+__device__ inline double quad_sum(double v) {
+  auto move = [](double x, auto ctrl) {
+    constexpr int c = decltype(ctrl)::value;
+    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), c, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(0, __double2loint(x), c, 0xF, 0xF, false));
+  };
+  v += move(v, std::integral_constant<int, 0xB1>{});  // quad_perm [1,0,3,2]
+  v += move(v, std::integral_constant<int, 0x4E>{});  // quad_perm [2,3,0,1]
+  return v;
+}
+
+// 1 / sqrt(x) for normal x > 0: the hardware estimate and one third-order step.
+__device__ inline double rsqrt_f64(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = __builtin_fma(-x * y, y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
+// Lane i receives lane i + 1's value (lane 63: zero).
+__device__ inline double next_lane(double v) {
+  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xF, 0xF, true),
+                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xF, 0xF, true));
+}
+
+// Tridiagonal form of the symmetric matrix M (q x q, global or LDS) and the
+// orthogonal factor, transposed, in Zt (column j of it at Zt + j ld).  d[q],
+// e[q] (e[k] couples k and k + 1) and, as scratch, H (q x ld reflectors), beta[q]
+// and xp[256] in LDS.  Quad i of the threads holds row i of the working
+// matrix in registers (lane sub of it columns sub, sub + 4, ...), then column i
+// of the factor: 4 C >= q rows, 16 C threads.  A step exchanges row k and the
+// product through LDS, two ordering points in all.  Threads past 16 C take part
+// as empty rows (row < 64).
+template <int C, bool kWave>
+__device__ inline void tridiagonalize(const double* M, double* Zt, double* H, int ld, int q, double* d, double* e,
+                                      double* beta, double* xp, int tid) {
+  const int row = tid >> 2, sub = tid & 3;
+  double a[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    const int j = sub + 4 * c;
+    a[c] = row < q && j < q ? M[row * q + j] : 0.0;
+  }
+  auto sum = [](const double (&u)[C], const double (&v)[C]) {  // over the quad's columns
+    double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+    for (int c = 0; c < C; c += 2) {
+      t0 = __builtin_fma(u[c], v[c], t0);
+      t1 = __builtin_fma(u[c + 1], v[c + 1], t1);
+    }
+    return quad_sum(t0 + t1);
+  };
+  for (int k = 0; k + 1 < q; ++k) {
+    double* xb = xp + (k & 1) * 128;  // row k, then the product
+    double* pb = xb + 64;
+    if (row == k) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) xb[sub + 4 * c] = a[c];
+    }
+    group_sync<kWave>();
+    const double x0 = xb[k + 1], xi = xb[row];
+    if (k + 2 == q) {
+      if (tid == 0) e[k] = x0;
+      break;
+    }
+    double v[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const int j = sub + 4 * c;
+      const double x = xb[j];
+      v[c] = j > k + 1 ? x : 0.0;
+    }
+    const double tail = sum(v, v);
+    if (tail < 1e-280) {  // already tridiagonal here (as far below any rounding)
+      if (row == k) {
+        if (sub == 0) {
+          beta[k] = 0.0;
+          e[k] = x0;
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+          if (sub + 4 * c < q) H[k * ld + sub + 4 * c] = 0.0;
+      }
+      continue;
+    }
+    const double n2 = __builtin_fma(x0, x0, tail), norm = n2 * rsqrt_f64(n2);
+    const double v0 = x0 >= 0.0 ? x0 + norm : x0 - norm;
+    const double bk = 1.0 / (norm * (norm + fabs(x0)));
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      if (sub + 4 * c == k + 1) v[c] = v0;
+    const bool in = row > k && row < q;
+    const double av = sum(a, v);
+    const double vi = row == k + 1 ? v0 : (in ? xi : 0.0);
+    const double pi = in ? bk * av : 0.0;
+    if (sub == 0) pb[row] = pi;
+    group_sync<kWave>();
+    double p[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) p[c] = pb[sub + 4 * c];
+    const double h = 0.5 * bk * sum(p, v);
+    const double wi = __builtin_fma(-h, vi, pi);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const double wj = __builtin_fma(-h, v[c], p[c]);
+      a[c] -= __builtin_fma(vi, wj, wi * v[c]);
+    }
+    if (row == k) {
+      if (sub == 0) {
+        beta[k] = bk;
+        e[k] = x0 >= 0.0 ? -norm : norm;
+      }
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+        if (sub + 4 * c < q) H[k * ld + sub + 4 * c] = v[c];
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    if (row < q && sub + 4 * c == row) d[row] = a[c];
+  if (tid == 0) e[q - 1] = 0.0;
+  group_sync<kWave>();
+  // H_0 H_1 ... from the last reflector on
+  double z[C];
+#pragma unroll
+  for (int c = 0; c < C; ++c) z[c] = sub + 4 * c == row ? 1.0 : 0.0;
+  for (int k = q - 3; k >= 0; --k) {
+    double v[C];
+#pragma unroll
+    for (int c = 0; c < C; ++c) v[c] = sub + 4 * c < q ? H[k * ld + sub + 4 * c] : 0.0;
+    const double t = beta[k] * sum(v, z);
+#pragma unroll
+    for (int c = 0; c < C; ++c) z[c] = __builtin_fma(-t, v[c], z[c]);
+  }
+  if (row < q) {
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+      if (sub + 4 * c < q) Zt[row * ld + sub + 4 * c] = z[c];
+  }
+  group_sync<kWave>();
+}
+
+// Implicit QL on (d, e) (one wave, q <= 63 < ld); the rotations are applied to
+// the columns of the factor in Zt.  The eigenvalues replace d.
+__device__ inline void implicit_ql(double* Zt, int ld, int q, double* dv, const double* ev, int lane) {
+  double d = lane < q ? dv[lane] : 0.0, e = lane + 1 < q ? ev[lane] : 0.0;
+  double* zp = Zt + min(lane, q);  // lanes without a component use the padding
+  for (int l = 0; l < q - 1; ++l) {
+    for (int it = 0; it < kMaxSweeps; ++it) {
+      // first negligible coupling at or after l
+      const uint64_t small = __builtin_amdgcn_ballot_w64(
+          fabs(e) <= 2.220446049250313e-16 * (fabs(d) + fabs(next_lane(d))) || lane >= q - 1);
+      const int m = l + __builtin_ctzll(small >> l);
+      if (m == l) break;
+      // Wilkinson's shift (any shift is exact; approximate operations do)
+      const double dl = lane_value(d, l), el = lane_value(e, l), dm = lane_value(d, m);
+      const double h = 0.5 * (lane_value(d, l + 1) - dl);
+      const double h2 = __builtin_fma(h, h, el * el);
+      double g = dm - dl;
+      if (h2 > 1e-280) g = __builtin_fma(el * el, __builtin_amdgcn_rcp(h + copysign(h2 * rsqrt_f64(h2), h)), g);
+      double s = 1.0, c = 1.0, p = 0.0, dnext = dm;  // dnext: d[i + 1] before this rotation
+      double zc = zp[m * ld];
+      int i = m - 1;
+      double ei = lane_value(e, i), di = lane_value(d, i), zi = zp[i * ld];
+#pragma unroll 2
+      for (; i >= l; --i) {
+        const int ip = max(i - 1, l);  // next rotation's inputs, in flight early
+        const double ein = lane_value(e, ip), din = lane_value(d, ip), zin = zp[ip * ld];
+        const double f = s * ei, b = c * ei;
+        const double x = __builtin_fma(f, f, g * g);
+        // a vanished bulge: the identity, and the next sweep splits here
+        const bool none = x < 1e-280;
+        const double y = rsqrt_f64(none ? 1.0 : x);
+        s = none ? 0.0 : f * y;
+        c = none ? 1.0 : g * y;
+        const bool up = lane == i + 1;
+        e = up ? (none ? 0.0 : x * y) : e;
+        g = dnext - p;
+        const double t = __builtin_fma(di - g, s, 2.0 * (c * b));
+        p = s * t;
+        d = up ? g + p : d;
+        g = __builtin_fma(c, t, -b);
+        zp[(i + 1) * ld] = __builtin_fma(s, zi, c * zc);
+        zc = __builtin_fma(c, zi, -(s * zc));
+        dnext = di;
+        ei = ein;
+        di = din;
+        zi = zin;
+      }
+      zp[l * ld] = zc;
+      if (lane == l) {
+        d = dnext - p;
+        e = g;
+      }
+      if (lane == m) e = 0.0;
+    }
+  }
+  if (lane < q) dv[lane] = d;
+}
+
+template <int PHASE>
+__global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k_finalize(Args f) {
   const Layout L = Layout::make(f.p);
   const uint64_t* st = f.state;
   const int64_t n = (int64_t)st[0];
@@ -248,21 +489,27 @@ __global__ __launch_bounds__(kThreads) void k_finalize(Args f) {
   // c[npairs], s[npairs], t[npairs], apq[npairs], the round's pairs, A, V
   extern __shared__ double s_dyn[];
   const RotTab R = RotTab::at(s_dyn, npairs);
-  double* A = f.scratch;
-  if (f.lds_mat) A = s_dyn + 5 * npairs;
-  double* V = A + (int64_t)q * q;
+  // (QL: d, e, beta, q each, and 256 words of exchange in their place, and rows
+  // padded to an odd length above q)
+  double* A;
+  if constexpr (PHASE == kQl) A = s_dyn + 3 * q + 256;
+  else if constexpr (PHASE == kLdsJacobi) A = s_dyn + 5 * npairs;
+  else A = f.scratch;
+  const int ld = PHASE == kQl ? (q + 1) | 1 : q;
+  double* V = A + (int64_t)q * ld;
 
-  if (f.phase == kPost) {
+  if constexpr (PHASE == kPost) {
     if (f.jc[1]) return;  // no decomposition: see the pre phase
-  } else if (n <= f.ddof) {
+  } else {
+  if (n <= f.ddof) {
     // covariance undefined (the host reports it); nothing is computed, and
     // the exact divisions by n and n - ddof are never reached
-    if (f.phase == kPre && tid == 0) {
+    if (PHASE == kPre && tid == 0) {
       f.jc[0] = 0;
       f.jc[1] = 1;
     }
     return;
-  } else {
+  }
   // ---- means and covariance ----
   const double dn = (double)(n - f.ddof);
   for (int a = tid; a < q; a += nth) {
@@ -273,9 +520,14 @@ __global__ __launch_bounds__(kThreads) void k_finalize(Args f) {
   // q <= 1024: every index below fits 32 bits (64-bit division is a long
   // software sequence on the GPU)
   const int qq = q * q;
-  for (int idx = tid; idx < qq; idx += nth) {
-    const int a = idx / q, b = idx % q;
-    if (a > b) continue;
+  // the triangle a <= b as a rectangle of (q + 1) / 2 rows of length q | 1: row r
+  // is row r of the triangle followed by its row of the remaining length, so
+  // that no thread idles in the exact divisions
+  const int len = q | 1, ntri = (q + 1) / 2 * len;
+  for (int idx = tid; idx < ntri; idx += nth) {
+    const int r = idx / len, c = idx % len;
+    const int a = c < q - r ? r : q - r - 1 + (q & 1);
+    const int b = c < q - r ? r + c : a + c - (q - r);
     const int i = f.sel[a], j = f.sel[b];  // sel ascending, so i <= j
     double v;
     if (f.intf[i] && f.intf[j]) v = exact_cov(st, L, i, j, n, f.ddof);
@@ -302,12 +554,15 @@ __global__ __launch_bounds__(kThreads) void k_finalize(Args f) {
   for (int idx = tid; idx < qq; idx += nth) {
     const double v = M[idx];
     if (!isfinite(v)) bad = 1;
-    A[idx] = v;
-    V[idx] = (idx / q == idx % q) ? 1.0 : 0.0;
+    const int i = idx / q, j = idx % q;
+    if constexpr (PHASE != kQl) {
+      A[i * ld + j] = v;
+      V[idx] = i == j ? 1.0 : 0.0;
+    }
   }
   if (bad) atomicOr(&s_flag, 1);
   __syncthreads();
-  if (f.phase == kPre && tid == 0) {
+  if (PHASE == kPre && tid == 0) {
     f.jc[0] = 0;
     f.jc[1] = s_flag ? 1u : 0u;
   }
@@ -318,8 +573,20 @@ __global__ __launch_bounds__(kThreads) void k_finalize(Args f) {
     }
     return;
   }
-  if (f.phase == kPre) return;
+  if constexpr (PHASE == kPre) return;
 
+  if constexpr (PHASE == kQl) {
+    double *d = s_dyn, *e = d + q, *beta = e + q, *xp = beta + q;
+    if (q <= 16) {  // one wave holds a quad per row
+      if (tid < 64) tridiagonalize<4, true>(M, V, A, ld, q, d, e, beta, xp, tid);
+    } else if (q <= 32) {
+      tridiagonalize<8, false>(M, V, A, ld, q, d, e, beta, xp, tid);
+    } else {
+      tridiagonalize<16, false>(M, V, A, ld, q, d, e, beta, xp, tid);
+    }
+    if (tid < 64) implicit_ql(V, ld, q, d, e, tid);
+    __syncthreads();
+  } else if constexpr (PHASE == kLdsJacobi) {
   // ---- cyclic Jacobi, round-robin ordering: q/2 disjoint rotations per round ----
   if (nth == 64 && q <= 16) {
     // One wave, at most one 2x2 block and two V row pairs per lane.  Each
@@ -433,41 +700,55 @@ __global__ __launch_bounds__(kThreads) void k_finalize(Args f) {
     __syncthreads();
   }
   }
-  }  // phase kAll / kPre
+  }
+  }  // all but kPost
 
   // ---- sort descending (ties: lower index first), sign rule, percentages ----
+  // component j of eigenvector k at V + j vj + k vk; sorted eigenvalues and their
+  // sources (complemented where the vector changes sign) in LDS that is free now
+  const int vj = PHASE == kQl ? 1 : q, vk = PHASE == kQl ? ld : 1;
+  double* lam = PHASE == kQl ? s_dyn + q : s_dyn;
+  double* var = PHASE == kQl ? s_dyn + 2 * q : s_dyn + q;
+  int* src = (int*)(s_dyn + (PHASE == kQl ? 3 : 2) * q);
   for (int k = tid; k < q; k += nth) {
-    const double lk = A[(int64_t)k * q + k];
+    const double lk = PHASE == kQl ? s_dyn[k] : A[(int64_t)k * q + k];
     int rank = 0;
     for (int j = 0; j < q; ++j) {
-      const double lj = A[(int64_t)j * q + j];
+      const double lj = PHASE == kQl ? s_dyn[j] : A[(int64_t)j * q + j];
       rank += (lj > lk) || (lj == lk && j < k);
     }
-    ev[rank] = lk;
-    // eigenvector k = column k of V; sign: largest |entry| positive (lowest index on ties)
-    int arg = 0;
-    double best = -1.0;
+    // eigenvector k's sign: largest |entry| positive (lowest index on ties)
+    double best = -1.0, top = 0.0;
     for (int j = 0; j < q; ++j) {
-      const double a = fabs(V[(int64_t)j * q + k]);
-      if (a > best) {
-        best = a;
-        arg = j;
+      const double x = V[(int64_t)j * vj + (int64_t)k * vk];
+      if (fabs(x) > best) {
+        best = fabs(x);
+        top = x;
       }
     }
-    const double sg = V[(int64_t)arg * q + k] < 0.0 ? -1.0 : 1.0;
-    if (f.want_vectors)
-      for (int j = 0; j < q; ++j) evec[(int64_t)rank * q + j] = sg * V[(int64_t)j * q + k];
+    lam[rank] = lk;
+    src[rank] = top < 0.0 ? ~k : k;
   }
   __syncthreads();
-  if (tid == 0) {
-    double tot = 0.0;
-    for (int k = 0; k < q; ++k) tot += ev[k];
-    double run = 0.0;
-    for (int k = 0; k < q; ++k) {
-      varp[k] = 100.0 * ev[k] / tot;
-      run += varp[k];
-      cump[k] = run;
+  if (f.want_vectors) {
+    for (int idx = tid; idx < q * q; idx += nth) {
+      const int r = idx / q, j = idx % q;
+      const int k = src[r] < 0 ? ~src[r] : src[r];
+      const double x = V[(int64_t)j * vj + (int64_t)k * vk];
+      evec[idx] = src[r] < 0 ? -x : x;
     }
+  }
+  double tot = 0.0;
+  for (int k = 0; k < q; ++k) tot += lam[k];
+  for (int k = tid; k < q; k += nth) {
+    ev[k] = lam[k];
+    varp[k] = var[k] = 100.0 * lam[k] / tot;
+  }
+  __syncthreads();
+  for (int k = tid; k < q; k += nth) {
+    double run = 0.0;
+    for (int j = 0; j <= k; ++j) run += var[j];
+    cump[k] = run;
   }
 }
 
@@ -574,20 +855,21 @@ hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
   a.scratch = F.scratch;
   a.jc = F.jc;
   const int npairs = (F.q + (F.q & 1)) / 2;
-  size_t shm = (size_t)npairs * 5 * sizeof(double);
-  a.lds_mat = F.q <= kLdsQ;
-  if (a.lds_mat) {
-    // one workgroup does everything; one wave for the small matrices of the
-    // narrow path (its barriers cost nothing)
-    shm += 2 * sizeof(double) * (size_t)F.q * F.q;
-    a.phase = kAll;
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(F.q <= 16 ? 64 : 256), shm, s, a);
+  const size_t tab_shm = (size_t)npairs * 5 * sizeof(double);
+  if (F.q <= kLdsQ) {
+    if (!F.pca_on) {
+      const size_t shm = (256 + (3 + 2 * (size_t)((F.q + 1) | 1)) * (size_t)F.q) * sizeof(double);
+      hipLaunchKernelGGL(k_finalize<kQl>, dim3(1), dim3(kQlThreads), shm, s, a);
+    } else {
+      // one wave for the small matrices (its barriers cost nothing)
+      const size_t shm = tab_shm + 2 * sizeof(double) * (size_t)F.q * F.q;
+      hipLaunchKernelGGL(k_finalize<kLdsJacobi>, dim3(1), dim3(F.q <= 16 ? 64 : 256), shm, s, a);
+    }
     return hipGetLastError();
   }
   // wide matrices: the Jacobi rounds as separate kernels over the whole GPU,
   // sweeps until one makes no rotation
-  a.phase = kPre;
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kThreads), shm, s, a);
+  hipLaunchKernelGGL(k_finalize<kPre>, dim3(1), dim3(kThreads), tab_shm, s, a);
   hipError_t e = hipGetLastError();
   double* A = F.scratch;
   double* V = A + (int64_t)F.q * F.q;
@@ -597,7 +879,6 @@ hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
   if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   const int64_t work = (int64_t)npairs * npairs + (int64_t)F.q * npairs;
   const int nwg = (int)std::max<int64_t>(1, std::min<int64_t>((work + kJThreads * kNB - 1) / (kJThreads * kNB), 4 * ncu));
-  const size_t tab_shm = (size_t)npairs * 5 * sizeof(double);
   for (int sweep = 0; sweep < kMaxSweeps && F.q > 1 && e == hipSuccess; ++sweep) {
     e = hipMemsetAsync(F.jc, 0, sizeof(unsigned), s);
     for (int r = 0; r < m - 1 && e == hipSuccess; ++r) {
@@ -618,8 +899,7 @@ hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
     if (e != hipSuccess || w[0] == 0 || w[2] == 0) break;
   }
   if (e != hipSuccess) return e;
-  a.phase = kPost;
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kThreads), shm, s, a);
+  hipLaunchKernelGGL(k_finalize<kPost>, dim3(1), dim3(kThreads), tab_shm, s, a);
   return hipGetLastError();
 }
 
