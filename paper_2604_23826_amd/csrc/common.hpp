@@ -441,13 +441,15 @@ struct FinalizeLaunch {
   int pca_on;
   int want_vectors;
   double* out;      // mean q, cov q*q, corr q*q, eigval q, eigvec q*q, var q, cum q
-  double* scratch;  // 2 q*q (Jacobi A and V)
-  double* jtab;     // q > 60: 5 * ceil(q / 2) (rotation tables of a round)
-  unsigned* jc;     // q > 60: 3 words (rotations, non-finite flag, pairs still to rotate)
+  double* scratch;  // finalize_scratch_words(q)
 };
-// Enqueues the finalize kernels on s.  Matrices above 60 x 60 run one kernel
-// pair per Jacobi round and wait on s after every sweep.
+// Device words launch_finalize needs as scratch for q columns.
+int64_t finalize_scratch_words(int q);
+// Enqueues the finalize kernels on s.  Above 60 columns (launch_finalize_wide)
+// it waits on s to learn whether the eigenpairs are accepted, and after every
+// sweep where the Jacobi method runs.
 hipError_t launch_finalize(const FinalizeLaunch& f, hipStream_t s);
+hipError_t launch_finalize_wide(const FinalizeLaunch& f, hipStream_t s);
 
 // Raw statistics as FP64: s_f64[p], C_f64[p*p] (full) from a state.
 void launch_raw(const uint64_t* state, int p, const uint8_t* intflags_dev, double* out,

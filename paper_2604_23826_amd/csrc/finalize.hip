@@ -17,24 +17,15 @@
 // (Correlation matrices up to 60 x 60 take Householder reduction and implicit QL
 // instead, see below.)
 //
-// One workgroup does the whole job.  The working matrices live in LDS when
-// they fit (q <= kLdsQ, every PCA of the narrow path), else in a global
-// scratch buffer that stays in L2; there each thread loads the 2 x 2 blocks
-// of several rotations before it writes any (the blocks of one round are
-// disjoint), so the L2 latency is paid once per batch.
-#include <type_traits>
-
+// Up to kLdsQ columns (every PCA of the narrow path) one workgroup does the
+// whole job with the matrices in LDS; eigen_wide.hip takes the rest.
 #include "common.hpp"
+#include "eigen.hpp"
 
 namespace st {
 namespace {
 
-constexpr int kThreads = 1024;
 constexpr int kLdsQ = 60;  // A and V in LDS up to this size (2 q^2 doubles <= 57.6 KiB)
-constexpr int kNB = 4;     // 2 x 2 blocks per thread and batch
-constexpr int kNV = 4;     // V row pairs per thread and batch
-constexpr int kMaxSweeps = 60;
-constexpr int kJThreads = 256;  // workgroup of the multi-kernel rounds
 
 struct Args {
   const uint64_t* state;
@@ -46,176 +37,12 @@ struct Args {
   int pca_on;
   int want_vectors;
   double* out;
-  double* scratch;
-  unsigned* jc;  // kPre / kPost: [0] rotations of a sweep, [1] no decomposition (non-finite
-                 // input, or n <= ddof),
-                 // [2] pairs that would still rotate after the sweep
 };
 
-// What one k_finalize launch does: everything with the matrices in LDS
-// (q <= kLdsQ; Householder and QL for a correlation matrix, Jacobi for a
-// covariance matrix), or the parts before and after the multi-kernel Jacobi.
-// A template parameter, so that LDS accesses are known to be that and the
-// small sizes fetch only the code they run.
-enum { kQl = 0, kLdsJacobi = 1, kPre = 2, kPost = 3 };
-
-// Round-robin schedule on m (even) players: player at position pos in round
-// r (0 <= pos < m, 0 <= r < m - 1).
-__device__ inline int rr_player(int pos, int r, int m) {
-  if (pos == 0) return 0;
-  const int x = pos - 1 + r;  // < 2 (m - 1)
-  return (x >= m - 1 ? x - (m - 1) : x) + 1;
-}
-
-// The two players of pair k in round r, smaller first.
-__device__ inline void rr_pair(int k, int r, int m, int& a, int& b) {
-  const int x = rr_player(k, r, m), y = rr_player(m - 1 - k, r, m);
-  a = min(x, y);
-  b = max(x, y);
-}
-
-// Rotation tables of one round: cosine, sine, tangent, the annihilated
-// element and the pair (a, b) of every pair k.
-struct RotTab {
-  double* c;
-  double* s;
-  double* t;
-  double* apq;
-  int2* pair;
-  __device__ static RotTab at(double* base, int npairs) {
-    return RotTab{base, base + npairs, base + 2 * npairs, base + 3 * npairs, (int2*)(base + 4 * npairs)};
-  }
-};
-
-// Whether the element apq of the pair with diagonal entries app, aqq is
-// rotated away: not when it is already negligible against them.
-__device__ inline bool rotates(double apq, double app, double aqq) {
-  const double tol = 2.220446049250313e-16;
-  return apq != 0.0 && fabs(apq) > tol * sqrt(fabs(app * aqq));
-}
-
-// Jacobi rotation annihilating A[a][b] (a < b < q), or none (c = 1, s = 0)
-// when the element is already negligible.  Returns whether it rotates.
-__device__ inline bool jacobi_rotation(const double* A, int q, int a, int b, double& c, double& s, double& t,
-                                       double& apq) {
-  c = 1.0;
-  s = t = 0.0;
-  apq = A[(int64_t)a * q + b];
-  const double app = A[(int64_t)a * q + a], aqq = A[(int64_t)b * q + b];
-  if (rotates(apq, app, aqq)) {
-    const double theta = (aqq - app) / (2.0 * apq);
-    t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(theta * theta + 1.0));
-    c = 1.0 / sqrt(t * t + 1.0);
-    s = t * c;
-    return true;
-  }
-  apq = 0.0;
-  return false;
-}
-
-// A <- J^T A J on the 2x2 blocks idx = u * npairs + v of one round (pair u
-// rows, pair v columns), idx = start, start + stride, ...  The blocks of a
-// round are disjoint, so a batch is loaded before it is written; (u, v)
-// advance by stride without division.
-__device__ inline void jacobi_blocks(double* A, int q, int npairs, const RotTab& R, int start, int stride) {
-  const int nblk = npairs * npairs;
-  const int du = stride / npairs, dv = stride % npairs;
-  int cu = start / npairs, cv = start % npairs;
-  for (int base = start; base < nblk; base += stride * kNB) {
-    double x[kNB][4];
-    int ia[kNB], ib[kNB], ic[kNB], id[kNB], iu[kNB], iv[kNB];
-#pragma unroll
-    for (int e = 0; e < kNB; ++e) {
-      iu[e] = cu;
-      iv[e] = cv;
-      cv += dv;
-      cu += du;
-      if (cv >= npairs) {
-        cv -= npairs;
-        ++cu;
-      }
-      x[e][0] = x[e][1] = x[e][2] = x[e][3] = 0.0;
-      ia[e] = ib[e] = ic[e] = id[e] = 0;
-      if (base + e * stride >= nblk) continue;
-      const int2 pu = R.pair[iu[e]], pv = R.pair[iv[e]];
-      ia[e] = pu.x;
-      ib[e] = pu.y;
-      ic[e] = pv.x;
-      id[e] = pv.y;
-      const bool bq = ib[e] < q, dq = id[e] < q;
-      x[e][0] = A[(int64_t)ia[e] * q + ic[e]];
-      if (dq) x[e][1] = A[(int64_t)ia[e] * q + id[e]];
-      if (bq) x[e][2] = A[(int64_t)ib[e] * q + ic[e]];
-      if (bq && dq) x[e][3] = A[(int64_t)ib[e] * q + id[e]];
-    }
-#pragma unroll
-    for (int e = 0; e < kNB; ++e) {
-      if (base + e * stride >= nblk) continue;
-      const int u = iu[e], v = iv[e];
-      const double cu_ = R.c[u], su = R.s[u], cv_ = R.c[v], sv = R.s[v];
-      if (su == 0.0 && sv == 0.0) continue;
-      const int a = ia[e], b = ib[e], c2 = ic[e], d2 = id[e];
-      const bool bq = b < q, dq = d2 < q;
-      const double x00 = x[e][0], x01 = x[e][1], x10 = x[e][2], x11 = x[e][3];
-      // rows: (row a, row b) <- (c row a - s row b, s row a + c row b)
-      const double y00 = cu_ * x00 - su * x10, y10 = su * x00 + cu_ * x10;
-      const double y01 = cu_ * x01 - su * x11, y11 = su * x01 + cu_ * x11;
-      // columns: (col c2, col d2) <- (c col c2 - s col d2, s col c2 + c col d2)
-      double z00 = cv_ * y00 - sv * y01, z01 = sv * y00 + cv_ * y01;
-      double z10 = cv_ * y10 - sv * y11, z11 = sv * y10 + cv_ * y11;
-      if (u == v && su != 0.0) {  // the rotated 2x2 block itself: exact update
-        const double t = R.t[u], apq = R.apq[u];
-        z00 = x00 - t * apq;
-        z11 = x11 + t * apq;
-        z01 = 0.0;
-        z10 = 0.0;
-      }
-      A[(int64_t)a * q + c2] = z00;
-      if (dq) A[(int64_t)a * q + d2] = z01;
-      if (bq) A[(int64_t)b * q + c2] = z10;
-      if (bq && dq) A[(int64_t)b * q + d2] = z11;
-    }
-  }
-}
-
-// V <- V J on the entries idx = row * npairs + u, batched the same way.
-__device__ inline void jacobi_vectors(double* V, int q, int npairs, const RotTab& R, int start, int stride) {
-  const int nv = q * npairs;
-  const int du = stride / npairs, dv = stride % npairs;
-  int vr = start / npairs, vu = start % npairs;
-  for (int base = start; base < nv; base += stride * kNV) {
-    double va[kNV], vb[kNV];
-    int jr[kNV], ju[kNV];
-#pragma unroll
-    for (int e = 0; e < kNV; ++e) {
-      jr[e] = vr;
-      ju[e] = vu;
-      vu += dv;
-      vr += du;
-      if (vu >= npairs) {
-        vu -= npairs;
-        ++vr;
-      }
-      va[e] = vb[e] = 0.0;
-      if (base + e * stride >= nv) continue;
-      const int2 pu = R.pair[ju[e]];
-      if (pu.y >= q) continue;  // the dummy player of odd q
-      va[e] = V[(int64_t)jr[e] * q + pu.x];
-      vb[e] = V[(int64_t)jr[e] * q + pu.y];
-    }
-#pragma unroll
-    for (int e = 0; e < kNV; ++e) {
-      if (base + e * stride >= nv) continue;
-      const int u = ju[e];
-      const double s = R.s[u];
-      if (s == 0.0) continue;  // also the dummy player's pair
-      const int2 pu = R.pair[u];
-      const double c = R.c[u];
-      V[(int64_t)jr[e] * q + pu.x] = c * va[e] - s * vb[e];
-      V[(int64_t)jr[e] * q + pu.y] = s * va[e] + c * vb[e];
-    }
-  }
-}
+// The method: Householder and QL for a correlation matrix, Jacobi for a
+// covariance matrix.  A template parameter, so that a launch fetches only the
+// code it runs.
+enum { kQl = 0, kLdsJacobi = 1 };
 
 // End of a sweep (after its last barrier): true when no pair would rotate,
 // i.e. the next sweep would change nothing, so stopping now gives the same
@@ -248,56 +75,11 @@ __device__ inline bool converged(const double* A, int q, int tid, int nth, int* 
 // two barriers.  Whole kernel, 9 x 9: 89 -> 38 us; 15 x 15: 168 -> 72 us.
 constexpr int kQlThreads = 256;
 
-// Ordering point between the lanes that share the work: the whole workgroup,
-// or (kWave) one wave, whose LDS accesses execute in order.
-template <bool kWave>
-__device__ inline void group_sync() {
-  if constexpr (kWave) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-  } else {
-    __syncthreads();
-  }
-}
-
-__device__ inline double lane_value(double v, int lane) {  // lane wave-uniform
-  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
-                          __builtin_amdgcn_readlane(__double2loint(v), lane));
-}
-
-// Sum over the four lanes of a quad, in every lane of it.
-__device__ inline double quad_sum(double v) {
-  auto move = [](double x, auto ctrl) {
-    constexpr int c = decltype(ctrl)::value;
-    return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(x), c, 0xF, 0xF, false),
-                            __builtin_amdgcn_update_dpp(0, __double2loint(x), c, 0xF, 0xF, false));
-  };
-  v += move(v, std::integral_constant<int, 0xB1>{});  // quad_perm [1,0,3,2]
-  v += move(v, std::integral_constant<int, 0x4E>{});  // quad_perm [2,3,0,1]
-  return v;
-}
-
-// 1 / sqrt(x) for normal x > 0: the hardware estimate and one third-order step.
-__device__ inline double rsqrt_f64(double x) {
-  const double y = __builtin_amdgcn_rsq(x);
-  const double e = __builtin_fma(-x * y, y, 1.0);
-  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
-}
-
-// Lane i receives lane i + 1's value (lane 63: zero).
-__device__ inline double next_lane(double v) {
-  return __hiloint2double(__builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xF, 0xF, true),
-                          __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xF, 0xF, true));
-}
-
 // Tridiagonal form of the symmetric matrix M (q x q, global or LDS) and the
 // orthogonal factor, transposed, in Zt (column j of it at Zt + j ld).  d[q],
 // e[q] (e[k] couples k and k + 1) and, as scratch, H (q x ld reflectors), beta[q]
-// and xp[256] in LDS.  Quad i of the threads holds row i of the working
-// matrix in registers (lane sub of it columns sub, sub + 4, ...), then column i
-// of the factor: 4 C >= q rows, 16 C threads.  A step exchanges row k and the
-// product through LDS, two ordering points in all.  Threads past 16 C take part
-// as empty rows (row < 64).
+// and xp[256] in LDS.  See tri_reduce for the threads' shares; here quad i then
+// holds column i of the factor.
 template <int C, bool kWave>
 __device__ inline void tridiagonalize(const double* M, double* Zt, double* H, int ld, int q, double* d, double* e,
                                       double* beta, double* xp, int tid) {
@@ -308,84 +90,7 @@ __device__ inline void tridiagonalize(const double* M, double* Zt, double* H, in
     const int j = sub + 4 * c;
     a[c] = row < q && j < q ? M[row * q + j] : 0.0;
   }
-  auto sum = [](const double (&u)[C], const double (&v)[C]) {  // over the quad's columns
-    double t0 = 0.0, t1 = 0.0;
-#pragma unroll
-    for (int c = 0; c < C; c += 2) {
-      t0 = __builtin_fma(u[c], v[c], t0);
-      t1 = __builtin_fma(u[c + 1], v[c + 1], t1);
-    }
-    return quad_sum(t0 + t1);
-  };
-  for (int k = 0; k + 1 < q; ++k) {
-    double* xb = xp + (k & 1) * 128;  // row k, then the product
-    double* pb = xb + 64;
-    if (row == k) {
-#pragma unroll
-      for (int c = 0; c < C; ++c) xb[sub + 4 * c] = a[c];
-    }
-    group_sync<kWave>();
-    const double x0 = xb[k + 1], xi = xb[row];
-    if (k + 2 == q) {
-      if (tid == 0) e[k] = x0;
-      break;
-    }
-    double v[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const int j = sub + 4 * c;
-      const double x = xb[j];
-      v[c] = j > k + 1 ? x : 0.0;
-    }
-    const double tail = sum(v, v);
-    if (tail < 1e-280) {  // already tridiagonal here (as far below any rounding)
-      if (row == k) {
-        if (sub == 0) {
-          beta[k] = 0.0;
-          e[k] = x0;
-        }
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-          if (sub + 4 * c < q) H[k * ld + sub + 4 * c] = 0.0;
-      }
-      continue;
-    }
-    const double n2 = __builtin_fma(x0, x0, tail), norm = n2 * rsqrt_f64(n2);
-    const double v0 = x0 >= 0.0 ? x0 + norm : x0 - norm;
-    const double bk = 1.0 / (norm * (norm + fabs(x0)));
-#pragma unroll
-    for (int c = 0; c < C; ++c)
-      if (sub + 4 * c == k + 1) v[c] = v0;
-    const bool in = row > k && row < q;
-    const double av = sum(a, v);
-    const double vi = row == k + 1 ? v0 : (in ? xi : 0.0);
-    const double pi = in ? bk * av : 0.0;
-    if (sub == 0) pb[row] = pi;
-    group_sync<kWave>();
-    double p[C];
-#pragma unroll
-    for (int c = 0; c < C; ++c) p[c] = pb[sub + 4 * c];
-    const double h = 0.5 * bk * sum(p, v);
-    const double wi = __builtin_fma(-h, vi, pi);
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const double wj = __builtin_fma(-h, v[c], p[c]);
-      a[c] -= __builtin_fma(vi, wj, wi * v[c]);
-    }
-    if (row == k) {
-      if (sub == 0) {
-        beta[k] = bk;
-        e[k] = x0 >= 0.0 ? -norm : norm;
-      }
-#pragma unroll
-      for (int c = 0; c < C; ++c)
-        if (sub + 4 * c < q) H[k * ld + sub + 4 * c] = v[c];
-    }
-  }
-#pragma unroll
-  for (int c = 0; c < C; ++c)
-    if (row < q && sub + 4 * c == row) d[row] = a[c];
-  if (tid == 0) e[q - 1] = 0.0;
+  tri_reduce<C, kWave, 64>(a, H, ld, q, d, e, beta, xp, tid);
   group_sync<kWave>();
   // H_0 H_1 ... from the last reflector on
   double z[C];
@@ -395,7 +100,7 @@ __device__ inline void tridiagonalize(const double* M, double* Zt, double* H, in
     double v[C];
 #pragma unroll
     for (int c = 0; c < C; ++c) v[c] = sub + 4 * c < q ? H[k * ld + sub + 4 * c] : 0.0;
-    const double t = beta[k] * sum(v, z);
+    const double t = beta[k] * quad_dot<C>(v, z);
 #pragma unroll
     for (int c = 0; c < C; ++c) z[c] = __builtin_fma(-t, v[c], z[c]);
   }
@@ -465,8 +170,8 @@ __device__ inline void implicit_ql(double* Zt, int ld, int q, double* dv, const 
   if (lane < q) dv[lane] = d;
 }
 
-template <int PHASE>
-__global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k_finalize(Args f) {
+template <int METHOD>
+__global__ __launch_bounds__(kQlThreads) void k_finalize(Args f) {
   const Layout L = Layout::make(f.p);
   const uint64_t* st = f.state;
   const int64_t n = (int64_t)st[0];
@@ -492,24 +197,14 @@ __global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k
   // (QL: d, e, beta, q each, and 256 words of exchange in their place, and rows
   // padded to an odd length above q)
   double* A;
-  if constexpr (PHASE == kQl) A = s_dyn + 3 * q + 256;
-  else if constexpr (PHASE == kLdsJacobi) A = s_dyn + 5 * npairs;
-  else A = f.scratch;
-  const int ld = PHASE == kQl ? (q + 1) | 1 : q;
+  if constexpr (METHOD == kQl) A = s_dyn + 3 * q + 256;
+  else A = s_dyn + 5 * npairs;
+  const int ld = METHOD == kQl ? (q + 1) | 1 : q;
   double* V = A + (int64_t)q * ld;
 
-  if constexpr (PHASE == kPost) {
-    if (f.jc[1]) return;  // no decomposition: see the pre phase
-  } else {
-  if (n <= f.ddof) {
-    // covariance undefined (the host reports it); nothing is computed, and
-    // the exact divisions by n and n - ddof are never reached
-    if (PHASE == kPre && tid == 0) {
-      f.jc[0] = 0;
-      f.jc[1] = 1;
-    }
-    return;
-  }
+  // covariance undefined (the host reports it); nothing is computed, and the
+  // exact divisions by n and n - ddof are never reached
+  if (n <= f.ddof) return;
   // ---- means and covariance ----
   const double dn = (double)(n - f.ddof);
   for (int a = tid; a < q; a += nth) {
@@ -555,17 +250,13 @@ __global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k
     const double v = M[idx];
     if (!isfinite(v)) bad = 1;
     const int i = idx / q, j = idx % q;
-    if constexpr (PHASE != kQl) {
+    if constexpr (METHOD != kQl) {
       A[i * ld + j] = v;
       V[idx] = i == j ? 1.0 : 0.0;
     }
   }
   if (bad) atomicOr(&s_flag, 1);
   __syncthreads();
-  if (PHASE == kPre && tid == 0) {
-    f.jc[0] = 0;
-    f.jc[1] = s_flag ? 1u : 0u;
-  }
   if (s_flag) {
     for (int idx = tid; idx < qq; idx += nth) evec[idx] = __builtin_nan("");
     for (int a = tid; a < q; a += nth) {
@@ -573,9 +264,7 @@ __global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k
     }
     return;
   }
-  if constexpr (PHASE == kPre) return;
-
-  if constexpr (PHASE == kQl) {
+  if constexpr (METHOD == kQl) {
     double *d = s_dyn, *e = d + q, *beta = e + q, *xp = beta + q;
     if (q <= 16) {  // one wave holds a quad per row
       if (tid < 64) tridiagonalize<4, true>(M, V, A, ld, q, d, e, beta, xp, tid);
@@ -586,7 +275,7 @@ __global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k
     }
     if (tid < 64) implicit_ql(V, ld, q, d, e, tid);
     __syncthreads();
-  } else if constexpr (PHASE == kLdsJacobi) {
+  } else {
   // ---- cyclic Jacobi, round-robin ordering: q/2 disjoint rotations per round ----
   if (nth == 64 && q <= 16) {
     // One wave, at most one 2x2 block and two V row pairs per lane.  Each
@@ -701,20 +390,19 @@ __global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k
   }
   }
   }
-  }  // all but kPost
 
   // ---- sort descending (ties: lower index first), sign rule, percentages ----
   // component j of eigenvector k at V + j vj + k vk; sorted eigenvalues and their
   // sources (complemented where the vector changes sign) in LDS that is free now
-  const int vj = PHASE == kQl ? 1 : q, vk = PHASE == kQl ? ld : 1;
-  double* lam = PHASE == kQl ? s_dyn + q : s_dyn;
-  double* var = PHASE == kQl ? s_dyn + 2 * q : s_dyn + q;
-  int* src = (int*)(s_dyn + (PHASE == kQl ? 3 : 2) * q);
+  const int vj = METHOD == kQl ? 1 : q, vk = METHOD == kQl ? ld : 1;
+  double* lam = METHOD == kQl ? s_dyn + q : s_dyn;
+  double* var = METHOD == kQl ? s_dyn + 2 * q : s_dyn + q;
+  int* src = (int*)(s_dyn + (METHOD == kQl ? 3 : 2) * q);
   for (int k = tid; k < q; k += nth) {
-    const double lk = PHASE == kQl ? s_dyn[k] : A[(int64_t)k * q + k];
+    const double lk = METHOD == kQl ? s_dyn[k] : A[(int64_t)k * q + k];
     int rank = 0;
     for (int j = 0; j < q; ++j) {
-      const double lj = PHASE == kQl ? s_dyn[j] : A[(int64_t)j * q + j];
+      const double lj = METHOD == kQl ? s_dyn[j] : A[(int64_t)j * q + j];
       rank += (lj > lk) || (lj == lk && j < k);
     }
     // eigenvector k's sign: largest |entry| positive (lowest index on ties)
@@ -750,52 +438,6 @@ __global__ __launch_bounds__(PHASE <= kLdsJacobi ? kQlThreads : kThreads) void k
     for (int j = 0; j <= k; ++j) run += var[j];
     cump[k] = run;
   }
-}
-
-// Multi-kernel Jacobi for q > kLdsQ (A and V in global memory): one round is
-// k_jrot (one workgroup: the round's rotation tables, and the count of
-// rotations) followed by k_japply (the 2x2 blocks of A and the rows of V,
-// spread over many workgroups).  Same arithmetic as the one-workgroup loop.
-__global__ __launch_bounds__(kThreads) void k_jrot(const double* __restrict__ A, int q, int m, int r,
-                                                   double* tab, unsigned* jc) {
-  const int npairs = m / 2;
-  const RotTab R = RotTab::at(tab, npairs);
-  unsigned cnt = 0;
-  for (int k = threadIdx.x; k < npairs; k += blockDim.x) {
-    int a, b;
-    rr_pair(k, r, m, a, b);
-    double c = 1.0, s = 0.0, t = 0.0, apq = 0.0;
-    if (!jc[1] && b < q && jacobi_rotation(A, q, a, b, c, s, t, apq)) ++cnt;
-    R.c[k] = c;
-    R.s[k] = s;
-    R.t[k] = t;
-    R.apq[k] = apq;
-    R.pair[k] = make_int2(a, b);
-  }
-  if (cnt) atomicAdd(&jc[0], cnt);
-}
-
-// End of a sweep: count (into jc[2]) the pairs that would still rotate; none
-// means the next sweep would change nothing.
-__global__ __launch_bounds__(kJThreads) void k_jcheck(const double* __restrict__ A, int q, unsigned* jc) {
-  const int64_t n = (int64_t)q * q;
-  unsigned any = 0;
-  for (int64_t idx = (int64_t)blockIdx.x * kJThreads + threadIdx.x; idx < n; idx += (int64_t)gridDim.x * kJThreads) {
-    const int i = (int)(idx / q), j = (int)(idx % q);
-    if (i < j && rotates(A[idx], A[(int64_t)i * q + i], A[(int64_t)j * q + j])) any = 1;
-  }
-  if (any) atomicOr(&jc[2], 1u);
-}
-
-__global__ __launch_bounds__(kJThreads) void k_japply(double* A, double* V, int q, int m, const double* tab) {
-  const int npairs = m / 2;
-  extern __shared__ double s_tab[];  // the round's tables, copied once
-  for (int i = threadIdx.x; i < 5 * npairs; i += kJThreads) s_tab[i] = tab[i];
-  __syncthreads();
-  const RotTab R = RotTab::at(s_tab, npairs);
-  const int start = blockIdx.x * kJThreads + threadIdx.x, stride = gridDim.x * kJThreads;
-  jacobi_blocks(A, q, npairs, R, start, stride);
-  jacobi_vectors(V, q, npairs, R, start, stride);
 }
 
 __global__ void k_raw(const uint64_t* st, int p, const uint8_t* intf, double* out) {
@@ -842,6 +484,7 @@ __global__ void k_raw(const uint64_t* st, int p, const uint8_t* intf, double* ou
 }  // namespace
 
 hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
+  if (F.q > kLdsQ) return launch_finalize_wide(F, s);
   Args a;
   a.state = F.state;
   a.p = F.p;
@@ -852,54 +495,15 @@ hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
   a.pca_on = F.pca_on;
   a.want_vectors = F.want_vectors;
   a.out = F.out;
-  a.scratch = F.scratch;
-  a.jc = F.jc;
-  const int npairs = (F.q + (F.q & 1)) / 2;
-  const size_t tab_shm = (size_t)npairs * 5 * sizeof(double);
-  if (F.q <= kLdsQ) {
-    if (!F.pca_on) {
-      const size_t shm = (256 + (3 + 2 * (size_t)((F.q + 1) | 1)) * (size_t)F.q) * sizeof(double);
-      hipLaunchKernelGGL(k_finalize<kQl>, dim3(1), dim3(kQlThreads), shm, s, a);
-    } else {
-      // one wave for the small matrices (its barriers cost nothing)
-      const size_t shm = tab_shm + 2 * sizeof(double) * (size_t)F.q * F.q;
-      hipLaunchKernelGGL(k_finalize<kLdsJacobi>, dim3(1), dim3(F.q <= 16 ? 64 : 256), shm, s, a);
-    }
-    return hipGetLastError();
+  const size_t q = (size_t)F.q;
+  if (!F.pca_on) {
+    const size_t shm = (256 + (3 + 2 * ((q + 1) | 1)) * q) * sizeof(double);
+    hipLaunchKernelGGL(k_finalize<kQl>, dim3(1), dim3(kQlThreads), shm, s, a);
+  } else {
+    // one wave for the small matrices (its barriers cost nothing)
+    const size_t shm = (5 * ((q + 1) / 2) + 2 * q * q) * sizeof(double);
+    hipLaunchKernelGGL(k_finalize<kLdsJacobi>, dim3(1), dim3(F.q <= 16 ? 64 : kQlThreads), shm, s, a);
   }
-  // wide matrices: the Jacobi rounds as separate kernels over the whole GPU,
-  // sweeps until one makes no rotation
-  hipLaunchKernelGGL(k_finalize<kPre>, dim3(1), dim3(kThreads), tab_shm, s, a);
-  hipError_t e = hipGetLastError();
-  double* A = F.scratch;
-  double* V = A + (int64_t)F.q * F.q;
-  const int m = 2 * npairs;
-  int dev = 0, ncu = 256;
-  if (e == hipSuccess) e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  const int64_t work = (int64_t)npairs * npairs + (int64_t)F.q * npairs;
-  const int nwg = (int)std::max<int64_t>(1, std::min<int64_t>((work + kJThreads * kNB - 1) / (kJThreads * kNB), 4 * ncu));
-  for (int sweep = 0; sweep < kMaxSweeps && F.q > 1 && e == hipSuccess; ++sweep) {
-    e = hipMemsetAsync(F.jc, 0, sizeof(unsigned), s);
-    for (int r = 0; r < m - 1 && e == hipSuccess; ++r) {
-      hipLaunchKernelGGL(k_jrot, dim3(1), dim3(kThreads), 0, s, A, F.q, m, r, F.jtab, F.jc);
-      hipLaunchKernelGGL(k_japply, dim3(nwg), dim3(kJThreads), tab_shm, s, A, V, F.q, m, F.jtab);
-      e = hipGetLastError();
-    }
-    // stop when this sweep rotated nothing, or when nothing would rotate in
-    // the next one (same result, one sweep earlier)
-    if (e == hipSuccess) e = hipMemsetAsync(F.jc + 2, 0, sizeof(unsigned), s);
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_jcheck, dim3(nwg), dim3(kJThreads), 0, s, A, F.q, F.jc);
-      e = hipGetLastError();
-    }
-    unsigned w[3] = {0, 0, 0};
-    if (e == hipSuccess) e = hipMemcpyAsync(w, F.jc, sizeof w, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess || w[0] == 0 || w[2] == 0) break;
-  }
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_finalize<kPost>, dim3(1), dim3(kThreads), tab_shm, s, a);
   return hipGetLastError();
 }
 

@@ -88,3 +88,35 @@ def test_one_workgroup(kind, q):
     print(f"eigen {kind} q={q}", flush=True)
     A = matrix(kind, q)
     check(A, finalize_of(A))
+
+
+@pytest.mark.parametrize("kind", ["random", "identity", "rank1", "equi", "near", "twins", "blocks"])
+@pytest.mark.parametrize("q", [61, 64, 100, 128, 129, 192, 256, 257])
+def test_whole_gpu(kind, q):
+    print(f"eigen {kind} q={q}", flush=True)
+    A = matrix(kind, q)
+    check(A, finalize_of(A))
+
+
+@pytest.mark.parametrize("q", [513, 1024])
+def test_whole_gpu_largest(q):
+    print(f"eigen random q={q}", flush=True)
+    A = matrix("random", q)
+    check(A, finalize_of(A))
+
+
+@pytest.mark.parametrize("q", [5, 61, 130])
+def test_covariance_stays_graded(q):
+    # eigenvalues of a covariance matrix over 12 decades keep their relative
+    # accuracy (the Jacobi method); a zero variance gives NaN eigenpairs
+    s = 10.0 ** np.linspace(0, -6, q)
+    A = matrix("random", q) * np.outer(s, s)
+    A = 0.5 * (A + A.T)
+    lam = finalize_of(A, pca_on=1)["eigval"]
+    # bounds from the scaled matrix: lambda_k / s_k^2 within its extreme eigenvalues
+    w = np.linalg.eigvalsh(unit(A))
+    assert np.all(lam / (s * s) >= w[0] * (1 - 1e-9)) and np.all(lam / (s * s) <= w[-1] * (1 + 1e-9))
+    A[1] = A[:, 1] = 0.0
+    for on in (0, 1):
+        fin = finalize_of(A, pca_on=on)
+        assert np.all(np.isnan(fin["corr"][1])) and np.all(np.isnan(fin["eigval"])) == (on == 0)
