@@ -445,8 +445,8 @@ struct FinalizeLaunch {
 };
 // Device words launch_finalize needs as scratch for q columns.
 int64_t finalize_scratch_words(int q);
-// Enqueues the finalize kernels on s.  Above 60 columns (launch_finalize_wide)
-// it waits on s to learn whether the eigenpairs are accepted, and after every
+// Enqueues the finalize kernels on s.  Where launch_finalize_wide takes
+// the columns it waits on s to learn whether the eigenpairs are accepted, and after every
 // sweep where the Jacobi method runs.
 hipError_t launch_finalize(const FinalizeLaunch& f, hipStream_t s);
 hipError_t launch_finalize_wide(const FinalizeLaunch& f, hipStream_t s);

@@ -1,5 +1,6 @@
-// Finalize of more than 60 columns over the whole GPU: covariance, correlation
-// and the eigenpairs of either, as a sequence of launches on the handle's
+// Finalize of more columns than one workgroup takes (24 of a correlation matrix,
+// 60 of a covariance matrix) over the whole GPU: covariance, correlation and
+// eigenpairs, as a sequence of launches on the handle's
 // stream (finalize.hip has the one-workgroup form and the conventions).
 //
 // Correlation matrix (unit diagonal, so errors small against its norm are all
@@ -658,7 +659,11 @@ __global__ __launch_bounds__(kJThreads) void k_correct(const double* __restrict_
 
 // A wave per eigenpair k: its rank (descending, ties by index), sign (entry of
 // largest magnitude positive, lowest index on ties), eigenvalue and vector.
+// Entries within kTie of the largest differ from it by the solver's rounding
+// only (the all-equal vector of collinear columns, say): they are ties, and are
+// returned equal, so that the sign does not hang on that rounding.
 // Eigenvalue j at lam + j ls, component j of vector k at V + j vj + k vk.
+constexpr double kTie = 1.0 - 8 * kEps;
 __global__ __launch_bounds__(kJThreads) void k_pairs(const double* __restrict__ lam, int ls,
                                                      const double* __restrict__ V, int64_t vj, int64_t vk, int q,
                                                      int want_vectors, double* out, const unsigned* jc) {
@@ -674,33 +679,29 @@ __global__ __launch_bounds__(kJThreads) void k_pairs(const double* __restrict__ 
   }
   const double lk = lam[(int64_t)k * ls];
   int rank = 0;
-  double best = -1.0, top = 0.0;
-  int arg = q;
+  double best = 0.0;
   for (int j = lane; j < q; j += 64) {
     const double lj = lam[(int64_t)j * ls];
     rank += (lj > lk) || (lj == lk && j < k);
-    const double x = V[j * vj + k * vk];
-    if (fabs(x) > best) {
-      best = fabs(x);
-      top = x;
-      arg = j;
-    }
+    best = fmax(best, fabs(V[j * vj + k * vk]));
   }
   for (int d = 32; d > 0; d >>= 1) {
     rank += __shfl_xor(rank, d, 64);
-    const double ob = __shfl_xor(best, d, 64), ot = __shfl_xor(top, d, 64);
-    const int oa = __shfl_xor(arg, d, 64);
-    if (ob > best || (ob == best && oa < arg)) {
-      best = ob;
-      top = ot;
-      arg = oa;
-    }
+    best = fmax(best, __shfl_xor(best, d, 64));
   }
+  const double tie = kTie * best;
+  int first = 2 * q;  // lowest tied index, doubled, odd where its entry is negative
+  for (int j = lane; j < q; j += 64) {
+    const double x = V[j * vj + k * vk];
+    if (fabs(x) >= tie) first = min(first, 2 * j + (x < 0.0));
+  }
+  for (int d = 32; d > 0; d >>= 1) first = min(first, __shfl_xor(first, d, 64));
   if (lane == 0) ev[rank] = lk;
   if (want_vectors) {
     for (int j = lane; j < q; j += 64) {
-      const double x = V[j * vj + k * vk];
-      evec[(int64_t)rank * q + j] = top < 0.0 ? -x : x;
+      double x = V[j * vj + k * vk];
+      if (fabs(x) >= tie) x = copysign(best, x);
+      evec[(int64_t)rank * q + j] = first & 1 ? -x : x;
     }
   }
 }
@@ -785,7 +786,7 @@ __global__ __launch_bounds__(kJThreads) void k_japply(double* A, double* V, int 
 }  // namespace
 
 int64_t finalize_scratch_words(int q) {
-  if (q <= 60) return 0;
+  if (q <= 24) return 0;  // one workgroup, in LDS
   const int64_t qq = (int64_t)q * q;
   // A, V (rows of eigenvectors or Jacobi's V), H, X, four LU arrays, row
   // exchanges, vectors (d, e, beta, lam, two products, rotation tables), flags

@@ -14,18 +14,17 @@
 // Table 3: eigenvalues descending, variance %, cumulative %, loadings (one
 // row per component).
 //
-// (Correlation matrices up to 60 x 60 take Householder reduction and implicit QL
-// instead, see below.)
-//
-// Up to kLdsQ columns (every PCA of the narrow path) one workgroup does the
-// whole job with the matrices in LDS; eigen_wide.hip takes the rest.
+// One workgroup does the whole job with the matrices in LDS up to kQlQ columns of
+// a correlation matrix (by Householder reduction and implicit QL, see below) and
+// up to kLdsQ columns of a covariance matrix (by Jacobi); eigen_wide.hip takes
+// the rest.
 #include "common.hpp"
 #include "eigen.hpp"
 
 namespace st {
 namespace {
 
-constexpr int kLdsQ = 60;  // A and V in LDS up to this size (2 q^2 doubles <= 57.6 KiB)
+constexpr int kLdsQ = 60;  // Jacobi: A and V in LDS up to this size (2 q^2 doubles <= 57.6 KiB)
 
 struct Args {
   const uint64_t* state;
@@ -60,7 +59,7 @@ __device__ inline bool converged(const double* A, int q, int tid, int nth, int* 
   return *cnt == 0;
 }
 
-// ---- correlation matrices up to 60 x 60: Householder + implicit QL -----------
+// ---- correlation matrices up to kQlQ columns: Householder + implicit QL --------
 //
 // A correlation matrix has a unit diagonal, so a solver whose errors are small
 // against its norm loses nothing on its small eigenvalues that Jacobi would
@@ -74,6 +73,10 @@ __device__ inline bool converged(const double* A, int q, int tid, int nth, int* 
 // Jacobi round (about 5 q of them) is three divisions, three square roots and
 // two barriers.  Whole kernel, 9 x 9: 89 -> 38 us; 15 x 15: 168 -> 72 us.
 constexpr int kQlThreads = 256;
+// The rotation chain grows with q^2, the launches of eigen_wide.hip with little
+// more than a constant: a whole finalize call takes 168 and 189 us at 20 columns,
+// 201 and 200 at 24, 251 and 220 at 28, 791 and 333 at 60.
+constexpr int kQlQ = 24;
 
 // Tridiagonal form of the symmetric matrix M (q x q, global or LDS) and the
 // orthogonal factor, transposed, in Zt (column j of it at Zt + j ld).  d[q],
@@ -268,10 +271,9 @@ __global__ __launch_bounds__(kQlThreads) void k_finalize(Args f) {
     double *d = s_dyn, *e = d + q, *beta = e + q, *xp = beta + q;
     if (q <= 16) {  // one wave holds a quad per row
       if (tid < 64) tridiagonalize<4, true>(M, V, A, ld, q, d, e, beta, xp, tid);
-    } else if (q <= 32) {
-      tridiagonalize<8, false>(M, V, A, ld, q, d, e, beta, xp, tid);
     } else {
-      tridiagonalize<16, false>(M, V, A, ld, q, d, e, beta, xp, tid);
+      static_assert(kQlQ <= 32, "eight columns per lane of a quad");
+      tridiagonalize<8, false>(M, V, A, ld, q, d, e, beta, xp, tid);
     }
     if (tid < 64) implicit_ql(V, ld, q, d, e, tid);
     __syncthreads();
@@ -484,7 +486,7 @@ __global__ void k_raw(const uint64_t* st, int p, const uint8_t* intf, double* ou
 }  // namespace
 
 hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
-  if (F.q > kLdsQ) return launch_finalize_wide(F, s);
+  if (F.q > (F.pca_on ? kLdsQ : kQlQ)) return launch_finalize_wide(F, s);
   Args a;
   a.state = F.state;
   a.p = F.p;
