@@ -397,6 +397,14 @@ __device__ inline double exact_mean(const uint64_t* st, const Layout& L, int i, 
   return u256_div_to_double(neg, u256_from_u128(m), u256_from_u128((u128)n));
 }
 
+// Element at an address that came out of a table in memory.  The compiler cannot
+// see that it is global and would use flat accesses, whose waits also cover the
+// LDS traffic around them.
+template <typename T>
+__device__ inline T load_global(const char* p) {
+  return *(const __attribute__((address_space(1))) T*)(const __attribute__((address_space(1))) char*)p;
+}
+
 // ---- kernel launchers (defined in the .hip files) ----------------------------
 
 struct AccumLaunch {

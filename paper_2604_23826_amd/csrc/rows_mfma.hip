@@ -68,9 +68,9 @@ __device__ inline typename Raw<KIND>::type load_raw(const Col& c, const char* p)
   if constexpr (KIND == K_MIX) {
     // two words; the second re-reads the first for 4-byte types
     const int hoff = (c.dt == STATS_I64 || c.dt == STATS_F64) ? 4 : 0;
-    return make_uint2(*(const uint32_t*)p, *(const uint32_t*)(p + hoff));
+    return make_uint2(load_global<uint32_t>(p), load_global<uint32_t>(p + hoff));
   } else {
-    return *(const typename Raw<KIND>::type*)p;
+    return load_global<typename Raw<KIND>::type>(p);
   }
 }
 

@@ -389,7 +389,7 @@ static void build_rowtiles(const int64_t* off, int ngroups, int64_t T, int64_t m
   (*gt)[ngroups] = (int64_t)tiles->size();
 }
 
-static int seg_prepare(stats_ctx* h, const void* const* planes, int ST, int64_t cap_rt,
+static int seg_prepare(stats_ctx* h, const void* const* planes, int64_t cap_rt,
                        SegBuffers* B, const std::vector<int2>& sts) {
   size_t need = 0;
   seg_layout(h, (int)sts.size(), cap_rt, &need);
@@ -423,7 +423,6 @@ static int seg_prepare(stats_ctx* h, const void* const* planes, int ST, int64_t 
   if (e == hipSuccess)
     e = hipMemcpyAsync(B->sts, sts.data(), sizeof(int2) * sts.size(), hipMemcpyHostToDevice, h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "uploading segment tables");
-  (void)ST;
   return STATS_OK;
 }
 
@@ -462,7 +461,7 @@ static int num_cus(int device) {
 
 // Times the persistent reduction alone on (a sample of) this call's rows for
 // each candidate tile height and occupancy; keeps the fastest per row.
-static int autotune(stats_ctx* h, const void* const* planes, const int64_t* off, int ST,
+static int autotune(stats_ctx* h, const void* const* planes, const int64_t* off,
                     const std::vector<int2>& sts, Tuned* best) {
   const bool aos64 = seg_aos64_layout(h, planes);
   const int64_t cands_T[] = {8192, 16384, 32768, 65536, 131072};
@@ -483,7 +482,7 @@ static int autotune(stats_ctx* h, const void* const* planes, const int64_t* off,
     int64_t rows = 0;
     for (const auto& t : tiles) rows += t.r1 - t.r0;
     SegBuffers B;
-    rc = seg_prepare(h, planes, ST, (int64_t)tiles.size(), &B, sts);
+    rc = seg_prepare(h, planes, (int64_t)tiles.size(), &B, sts);
     if (rc) break;
     const int64_t nt = (int64_t)tiles.size();
     rc = ensure_dev(h, (void**)&h->rec, &h->rec_cap, (size_t)(nt * rec_words(h->p) * 8));
@@ -560,11 +559,8 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
   DeviceGuard dg(h->device);
   if (!dg.ok) return fail(STATS_E_HIP, "hipSetDevice failed");
   const int p = h->p;
-  const int ST = p <= 32 ? 32 : 64;
-  const int ng = (p + ST - 1) / ST;
   std::vector<int2> sts;
-  for (int A = 0; A < ng; ++A)
-    for (int B = A; B < ng; ++B) sts.push_back(make_int2(A, B));
+  wide_pairs(p, wide::kWideGroup, &sts);
 
   // tile height and occupancy: configured, cached, or tuned now
   Tuned tu{h->block_rows, 4};
@@ -574,7 +570,7 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
     if (hipGetDeviceProperties(&prop, h->device) == hipSuccess) arch = prop.gcnArchName;
     const std::string key = tune_key(h, arch, seg_aos64_layout(h, planes));
     if (!tune_cache_lookup(key, &tu)) {
-      int rc = autotune(h, planes, row_offsets, ST, sts, &tu);
+      int rc = autotune(h, planes, row_offsets, sts, &tu);
       if (rc) return rc;
       tune_cache_store(key, tu);
     }
@@ -612,7 +608,7 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
     }
   }
   SegBuffers B;
-  int rc = seg_prepare(h, planes, ST, cap_rt, &B, sts);
+  int rc = seg_prepare(h, planes, cap_rt, &B, sts);
   if (rc) return rc;
   if (rec_need > h->rec_cap) {
     rc = ensure_dev(h, (void**)&h->rec, &h->rec_cap, rec_need);

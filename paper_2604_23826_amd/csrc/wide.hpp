@@ -1,5 +1,7 @@
 // Wide-table (p > 16) kernels: shared definitions.
 #pragma once
+#include <vector>
+
 #include "common.hpp"
 
 namespace st {
@@ -7,6 +9,7 @@ namespace wide {
 
 constexpr int kThreads = 256;
 constexpr int KR = 32;  // rows staged per step
+constexpr int kWideGroup = 128;  // columns per group of the FP64 kernels
 
 enum { MODE_FP64 = 0, MODE_SPLIT = 1 };
 
@@ -83,9 +86,14 @@ struct SyrkArgs {
 }  // namespace wide
 
 void launch_syrk_split(const wide::SyrkArgs& a, hipStream_t s);
-// FP64 records again for the blocks whose ovf flag is set (a.rec, a.R, a.nrows,
-// a.nblocks as for the launch that set them).
-void launch_wide_fixup(const wide::Args& a, int st, const int* ovf, hipStream_t s);
+// FP64 records (p > 32, or any p with ovf).  With ovf only of the blocks whose
+// flag is set (a.rec, a.R, a.nrows, a.nblocks as for the launch that set them).
+// a.tiles as wide_pairs(p, kWideGroup) lists them; kind: the STATS_* type of
+// every column, or 0.
+void launch_wide_f64(const wide::Args& a, int kind, const int* ovf, hipStream_t s);
+
+// Pairs (A, B), A <= B, of groups of `group` columns: the diagonal ones first.
+void wide_pairs(int p, int group, std::vector<int2>* tiles);
 
 // Persistent segmented launch of p > 32 columns (zeroes the queue first): nwg
 // workgroups.
@@ -97,8 +105,7 @@ void launch_seg_aos64(const wide::Args& a, const wide::SegArgs& g, int nwg, hipS
 // dtypes: the columns' STATS_* types.
 void launch_seg_rows(const wide::Args& a, const wide::SegArgs& g, const int32_t* dtypes, int nwg, hipStream_t s);
 
-// st = super-group width (32 or 64); mode = MODE_FP64 or MODE_SPLIT.
-void launch_wide(const wide::Args& a, int st, int mode, hipStream_t s);
+// General BF16 split kernel; st = super-group width (32 or 64).
 void launch_wide_split(const wide::Args& a, int st, hipStream_t s);
 
 }  // namespace st

@@ -83,12 +83,9 @@ static int accumulate_syrk(stats_ctx* h, const void* const* planes, int64_t nrow
   const int64_t W = rec_words(p);
   // records of one launch stay below ~1 GB
   const int64_t max_blocks = std::max<int64_t>(1, ((int64_t)1 << 30) / (W * 8));
-  // FP64 super-tiles of the blocks that are computed again (launch_wide_fixup)
-  const int ST = p <= 32 ? 32 : 64;
-  const int fng = (p + ST - 1) / ST;
+  // FP64 pairs of the blocks that are computed again
   std::vector<int2> tiles;
-  for (int A = 0; A < fng; ++A)
-    for (int B = A; B < fng; ++B) tiles.push_back(make_int2(A, B));
+  wide_pairs(p, wide::kWideGroup, &tiles);
   auto up = [](size_t n) { return (n + 255) / 256 * 256; };
   const size_t col_bytes = up(sizeof(int32_t) * (size_t)p);
   const size_t tile_bytes = up(sizeof(int2) * tiles.size());
@@ -178,7 +175,7 @@ static int accumulate_syrk(stats_ctx* h, const void* const* planes, int64_t nrow
     }
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "matrix-core kernel launch");
-    launch_wide_fixup(f, ST, ovf_dev, h->stream);
+    launch_wide_f64(f, 0, ovf_dev, h->stream);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "FP64 block launch");
     {
@@ -204,13 +201,14 @@ int accumulate_device_wide(stats_ctx* h, const void* const* planes, int64_t nrow
     if (syrk_layout(h, planes, &F, &xplane, &col_of))
       return accumulate_syrk(h, planes, nrows, F, xplane, col_of);
   }
-  const int ST = p <= 32 ? 32 : 64;
-  const int ng = (p + ST - 1) / ST;
   const int mode = h->precision == STATS_PREC_SPLIT ? wide::MODE_SPLIT : wide::MODE_FP64;
   if (mode == wide::MODE_FP64 && p <= 32) return accumulate_rows(h, planes, nrows, wide_block_rows(h, nrows), 0);
+  const int ST = p <= 32 ? 32 : 64;  // groups of the split kernel
   std::vector<int2> tiles;
-  for (int A = 0; A < ng; ++A)
-    for (int B = A; B < ng; ++B) tiles.push_back(make_int2(A, B));
+  wide_pairs(p, mode == wide::MODE_FP64 ? wide::kWideGroup : ST, &tiles);
+  int kind = h->cols[0].dtype;  // of every column, or 0
+  for (const auto& c : h->cols)
+    if (c.dtype != kind) kind = 0;
   const int64_t R = wide_block_rows(h, nrows);
   const int64_t W = rec_words(p);
   // records of one launch stay below ~256 MB
@@ -256,7 +254,8 @@ int accumulate_device_wide(stats_ctx* h, const void* const* planes, int64_t nrow
     {
       Timer t;
       t.begin(h, STATS_K_SYRK);
-      launch_wide(a, ST, mode, h->stream);
+      if (mode == wide::MODE_FP64) launch_wide_f64(a, kind, nullptr, h->stream);
+      else launch_wide_split(a, ST, h->stream);
       t.end();
     }
     e = hipGetLastError();
