@@ -13,10 +13,17 @@
 //     S = D^T V          S[i][j] = sum over rows with j present of d_i
 //     Q = (D o D)^T V    Q[i][j] = sum over rows with j present of d_i^2
 //     C = D^T D          sum of d_i d_j (zero wherever either is missing)
-// On the FP64 matrix cores (v_mfma_f64_16x16x4f64, p <= 16) a lane holds
-// d, d^2 and v of column (lane % 16) in row (lane / 16) of a 4-row step,
-// which is its element of both operands: four products per 4 rows.
+// S, Q and C on the FP64 matrix cores (v_mfma_f64_16x16x4, p <= 16): a lane holds
+// d, d^2 and v of one column in one row of a step, its element of both operands:
+// three products per 4 rows above 8 columns.  Up to 8 columns half of the A
+// operand is D and half D o D, half of B V and half D, so one product gives all
+// three; up to 4 columns it also takes two groups of 4 rows.  N is counted on the
+// int8 matrix cores, one product per 64 rows (the presence bits of 16 steps as
+// bytes).  The next steps' values are in flight while the current ones are
+// multiplied.  2e6 rows of 12 FP64 columns: 215 -> 71 us (four FP64 products per
+// step and no loads in flight before); the products' own time is 39 us, HBM's 27.
 #include <cstring>
+#include <type_traits>
 #include <vector>
 
 #include "common.hpp"
@@ -26,6 +33,7 @@ namespace st {
 namespace pw {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
+typedef int i4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kMaxP = 16;
@@ -43,77 +51,175 @@ struct Args {
   double* rec;
 };
 
-__device__ inline double load_value(const Args& a, int c, int64_t r) {
-  const char* ptr = a.colbase[c] + r * a.colstride[c];
-  return a.dtype[c] == STATS_F32 ? (double)__builtin_nontemporal_load((const float*)ptr)
-                                 : __builtin_nontemporal_load((const double*)ptr);
+constexpr int kU = 8;  // steps in flight per wave
+
+// Columns of a launch: all FP64, all FP32, or both (two words per value, the
+// second re-read for FP32).
+enum { K_F64 = 0, K_F32 = 1, K_MIX = 2 };
+template <int KIND> struct Raw { typedef double type; };
+template <> struct Raw<K_F32> { typedef float type; };
+template <> struct Raw<K_MIX> { typedef uint2 type; };
+
+template <int KIND>
+__device__ inline typename Raw<KIND>::type load_raw(const char* p, bool f32) {
+  if constexpr (KIND == K_MIX) return make_uint2(load_global<uint32_t>(p), load_global<uint32_t>(p + (f32 ? 0 : 4)));
+  else return load_global<typename Raw<KIND>::type>(p);
+}
+template <int KIND>
+__device__ inline double value(typename Raw<KIND>::type x, bool f32) {
+  if constexpr (KIND == K_MIX)
+    return f32 ? (double)__uint_as_float(x.x) : __longlong_as_double((long long)(((uint64_t)x.y << 32) | x.x));
+  else return (double)x;
 }
 
+// W: columns per operand part, 16, 8 or 4 (p <= W).
+template <int KIND, int W>
 __global__ __launch_bounds__(kThreads) void k_pairwise(Args a) {
+  typedef typename Raw<KIND>::type T;
+  constexpr int NT = W == 16 ? 3 : 1;     // FP64 tiles: S, Q, C, or one with all
+  constexpr int NG = W == 4 ? 2 : 1;      // row groups per product
+  constexpr int kStep = 4 * NG;           // rows per step
+  constexpr int kWave = kU * kStep;       // rows per wave and stage
   __shared__ double sK[kMaxP];
-  __shared__ double red[4][4][4][64];  // [wave][tile][register][lane]
+  __shared__ int s_first[kMaxP];
+  __shared__ double red[4][NT][4][64];  // [wave][tile][register][lane]
+  __shared__ int redn[4][4][64];
   const int64_t r0 = (int64_t)blockIdx.x * a.R, r1 = min(r0 + a.R, a.nrows);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int col = lane & 15, kq = lane >> 4;
-  const bool cv = col < a.p;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q16 = lane & 15;
+  const int p = a.p;
   // shift: the first present value of each column among the block's first rows
-  if (threadIdx.x < kMaxP) {
-    double K = 0.0;
-    if ((int)threadIdx.x < a.p) {
-      const int64_t lim = min(r1, r0 + kScan);
-      for (int64_t r = r0; r < lim; ++r) {
-        const double x = load_value(a, threadIdx.x, r);
-        if (x == x) {
-          K = x;
-          break;
-        }
+  {
+    const int c = tid & 15, cc = c < p ? c : 0;
+    const bool f32 = a.dtype[cc] == STATS_F32;
+    const int lim = (int)min((int64_t)kScan, r1 - r0);
+    if (tid < kMaxP) s_first[tid] = INT32_MAX;
+    __syncthreads();
+    for (int k = tid >> 4; k - (tid >> 4) < lim; k += 16) {
+      bool found = c >= p;
+      if (!found && k < lim) {
+        const double x = value<KIND>(load_raw<KIND>(a.colbase[cc] + (r0 + k) * a.colstride[cc], f32), f32);
+        if (x == x) atomicMin(&s_first[c], k);
+      }
+      __syncthreads();
+      found = found || s_first[c] != INT32_MAX;
+      if (__syncthreads_and(found)) break;
+    }
+    if (tid < kMaxP) {
+      double K = 0.0;
+      if (tid < p && s_first[tid] != INT32_MAX)
+        K = value<KIND>(load_raw<KIND>(a.colbase[tid] + (r0 + s_first[tid]) * a.colstride[tid], f32), f32);
+      sK[tid] = K;
+    }
+    __syncthreads();
+  }
+  const int col = q16 % W, part = W == 16 ? 0 : q16 / W % 2;  // part 1: d^2 in A, d in B
+  const int rl = (lane >> 4) + (NG == 2 ? 4 * (q16 / 8) : 0);  // row of a step
+  const bool cv = col < p;
+  const int cc = cv ? col : 0;
+  const bool f32 = a.dtype[cc] == STATS_F32;
+  const int64_t stride = a.colstride[cc];
+  const double K = sK[cc];
+  d4 tile[NT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) tile[t] = (d4){0.0, 0.0, 0.0, 0.0};
+  i4 tn = {0, 0, 0, 0};
+  i4 bits = {0, 0, 0, 0};  // presence bytes of 16 steps
+  const char* pc = a.colbase[cc] + (r0 + kWave * wave + rl) * stride;
+  const int64_t step = kStep * stride, sstep = (int64_t)4 * kWave * stride;
+  auto load = [&](T (&x)[kU]) {
+#pragma unroll
+    for (int u = 0; u < kU; ++u) x[u] = load_raw<KIND>(pc + u * step, f32);
+    pc += sstep;
+  };
+  // half: which eight of the sixteen presence bytes these steps fill; rows at or
+  // past `rows` (relative to this wave's first) are absent
+  auto use = [&](const T (&x)[kU], int rows, auto half_c) {
+    constexpr int half = decltype(half_c)::value;
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const double y = value<KIND>(x[u], f32);
+      const bool ok = cv && y == y && kStep * u + rl < rows;
+      const double d = ok ? y - K : 0.0, v = ok ? 1.0 : 0.0, d2 = d * d;
+      constexpr int base = half * kU;
+      bits[(base + u) / 4] |= ok ? 1 << (8 * ((base + u) % 4)) : 0;
+      if constexpr (NT == 3) {
+        tile[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(d, v, tile[0], 0, 0, 0);
+        tile[1] = __builtin_amdgcn_mfma_f64_16x16x4f64(d2, v, tile[1], 0, 0, 0);
+        tile[2] = __builtin_amdgcn_mfma_f64_16x16x4f64(d, d, tile[2], 0, 0, 0);
+      } else {
+        tile[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(part ? d2 : d, part ? d : v, tile[0], 0, 0, 0);
       }
     }
-    sK[threadIdx.x] = K;
+  };
+  auto count = [&]() {
+    tn = __builtin_amdgcn_mfma_i32_16x16x64_i8(bits, bits, tn, 0, 0, 0);
+    bits = (i4){0, 0, 0, 0};
+  };
+  using H0 = std::integral_constant<int, 0>;
+  using H1 = std::integral_constant<int, 1>;
+  const int64_t nst = (r1 - r0) / (4 * kWave);  // whole stages
+  T xa[kU], xb[kU];
+  if (nst > 0) load(xa);
+  for (int64_t t = 0; t < nst; t += 2) {
+    if (t + 1 < nst) load(xb);
+    use(xa, kWave, H0{});
+    if (t + 1 < nst) {
+      if (t + 2 < nst) load(xa);
+      use(xb, kWave, H1{});
+    }
+    count();
   }
-  __syncthreads();
-  const double K = cv ? sK[col] : 0.0;
-  d4 tN = {}, tS = {}, tQ = {}, tC = {};
-  // wave w takes rows r0 + 4 (w + 4 s) + kq: 16 rows per step of the workgroup
-  constexpr int U = 4;  // steps in flight per wave
-  for (int64_t base = r0 + 4 * wave; base < r1; base += 16 * U) {
-    double x[U];
+  const int64_t rb = r0 + nst * 4 * kWave + kWave * wave;  // this wave's rows of the last stage
+  if (rb < r1) {
+    const int rows = (int)min((int64_t)kWave, r1 - rb);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t r = base + 16 * u + kq;
-      x[u] = (cv && r < r1) ? load_value(a, col, r) : __builtin_nan("");
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool ok = x[u] == x[u];
-      const double d = ok ? x[u] - K : 0.0;
-      const double v = ok ? 1.0 : 0.0;
-      const double d2 = d * d;
-      tN = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, tN, 0, 0, 0);
-      tS = __builtin_amdgcn_mfma_f64_16x16x4f64(d, v, tS, 0, 0, 0);
-      tQ = __builtin_amdgcn_mfma_f64_16x16x4f64(d2, v, tQ, 0, 0, 0);
-      tC = __builtin_amdgcn_mfma_f64_16x16x4f64(d, d, tC, 0, 0, 0);
-    }
+    for (int u = 0; u < kU; ++u)
+      xa[u] = load_raw<KIND>(a.colbase[cc] + (rb + min(kStep * u + rl, rows - 1)) * stride, f32);
+    use(xa, rows, H0{});
+    count();
   }
   // the four waves' tiles, added in a fixed order
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    red[wave][0][k][lane] = tN[k];
-    red[wave][1][k][lane] = tS[k];
-    red[wave][2][k][lane] = tQ[k];
-    red[wave][3][k][lane] = tC[k];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) red[wave][t][k][lane] = tile[t][k];
+    redn[wave][k][lane] = tn[k];
   }
   __syncthreads();
   double* out = a.rec + (int64_t)blockIdx.x * kRecWords;
-  // register k of lane l holds D[4 k + l / 16][l % 16]
-  for (int e = threadIdx.x; e < 4 * 4 * 64; e += kThreads) {
-    const int t = e >> 8, k = (e >> 6) & 3, l = e & 63;
-    const double v = red[0][t][k][l] + red[1][t][k][l] + red[2][t][k][l] + red[3][t][k][l];
-    const int i = 4 * k + (l >> 4), j = l & 15;
-    out[1 + kMaxP + 256 * t + 16 * i + j] = v;
+  // element (x, y) of FP64 tile t: register x / 4 of lane 16 (x % 4) + y; of the
+  // int32 tile: register x % 4 of lane 16 (x / 4) + y
+  auto at = [&](int t, int x, int y) {
+    const int k = x >> 2, l = 16 * (x & 3) + y;
+    return red[0][t][k][l] + red[1][t][k][l] + red[2][t][k][l] + red[3][t][k][l];
+  };
+  for (int e = tid; e < W * W; e += kThreads) {
+    const int i = e / W, j = e % W;
+    double S = 0.0, Q = 0.0, C = 0.0;
+    int n = 0;
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const int o = 2 * W * g;  // first operand column of the row group
+      if constexpr (NT == 3) {
+        S = at(0, i, j);
+        Q = at(1, i, j);
+        C = at(2, i, j);
+      } else {
+        S += at(0, o + i, o + j);
+        Q += at(0, o + W + i, o + j);
+        C += at(0, o + i, o + W + j);
+      }
+      const int k = (o + i) & 3, l = 16 * ((o + i) >> 2) + o + j;
+      n += redn[0][k][l] + redn[1][k][l] + redn[2][k][l] + redn[3][k][l];
+    }
+    double* rec = out + 1 + kMaxP + 16 * i + j;
+    rec[0] = (double)n;
+    rec[256] = S;
+    rec[512] = Q;
+    rec[768] = C;
   }
-  if (threadIdx.x < kMaxP) out[1 + threadIdx.x] = sK[threadIdx.x];
-  if (threadIdx.x == 0) out[0] = (double)(r1 - r0);
+  if (tid < kMaxP) out[1 + tid] = sK[tid];
+  if (tid == 0) out[0] = (double)(r1 - r0);
 }
 
 // ---- merge: block records -> per-pair state, states -> state ----------------
@@ -248,6 +354,22 @@ __global__ void k_pw_finalize(const double* st, int p, int ddof, double* out) {
 
 // ---- host ----------------------------------------------------------------------
 
+template <int KIND>
+static void go_pairwise(const pw::Args& a, int64_t nblocks, hipStream_t s) {
+  const dim3 grid((unsigned)nblocks), block(pw::kThreads);
+  if (a.p <= 4) hipLaunchKernelGGL((pw::k_pairwise<KIND, 4>), grid, block, 0, s, a);
+  else if (a.p <= 8) hipLaunchKernelGGL((pw::k_pairwise<KIND, 8>), grid, block, 0, s, a);
+  else hipLaunchKernelGGL((pw::k_pairwise<KIND, 16>), grid, block, 0, s, a);
+}
+
+static void launch_pairwise(const pw::Args& a, int64_t nblocks, hipStream_t s) {
+  int n32 = 0;
+  for (int c = 0; c < a.p; ++c) n32 += a.dtype[c] == STATS_F32;
+  if (n32 == 0) go_pairwise<pw::K_F64>(a, nblocks, s);
+  else if (n32 == a.p) go_pairwise<pw::K_F32>(a, nblocks, s);
+  else go_pairwise<pw::K_MIX>(a, nblocks, s);
+}
+
 int pairwise_state_words(int p) { return 6 * p * (p + 1) / 2; }
 
 int accumulate_pairwise(stats_ctx* h, const void* const* planes, int64_t nrows) {
@@ -278,7 +400,7 @@ int accumulate_pairwise(stats_ctx* h, const void* const* planes, int64_t nrows) 
     {
       Timer t;
       t.begin(h, STATS_K_ACCUM);
-      hipLaunchKernelGGL(pw::k_pairwise, dim3((unsigned)nblocks), dim3(pw::kThreads), 0, h->stream, b);
+      launch_pairwise(b, nblocks, h->stream);
       t.end();
     }
     hipError_t e = hipGetLastError();
