@@ -78,6 +78,36 @@ int ensure_dev(stats_ctx* h, void** ptr, size_t* cap, size_t need) {
   return STATS_OK;
 }
 
+// The same for page-locked host memory (no work of the handle may still use it).
+int ensure_pin(stats_ctx* h, void** ptr, size_t* cap, size_t need) {
+  (void)h;
+  if (*cap >= need && *ptr) return STATS_OK;
+  if (*ptr) {
+    (void)hipHostFree(*ptr);
+    *ptr = nullptr;
+    *cap = 0;
+  }
+  need = (need + 16383) / 16384 * 16384;
+  if (hipHostMalloc(ptr, need, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    *ptr = nullptr;
+    return fail(STATS_E_NOMEM, "hipHostMalloc of " + std::to_string(need) + " bytes failed");
+  }
+  *cap = need;
+  return STATS_OK;
+}
+
+// Column selection on the device; copied only when it is another one.
+int upload_selection(stats_ctx* h, const std::vector<int32_t>& sel) {
+  if (h->sel_dev && h->sel_host == sel) return STATS_OK;
+  int rc = ensure_dev(h, (void**)&h->sel_dev, &h->sel_cap, sel.size() * 4);
+  if (rc) return rc;
+  h->sel_host = sel;
+  hipError_t e = hipMemcpyAsync(h->sel_dev, h->sel_host.data(), sel.size() * 4, hipMemcpyHostToDevice, h->stream);
+  if (e != hipSuccess) return hip_fail(h, e, "uploading selection");
+  return STATS_OK;
+}
+
 void Timer::begin(stats_ctx* h, int which, hipStream_t s) {
   if (!(h->flags & STATS_CFG_TIMING)) return;
   hipEvent_t a, b;
@@ -120,7 +150,7 @@ hipError_t clear_status(stats_ctx* h) {
 }
 
 // The error recorded in a status word read back from the device, if any.
-static int status_error(const DevStatus& s) {
+int status_error(const DevStatus& s) {
   if (s.bits & ST_PARSE) {
     char buf[128];
     snprintf(buf, sizeof buf, "malformed text field at byte offset %llu",
@@ -307,6 +337,9 @@ extern "C" void stats_close(stats_ctx* h) {
     if (h->ev_copy[k]) (void)hipEventDestroy(h->ev_copy[k]);
     if (h->ev_free[k]) (void)hipEventDestroy(h->ev_free[k]);
   }
+  if (h->pin_out) (void)hipHostFree(h->pin_out);
+  if (h->pin_tab) (void)hipHostFree(h->pin_tab);
+  if (h->ev_tab) (void)hipEventDestroy(h->ev_tab);
   if (h->graph_exec) (void)hipGraphExecDestroy(h->graph_exec);
   if (h->graph) (void)hipGraphDestroy(h->graph);
   if (h->copy_stream) (void)hipStreamDestroy(h->copy_stream);
@@ -725,9 +758,8 @@ extern "C" int stats_reset(stats_ctx* h) {
   if (!h) return fail(STATS_E_ARG, "handle is NULL");
   if (h->poisoned) return fail(STATS_E_STATE, "handle is poisoned by an earlier HIP error");
   DeviceGuard g(h->device);
-  const size_t bytes = (size_t)state_words(h) * 8 * (size_t)(h->ngroups > 0 ? h->ngroups : 1);
-  hipError_t e = hipMemsetAsync(h->state[h->cur], 0, bytes, h->stream);
-  if (e == hipSuccess) e = clear_status(h);
+  launch_reset(h->state[h->cur], state_words(h) * (int64_t)(h->ngroups > 0 ? h->ngroups : 1), h->status_dev, h->stream);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "stats_reset");
   h->text_offset = 0;
   return STATS_OK;
@@ -914,13 +946,12 @@ extern "C" int stats_finalize(stats_ctx* h, const stats_finalize_opts* opts, int
   // (the kernel computes nothing when N <= ddof)
   const int q = (int)sel.size();
   const size_t out_words = (size_t)q * 4 + 3 * (size_t)q * q;
-  rc = ensure_dev(h, (void**)&h->fin_out, &h->fin_out_cap, out_words * 8);
+  rc = ensure_dev(h, (void**)&h->fin_out, &h->fin_out_cap, (out_words + 3) * 8);
   const size_t scratch_words = (size_t)finalize_scratch_words(q);
   if (!rc && scratch_words) rc = ensure_dev(h, (void**)&h->fin_scratch, &h->fin_scratch_cap, scratch_words * 8);
-  if (!rc) rc = ensure_dev(h, (void**)&h->sel_dev, &h->sel_cap, (size_t)q * 4);
+  if (!rc) rc = ensure_pin(h, &h->pin_out, &h->pin_out_cap, (out_words + 3) * 8);
+  if (!rc) rc = upload_selection(h, sel);
   if (rc) return rc;
-  hipError_t e = hipMemcpyAsync(h->sel_dev, sel.data(), (size_t)q * 4, hipMemcpyHostToDevice, h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "uploading selection");
   FinalizeLaunch F;
   F.state = h->state[h->cur];
   F.p = h->p;
@@ -932,28 +963,28 @@ extern "C" int stats_finalize(stats_ctx* h, const stats_finalize_opts* opts, int
   F.want_vectors = o->want_vectors ? 1 : 0;
   F.out = h->fin_out;
   F.scratch = h->fin_scratch;
+  F.status = h->status_dev;
+  F.host = (double*)h->pin_out;
+  hipError_t e;
   {
     Timer t;
     t.begin(h, STATS_K_FINALIZE);
     e = launch_finalize(F, h->stream);
     t.end();
   }
-  if (e != hipSuccess) return hip_fail(h, e, "finalize");
-  std::vector<double> out(out_words);
-  int64_t n = 0;
-  DevStatus st;
-  e = hipMemcpyAsync(out.data(), h->fin_out, out_words * 8, hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&n, h->state[h->cur], 8, hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(&st, h->status_dev, sizeof st, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e == hipSuccess && h->copy_stream) e = hipStreamSynchronize(h->copy_stream);
   if (e != hipSuccess) return hip_fail(h, e, "finalize");
   collect_timings(h);
+  const double* po = F.host;
+  int64_t n;
+  DevStatus st;
+  memcpy(&n, po + out_words, 8);
+  memcpy(&st, po + out_words + 1, sizeof st);
   rc = status_error(st);
   if (rc) return rc;
   if (n <= o->ddof) return fail(STATS_E_STATE, "N <= ddof: covariance undefined");
   const size_t qq = (size_t)q * q;
-  const double* po = out.data();
   if (p_out) *p_out = q;
   if (mean) memcpy(mean, po, q * 8);
   if (cov) memcpy(cov, po + q, qq * 8);

@@ -435,6 +435,9 @@ int64_t merge_slice_words(int64_t nblocks, int p);
 // dst status |= src status (stream-ordered; see k_status_or).
 void launch_status_or(DevStatus* dst, const DevStatus* src, hipStream_t s);
 
+// state[0 .. words) = 0 and a clear status word.
+void launch_reset(uint64_t* state, int64_t words, DevStatus* status, hipStream_t s);
+
 // Merge two states: out = merge(a, b).
 void launch_merge_states(const uint64_t* a, const uint64_t* b, uint64_t* out, int p,
                          const uint8_t* intflags_dev, hipStream_t s);
@@ -450,10 +453,12 @@ struct FinalizeLaunch {
   int want_vectors;
   double* out;      // mean q, cov q*q, corr q*q, eigval q, eigvec q*q, var q, cum q
   double* scratch;  // finalize_scratch_words(q)
+  const DevStatus* status;
+  double* host;     // page-locked: out, then N and the two words of the status
 };
 // Device words launch_finalize needs as scratch for q columns.
 int64_t finalize_scratch_words(int q);
-// Enqueues the finalize kernels on s.  Where launch_finalize_wide takes
+// Enqueues the finalize kernels on s; F.host is filled when s has run.  Where launch_finalize_wide takes
 // the columns it waits on s to learn whether the eigenpairs are accepted, and after every
 // sweep where the Jacobi method runs.
 hipError_t launch_finalize(const FinalizeLaunch& f, hipStream_t s);

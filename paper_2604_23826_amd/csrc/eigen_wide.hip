@@ -51,11 +51,16 @@ enum : unsigned { NONE_NAN = 1u, NONE_N = 2u };  // J_NONE: non-finite input; n 
 // ---- covariance, correlation ---------------------------------------------------
 
 __global__ __launch_bounds__(kJThreads) void k_cov(const uint64_t* st, int p, const int32_t* sel, int q,
-                                                   const uint8_t* intf, int ddof, double* out, unsigned* jc) {
+                                                   const uint8_t* intf, int ddof, const DevStatus* status, double* out,
+                                                   unsigned* jc) {
   const Layout L = Layout::make(p);
   const int64_t n = (int64_t)st[0];
   const int first = blockIdx.x * kJThreads + threadIdx.x;
   if (first == 0) {
+    double* tail = out + 4 * q + 3 * (int64_t)q * q;  // N and the status word
+    tail[0] = __longlong_as_double(n);
+    tail[1] = __longlong_as_double((long long)status->bits);
+    tail[2] = __longlong_as_double((long long)status->parse_off);
     jc[J_ROT] = jc[J_LEFT] = jc[J_REJECT] = 0;
     jc[J_NONE] = n <= ddof ? NONE_N : 0;
   }
@@ -810,7 +815,7 @@ hipError_t launch_finalize_wide(const FinalizeLaunch& F, hipStream_t s) {
   if (err == hipSuccess) err = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
   if (err != hipSuccess) return err;
   const dim3 grid((unsigned)std::min<int64_t>((qq + kJThreads - 1) / kJThreads, 4 * ncu)), block(kJThreads);
-  hipLaunchKernelGGL(k_cov, grid, block, 0, s, F.state, F.p, F.sel_dev, q, F.intflags_dev, F.ddof, F.out, jc);
+  hipLaunchKernelGGL(k_cov, grid, block, 0, s, F.state, F.p, F.sel_dev, q, F.intflags_dev, F.ddof, F.status, F.out, jc);
   hipLaunchKernelGGL(k_corr, grid, block, 0, s, F.out, q, F.pca_on, A, jc);
   unsigned w[4] = {0, 0, 0, 0};
   bool done = false;
@@ -882,7 +887,9 @@ hipError_t launch_finalize_wide(const FinalizeLaunch& F, hipStream_t s) {
   if (done) hipLaunchKernelGGL(k_pairs, gk, block, 0, s, lam, 1, X, (int64_t)1, (int64_t)q, q, F.want_vectors, F.out, jc);
   else hipLaunchKernelGGL(k_pairs, gk, block, 0, s, A, q + 1, V, (int64_t)q, (int64_t)1, q, F.want_vectors, F.out, jc);
   hipLaunchKernelGGL(k_percent, dim3(1), dim3(kThreads), 2 * sizeof(double) * (size_t)q, s, F.out, q, jc);
-  return hipGetLastError();
+  err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  return hipMemcpyAsync(F.host, F.out, (size_t)(4 * q + 3 * qq + 3) * sizeof(double), hipMemcpyDeviceToHost, s);
 }
 
 }  // namespace st

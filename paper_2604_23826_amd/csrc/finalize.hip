@@ -36,6 +36,8 @@ struct Args {
   int pca_on;
   int want_vectors;
   double* out;
+  const DevStatus* status;
+  double* host;
 };
 
 // The method: Householder and QL for a correlation matrix, Jacobi for a
@@ -173,8 +175,15 @@ __device__ inline void implicit_ql(double* Zt, int ld, int q, double* dv, const 
   if (lane < q) dv[lane] = d;
 }
 
+// N and the status word behind the outputs.
+__device__ inline void put_tail(double* to, const uint64_t* state, const DevStatus* status) {
+  to[0] = __longlong_as_double((long long)state[0]);
+  to[1] = __longlong_as_double((long long)status->bits);
+  to[2] = __longlong_as_double((long long)status->parse_off);
+}
+
 template <int METHOD>
-__global__ __launch_bounds__(kQlThreads) void k_finalize(Args f) {
+__device__ inline void finalize_body(const Args& f) {
   const Layout L = Layout::make(f.p);
   const uint64_t* st = f.state;
   const int64_t n = (int64_t)st[0];
@@ -442,6 +451,17 @@ __global__ __launch_bounds__(kQlThreads) void k_finalize(Args f) {
   }
 }
 
+// The outputs go to page-locked host memory from here: a copy command and its wait
+// cost more than these stores.
+template <int METHOD>
+__global__ __launch_bounds__(kQlThreads) void k_finalize(Args f) {
+  finalize_body<METHOD>(f);
+  __syncthreads();
+  const int words = 4 * f.q + 3 * f.q * f.q;
+  for (int i = threadIdx.x; i < words; i += blockDim.x) f.host[i] = f.out[i];
+  if (threadIdx.x == 0) put_tail(f.host + words, f.state, f.status);
+}
+
 __global__ void k_raw(const uint64_t* st, int p, const uint8_t* intf, double* out) {
   // out: s_f64[p], C_f64[p*p]
   const Layout L = Layout::make(p);
@@ -497,6 +517,8 @@ hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
   a.pca_on = F.pca_on;
   a.want_vectors = F.want_vectors;
   a.out = F.out;
+  a.status = F.status;
+  a.host = F.host;
   const size_t q = (size_t)F.q;
   if (!F.pca_on) {
     const size_t shm = (256 + (3 + 2 * ((q + 1) | 1)) * q) * sizeof(double);

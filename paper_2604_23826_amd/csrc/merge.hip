@@ -23,6 +23,8 @@
 // the result is deterministic.  The column means needed by a pair are recomputed by the
 // pair's owner with the same operations as the column's owner, hence
 // bitwise equal.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace st {
@@ -495,7 +497,22 @@ __global__ void k_status_or(DevStatus* dst, const DevStatus* src) {
   }
 }
 
+// A handle's statistics cleared: one launch instead of a fill and
+// a copy from the host.
+__global__ __launch_bounds__(256) void k_reset(uint64_t* state, int64_t words, DevStatus* status) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; 2 * i < words; i += (int64_t)gridDim.x * 256) {
+    state[2 * i] = 0;
+    if (2 * i + 1 < words) state[2 * i + 1] = 0;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *status = DevStatus{0u, 0u, ~0ull};
+}
+
 }  // namespace
+
+void launch_reset(uint64_t* state, int64_t words, DevStatus* status, hipStream_t s) {
+  const unsigned blocks = (unsigned)std::min<int64_t>(std::max<int64_t>((words + 511) / 512, 1), 1024);
+  hipLaunchKernelGGL(k_reset, dim3(blocks), dim3(256), 0, s, state, words, status);
+}
 
 // Slices of the split merge (1: the one-pass form).  Up to 256 entries and
 // from 8192 records, a workgroup folds each slice of 64 records for all

@@ -442,6 +442,7 @@ extern "C" int stats_finalize_pairwise(stats_ctx* h, int32_t ddof, int64_t* n_ou
   if (!g.ok) return fail(STATS_E_HIP, "hipSetDevice failed");
   const size_t words = (size_t)3 * p * p + p;
   int rc = ensure_dev(h, (void**)&h->fin_out, &h->fin_out_cap, words * 8);
+  if (!rc) rc = ensure_pin(h, &h->pin_out, &h->pin_out_cap, words * 8);
   if (rc) return rc;
   const int T = p * (p + 1) / 2;
   {
@@ -451,13 +452,12 @@ extern "C" int stats_finalize_pairwise(stats_ctx* h, int32_t ddof, int64_t* n_ou
                        (const double*)h->state[h->cur], p, ddof, h->fin_out);
     t.end();
   }
-  std::vector<double> host(words);
   hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipMemcpyAsync(host.data(), h->fin_out, words * 8, hipMemcpyDeviceToHost, h->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(h->pin_out, h->fin_out, words * 8, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "pairwise finalize");
   collect_timings(h);
-  const double* hn = host.data();
+  const double* hn = (const double*)h->pin_out;
   const double* hm = hn + (size_t)p * p;
   const double* hc = hm + p;
   const double* hr = hc + (size_t)p * p;

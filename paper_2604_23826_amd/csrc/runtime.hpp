@@ -46,6 +46,14 @@ struct stats_ctx {
   size_t aux2_cap = 0;
   void* aux3_dev = nullptr;
   size_t aux3_cap = 0;
+  // page-locked host memory: results on their way out, group tables on their
+  // way in (read by the device until ev_tab)
+  void* pin_out = nullptr;
+  size_t pin_out_cap = 0;
+  void* pin_tab = nullptr;
+  size_t pin_tab_cap = 0;
+  hipEvent_t ev_tab = nullptr;
+  std::vector<int32_t> sel_host;  // what sel_dev holds
   void* conv_dev = nullptr;  // text -> binary conversion: line counts, status
   size_t conv_cap = 0;
 
@@ -66,6 +74,7 @@ struct stats_ctx {
   int graph_aos64 = -1;  // kernel captured in the graph: 1 = k_seg_aos64
   int64_t seg_tile_rows = 0;
   int seg_wg_per_cu = 0;
+  int seg_tuned = -1;  // kernel the two are tuned for (as graph_aos64)
   int64_t seg_cap_rt = 0;
   uint64_t* seg_part = nullptr;  // partial states of the segmented merge's first stage
   size_t seg_part_cap = 0;
@@ -88,6 +97,9 @@ int fail(int code, const std::string& msg);
 int hip_fail(stats_ctx* h, hipError_t e, const char* what);
 int elem_size(int dtype);
 int ensure_dev(stats_ctx* h, void** ptr, size_t* cap, size_t need);
+int ensure_pin(stats_ctx* h, void** ptr, size_t* cap, size_t need);
+int upload_selection(stats_ctx* h, const std::vector<int32_t>& sel);
+int status_error(const DevStatus& s);
 int sync_handle(stats_ctx* h);
 void collect_timings(stats_ctx* h);
 int accumulate_device(stats_ctx* h, const void* const* planes, int64_t nrows);

@@ -324,49 +324,62 @@ void tune_cache_store(const std::string& key, const Tuned& t) {
 
 }  // namespace
 
-// Device buffers of a groups handle (inside aux2): slot table, super-tile
-// list, row tiles, per-group tile offsets, tile count, queue head, merge
-// chunks, per-group chunk offsets, chunk count.
+// Device buffers of a groups handle (inside aux2): slot table, pair list,
+// per-group chunk offsets, tile and chunk counts, row tiles, merge chunks, queue
+// head.
 struct SegBuffers {
-  wide::SlotInfo* slots;
+  wide::SlotInfo* slots;  // slots .. nch: filled by every call
   int2* sts;
-  wide::SegTile* rowtiles;
-  int64_t* gt;
-  int64_t* nrt;
-  unsigned long long* counter;
-  SegChunk* chunks;
   int64_t* gc;
+  int64_t* nrt;
   int64_t* nch;
+  wide::SegTile* rowtiles;
+  SegChunk* chunks;
+  unsigned long long* counter;
 };
 
 // Upper bound on the merge chunks of cap_rt records in ngroups groups.
 static int64_t chunk_cap(int64_t cap_rt, int ngroups) { return cap_rt / kChunk + ngroups; }
 
-static SegBuffers seg_layout(stats_ctx* h, int ntiles_st, int64_t cap_rt, size_t* total) {
+// The buffers' places from base on; *head: bytes of the parts before the row
+// tiles, *total: of everything.
+static SegBuffers seg_layout(const stats_ctx* h, char* base, int ntiles_st, int64_t cap_rt, size_t* head,
+                             size_t* total) {
   auto al = [](size_t x) { return (x + 255) / 256 * 256; };
   size_t off = 0;
   SegBuffers b;
-  char* base = (char*)h->aux2_dev;
   b.slots = (wide::SlotInfo*)(base + off);
   off += al(sizeof(wide::SlotInfo) * h->p);
   b.sts = (int2*)(base + off);
   off += al(sizeof(int2) * ntiles_st);
-  b.rowtiles = (wide::SegTile*)(base + off);
-  off += al(sizeof(wide::SegTile) * cap_rt);
-  b.gt = (int64_t*)(base + off);
-  off += al(sizeof(int64_t) * (h->ngroups + 1));
-  b.nrt = (int64_t*)(base + off);
-  off += 256;
-  b.counter = (unsigned long long*)(base + off);
-  off += 256;
-  b.chunks = (SegChunk*)(base + off);
-  off += al(sizeof(SegChunk) * chunk_cap(cap_rt, h->ngroups));
   b.gc = (int64_t*)(base + off);
   off += al(sizeof(int64_t) * (h->ngroups + 1));
-  b.nch = (int64_t*)(base + off);
+  b.nrt = (int64_t*)(base + off);
+  b.nch = b.nrt + 1;
+  off += 256;
+  *head = off;
+  b.rowtiles = (wide::SegTile*)(base + off);
+  off += al(sizeof(wide::SegTile) * cap_rt);
+  b.chunks = (SegChunk*)(base + off);
+  off += al(sizeof(SegChunk) * chunk_cap(cap_rt, h->ngroups));
+  b.counter = (unsigned long long*)(base + off);
   off += 256;
   *total = off;
   return b;
+}
+
+// The call's tables from page-locked host memory into their places: three runs
+// of 8-byte words in one launch, instead of a copy command each.
+struct Upload {
+  const uint64_t* src[3];
+  uint64_t* dst[3];
+  int64_t words[3];
+};
+__global__ __launch_bounds__(256) void k_upload(Upload u) {
+  const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, stride = (int64_t)gridDim.x * 256;
+#pragma unroll
+  for (int r = 0; r < 3; ++r)
+    for (int64_t i = i0; i < u.words[r]; i += stride) u.dst[r][i] = u.src[r][i];
 }
 
 static void build_rowtiles(const int64_t* off, int ngroups, int64_t T, int64_t max_rows,
@@ -389,10 +402,10 @@ static void build_rowtiles(const int64_t* off, int ngroups, int64_t T, int64_t m
   (*gt)[ngroups] = (int64_t)tiles->size();
 }
 
-static int seg_prepare(stats_ctx* h, const void* const* planes, int64_t cap_rt,
-                       SegBuffers* B, const std::vector<int2>& sts) {
+// Device buffers for cap_rt row tiles.
+static int seg_reserve(stats_ctx* h, int64_t cap_rt, int ntiles_st, SegBuffers* B, size_t* head) {
   size_t need = 0;
-  seg_layout(h, (int)sts.size(), cap_rt, &need);
+  seg_layout(h, nullptr, ntiles_st, cap_rt, head, &need);
   if (need > h->aux2_cap) {
     // buffers move: the captured graph must be rebuilt
     if (h->graph_exec) {
@@ -406,8 +419,11 @@ static int seg_prepare(stats_ctx* h, const void* const* planes, int64_t cap_rt,
     int rc = ensure_dev(h, &h->aux2_dev, &h->aux2_cap, need);
     if (rc) return rc;
   }
-  *B = seg_layout(h, (int)sts.size(), cap_rt, &need);
-  std::vector<wide::SlotInfo> slots(h->p);
+  *B = seg_layout(h, (char*)h->aux2_dev, ntiles_st, cap_rt, head, &need);
+  return STATS_OK;
+}
+
+static void fill_slots(const stats_ctx* h, const void* const* planes, wide::SlotInfo* slots) {
   for (int c = 0; c < h->p; ++c) {
     const stats_column& col = h->cols[c];
     wide::SlotInfo& s = slots[c];
@@ -418,12 +434,6 @@ static int seg_prepare(stats_ctx* h, const void* const* planes, int64_t cap_rt,
     s.isint = h->intf[c];
     s.pad[0] = s.pad[1] = 0;
   }
-  hipError_t e = hipMemcpyAsync(B->slots, slots.data(), sizeof(wide::SlotInfo) * h->p,
-                                hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(B->sts, sts.data(), sizeof(int2) * sts.size(), hipMemcpyHostToDevice, h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "uploading segment tables");
-  return STATS_OK;
 }
 
 // FP64 records of 256 bytes with column c at byte 8c (p <= 32), 16-byte
@@ -482,13 +492,19 @@ static int autotune(stats_ctx* h, const void* const* planes, const int64_t* off,
     int64_t rows = 0;
     for (const auto& t : tiles) rows += t.r1 - t.r0;
     SegBuffers B;
-    rc = seg_prepare(h, planes, (int64_t)tiles.size(), &B, sts);
+    size_t head;
+    rc = seg_reserve(h, (int64_t)tiles.size(), (int)sts.size(), &B, &head);
     if (rc) break;
+    std::vector<wide::SlotInfo> slots(h->p);
+    fill_slots(h, planes, slots.data());
     const int64_t nt = (int64_t)tiles.size();
     rc = ensure_dev(h, (void**)&h->rec, &h->rec_cap, (size_t)(nt * rec_words(h->p) * 8));
     if (rc) break;
-    hipError_t e = hipMemcpyAsync(B.rowtiles, tiles.data(), sizeof(wide::SegTile) * nt,
-                                  hipMemcpyHostToDevice, h->stream);
+    hipError_t e = hipMemcpyAsync(B.slots, slots.data(), sizeof(wide::SlotInfo) * h->p, hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(B.sts, sts.data(), sizeof(int2) * sts.size(), hipMemcpyHostToDevice, h->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync(B.rowtiles, tiles.data(), sizeof(wide::SegTile) * nt, hipMemcpyHostToDevice, h->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(B.nrt, &nt, 8, hipMemcpyHostToDevice, h->stream);
     if (e != hipSuccess) {
       rc = hip_fail(h, e, "autotune upload");
@@ -562,36 +578,40 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
   std::vector<int2> sts;
   wide_pairs(p, wide::kWideGroup, &sts);
 
-  // tile height and occupancy: configured, cached, or tuned now
+  // tile height and occupancy: configured, known to the handle, cached, or tuned now
+  const bool aos64 = seg_aos64_layout(h, planes);
   Tuned tu{h->block_rows, 4};
-  if (!h->block_rows) {
+  if (!h->block_rows && h->seg_tuned == (int)aos64) {
+    tu = Tuned{h->seg_tile_rows, h->seg_wg_per_cu};
+  } else if (!h->block_rows) {
     hipDeviceProp_t prop;
     const char* arch = "gfx";
     if (hipGetDeviceProperties(&prop, h->device) == hipSuccess) arch = prop.gcnArchName;
-    const std::string key = tune_key(h, arch, seg_aos64_layout(h, planes));
+    const std::string key = tune_key(h, arch, aos64);
     if (!tune_cache_lookup(key, &tu)) {
       int rc = autotune(h, planes, row_offsets, sts, &tu);
       if (rc) return rc;
       tune_cache_store(key, tu);
     }
+    h->seg_tuned = (int)aos64;
   }
   h->seg_tile_rows = tu.tile_rows;
   h->seg_wg_per_cu = tu.wg_per_cu;
 
-  std::vector<wide::SegTile> tiles;
-  std::vector<int64_t> gt;
-  build_rowtiles(row_offsets, h->ngroups, tu.tile_rows, INT64_MAX, &tiles, &gt);
-  const int64_t nt = (int64_t)tiles.size();
-  if (nt == 0) return STATS_OK;
-  // merge chunks: runs of at most kChunk consecutive records of one group
-  std::vector<SegChunk> chunks;
-  std::vector<int64_t> gc(h->ngroups + 1, 0);
+  // row tiles, and merge chunks: runs of at most kChunk consecutive records of
+  // one group
+  const int64_t T = tu.tile_rows;
+  auto tiles_of = [&](int g) {
+    const int64_t rows = row_offsets[g + 1] - row_offsets[g];
+    return rows <= T ? (int64_t)(rows > 0) : (rows + T - 1) / T;
+  };
+  int64_t nt = 0, nch = 0;
   for (int g = 0; g < h->ngroups; ++g) {
-    gc[g] = (int64_t)chunks.size();
-    for (int64_t k = gt[g]; k < gt[g + 1]; k += kChunk) chunks.push_back(SegChunk{k, std::min(k + kChunk, gt[g + 1])});
+    const int64_t k = tiles_of(g);
+    nt += k;
+    nch += (k + kChunk - 1) / kChunk;
   }
-  gc[h->ngroups] = (int64_t)chunks.size();
-  const int64_t nch = (int64_t)chunks.size();
+  if (nt == 0) return STATS_OK;
   // capacity grows in steps so that the graph is rarely rebuilt
   int64_t cap_rt = std::max<int64_t>(h->seg_cap_rt, 1024);
   while (cap_rt < nt) cap_rt *= 2;
@@ -608,7 +628,8 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
     }
   }
   SegBuffers B;
-  int rc = seg_prepare(h, planes, cap_rt, &B, sts);
+  size_t head = 0;
+  int rc = seg_reserve(h, cap_rt, (int)sts.size(), &B, &head);
   if (rc) return rc;
   if (rec_need > h->rec_cap) {
     rc = ensure_dev(h, (void**)&h->rec, &h->rec_cap, rec_need);
@@ -619,18 +640,40 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
     if (rc) return rc;
   }
   h->seg_cap_rt = cap_rt;
-  hipError_t e = hipMemcpyAsync(B.rowtiles, tiles.data(), sizeof(wide::SegTile) * nt,
-                                hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(B.gt, gt.data(), sizeof(int64_t) * gt.size(), hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(B.nrt, &nt, 8, hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(B.chunks, chunks.data(), sizeof(SegChunk) * nch, hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(B.gc, gc.data(), sizeof(int64_t) * gc.size(), hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(B.nch, &nch, 8, hipMemcpyHostToDevice, h->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(h->stream);  // host vectors go out of scope
-  if (e != hipSuccess) return hip_fail(h, e, "uploading segment tables");
+  // the page-locked tables are free once the last call's upload has run
+  hipError_t e = h->ev_tab ? hipEventSynchronize(h->ev_tab) : hipEventCreateWithFlags(&h->ev_tab, hipEventDisableTiming);
+  if (e != hipSuccess) return hip_fail(h, e, "group tables");
+  const size_t rt_bytes = sizeof(wide::SegTile) * (size_t)nt, ch_bytes = sizeof(SegChunk) * (size_t)nch;
+  rc = ensure_pin(h, &h->pin_tab, &h->pin_tab_cap, head + rt_bytes + ch_bytes);
+  if (rc) return rc;
+  {
+    char* pin = (char*)h->pin_tab;
+    size_t unused;
+    const SegBuffers H = seg_layout(h, pin, (int)sts.size(), 0, &unused, &unused);
+    wide::SegTile* tile = (wide::SegTile*)(pin + head);
+    SegChunk* chunk = (SegChunk*)(pin + head + rt_bytes);
+    fill_slots(h, planes, H.slots);
+    memcpy(H.sts, sts.data(), sizeof(int2) * sts.size());
+    *H.nrt = nt;
+    *H.nch = nch;
+    int64_t it = 0, ic = 0;
+    for (int g = 0; g < h->ngroups; ++g) {
+      H.gc[g] = ic;
+      const int64_t end = it + tiles_of(g);
+      for (int64_t k = it; k < end; k += kChunk) chunk[ic++] = SegChunk{k, std::min(k + kChunk, end)};
+      for (int64_t r = row_offsets[g]; r < row_offsets[g + 1]; r += T)
+        tile[it++] = wide::SegTile{r, std::min(r + T, row_offsets[g + 1]), g, 0};
+    }
+    H.gc[h->ngroups] = ic;
+    const Upload u{{(const uint64_t*)pin, (const uint64_t*)tile, (const uint64_t*)chunk},
+                   {(uint64_t*)B.slots, (uint64_t*)B.rowtiles, (uint64_t*)B.chunks},
+                   {(int64_t)(head / 8), (int64_t)(rt_bytes / 8), (int64_t)(ch_bytes / 8)}};
+    const int64_t most = std::max(u.words[0], std::max(u.words[1], u.words[2]));
+    hipLaunchKernelGGL(k_upload, dim3((unsigned)std::min<int64_t>((most + 255) / 256, 256)), dim3(256), 0, h->stream, u);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = hipEventRecord(h->ev_tab, h->stream);
+    if (e != hipSuccess) return hip_fail(h, e, "uploading segment tables");
+  }
 
   wide::Args a;
   a.slots = B.slots;
@@ -644,7 +687,6 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
   a.status = h->status_dev;
   wide::SegArgs sa{B.rowtiles, B.nrt, B.counter};
   const int nwg = num_cus(h->device) * tu.wg_per_cu;
-  const bool aos64 = seg_aos64_layout(h, planes);
 
   if (!h->graph_exec) {
     // capture on a private stream (the handle's stream may be a legacy default stream)
@@ -695,16 +737,13 @@ extern "C" int stats_finalize_groups(stats_ctx* h, const stats_finalize_opts* op
   int rc = selection(h, o, &sel);
   if (rc) return rc;
   DeviceGuard dg(h->device);
-  rc = sync_handle(h);
-  if (rc) return rc;
   const int q = (int)sel.size();
   const int64_t G = h->ngroups;
   const size_t words = (size_t)G * (1 + q + (size_t)q * q);
   rc = ensure_dev(h, (void**)&h->fin_out, &h->fin_out_cap, words * 8);
-  if (!rc) rc = ensure_dev(h, (void**)&h->sel_dev, &h->sel_cap, (size_t)q * 4);
+  if (!rc) rc = ensure_pin(h, &h->pin_out, &h->pin_out_cap, words * 8 + sizeof(DevStatus));
+  if (!rc) rc = upload_selection(h, sel);
   if (rc) return rc;
-  hipError_t e = hipMemcpyAsync(h->sel_dev, sel.data(), (size_t)q * 4, hipMemcpyHostToDevice, h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "uploading selection");
   int64_t* dn = (int64_t*)h->fin_out;
   double* dmean = h->fin_out + G;
   double* dcov = dmean + G * q;
@@ -715,17 +754,22 @@ extern "C" int stats_finalize_groups(stats_ctx* h, const stats_finalize_opts* op
                        h->sel_dev, q, h->intf_dev, o->ddof, dn, dmean, dcov);
     t.end();
   }
-  e = hipGetLastError();
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "group finalize launch");
-  std::vector<double> out(words);
-  e = hipMemcpyAsync(out.data(), h->fin_out, words * 8, hipMemcpyDeviceToHost, h->stream);
+  // the status word comes along, so that there is one wait
+  const double* out = (const double*)h->pin_out;
+  DevStatus* st = (DevStatus*)((double*)h->pin_out + words);
+  e = hipMemcpyAsync(h->pin_out, h->fin_out, words * 8, hipMemcpyDeviceToHost, h->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(st, h->status_dev, sizeof *st, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "group finalize");
   collect_timings(h);
+  rc = status_error(*st);
+  if (rc) return rc;
   if (p_out) *p_out = q;
-  if (n_out) memcpy(n_out, out.data(), (size_t)G * 8);
-  if (mean_out) memcpy(mean_out, out.data() + G, (size_t)G * q * 8);
-  if (cov_out) memcpy(cov_out, out.data() + G + G * q, (size_t)G * q * q * 8);
+  if (n_out) memcpy(n_out, out, (size_t)G * 8);
+  if (mean_out) memcpy(mean_out, out + G, (size_t)G * q * 8);
+  if (cov_out) memcpy(cov_out, out + G + G * q, (size_t)G * q * q * 8);
   return STATS_OK;
 }
 
