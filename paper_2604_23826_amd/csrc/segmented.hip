@@ -741,7 +741,10 @@ extern "C" int stats_finalize_groups(stats_ctx* h, const stats_finalize_opts* op
   const int64_t G = h->ngroups;
   const size_t words = (size_t)G * (1 + q + (size_t)q * q);
   rc = ensure_dev(h, (void**)&h->fin_out, &h->fin_out_cap, words * 8);
-  if (!rc) rc = ensure_pin(h, &h->pin_out, &h->pin_out_cap, words * 8 + sizeof(DevStatus));
+  // through page-locked memory while that is quickly had (a new handle pays for
+  // it); large results straight to the caller's arrays
+  const bool direct = words * 8 > ((size_t)1 << 20);
+  if (!rc) rc = ensure_pin(h, &h->pin_out, &h->pin_out_cap, (direct ? 0 : words * 8) + sizeof(DevStatus));
   if (!rc) rc = upload_selection(h, sel);
   if (rc) return rc;
   int64_t* dn = (int64_t*)h->fin_out;
@@ -757,19 +760,27 @@ extern "C" int stats_finalize_groups(stats_ctx* h, const stats_finalize_opts* op
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "group finalize launch");
   // the status word comes along, so that there is one wait
-  const double* out = (const double*)h->pin_out;
-  DevStatus* st = (DevStatus*)((double*)h->pin_out + words);
-  e = hipMemcpyAsync(h->pin_out, h->fin_out, words * 8, hipMemcpyDeviceToHost, h->stream);
-  if (e == hipSuccess) e = hipMemcpyAsync(st, h->status_dev, sizeof *st, hipMemcpyDeviceToHost, h->stream);
+  DevStatus* st = (DevStatus*)h->pin_out;
+  const double* out = (const double*)(st + 1);
+  e = hipMemcpyAsync(st, h->status_dev, sizeof *st, hipMemcpyDeviceToHost, h->stream);
+  if (e == hipSuccess && !direct)
+    e = hipMemcpyAsync((void*)out, h->fin_out, words * 8, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "group finalize");
   collect_timings(h);
   rc = status_error(*st);
   if (rc) return rc;
   if (p_out) *p_out = q;
-  if (n_out) memcpy(n_out, out, (size_t)G * 8);
-  if (mean_out) memcpy(mean_out, out + G, (size_t)G * q * 8);
-  if (cov_out) memcpy(cov_out, out + G + G * q, (size_t)G * q * q * 8);
+  const size_t nb = (size_t)G * 8, mb = nb * q, cb = mb * q;
+  if (direct) {
+    if (n_out) e = hipMemcpy(n_out, dn, nb, hipMemcpyDeviceToHost);
+    if (e == hipSuccess && mean_out) e = hipMemcpy(mean_out, dmean, mb, hipMemcpyDeviceToHost);
+    if (e == hipSuccess && cov_out) e = hipMemcpy(cov_out, dcov, cb, hipMemcpyDeviceToHost);
+    return e == hipSuccess ? STATS_OK : hip_fail(h, e, "reading group results");
+  }
+  if (n_out) memcpy(n_out, out, nb);
+  if (mean_out) memcpy(mean_out, out + G, mb);
+  if (cov_out) memcpy(cov_out, out + G + G * q, cb);
   return STATS_OK;
 }
 
