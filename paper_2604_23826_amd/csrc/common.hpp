@@ -407,6 +407,12 @@ __device__ inline T load_global(const char* p) {
 
 // ---- kernel launchers (defined in the .hip files) ----------------------------
 
+// Chunks of at most this many interleaved rows take the column-per-lane kernel
+// (rows_mfma.hip) whatever their layout: its short code and early loads start
+// faster than the LDS-DMA kernels, which overtake it where bandwidth counts
+// (80-byte rows, 250,000: 10 against 13 us; 1,000,000: 22 against 21 us).
+constexpr int64_t kLaneRows = (int64_t)1 << 18;
+
 struct AccumLaunch {
   const char* colbase[16];  // address of column c in row 0
   int64_t colstride[16];    // bytes between rows of column c
