@@ -9,17 +9,23 @@
 // Work split: workgroup w owns the lines whose first byte lies in
 // [w seg, (w + 1) seg), seg a multiple of 4096 up to 40 KiB chosen per chunk
 // from its mean line length (pick_text_seg); its threads find the line starts
-// of seg / 256-byte slices, then take the lines in turn, one per thread and
-// round.  The workgroup stages its bytes (plus MAXLINE bytes of the next
-// segment, for lines that run past the end) in LDS with 16 bytes of padding
-// per 256, so that threads reading their own slices hit different banks.  The
-// block shift is the workgroup's first line.
+// of their slices, then take the lines in turn, one per thread and round.  The
+// workgroup stages its bytes (plus MAXLINE bytes of the next segment, for lines
+// that run past the end) in LDS.  The block shift is the workgroup's first line.
+//
+// What bounds the kernels: instructions, 45 to 90 vector instructions a short
+// integer field and some 300 a 17-digit decimal one, at two to three waves per
+// SIMD (the text and the parsed rows fill LDS).  8 million ten-column Table-1
+// lines (458 MB): 1050 us in the kernel with the fields unrolled (78 KiB of
+// code) and a corrected FP64 division per decimal field, 490 us as it is;
+// conversion of 2 million lines of eight decimals: 474 and 209 us.
 //
 // Fields: integer columns are decimal integers (optional sign, at most 18
 // digits), parsed exactly; other columns are decimal numbers (optional sign,
 // digits with an optional point, optional exponent), converted to the nearest
-// FP64 value: the decimal significand w and exponent q give w * 10^q, formed
-// as an exact 256-bit integer ratio and divided once with correct rounding.
+// FP64 value: the decimal significand w and exponent q give w * 10^q, rounded
+// from a 128-bit product where that settles it (scaled_decimal), else formed as
+// an exact integer ratio and divided once with correct rounding.
 // The ratio's range: every |value| below 1e73 whose last written digit has
 // exponent q >= -57 converts; a field beyond 2^247 (about 2.3e74) or with
 // q < -57 is refused as malformed (in between, by the significand's bit
@@ -37,14 +43,25 @@ namespace text {
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
-constexpr int SEG = 1 << 15;     // bytes of line starts per workgroup (conversion, line counts)
-constexpr int SEG_MAX = 40 << 10;  // the fused kernel's segments: a multiple of 4096 up to this (chosen per chunk)
-constexpr int MAXLINE = 4096;    // longest line accepted
-constexpr int SLICE = SEG / 256;  // bytes of line starts per thread (one slice per thread)
-constexpr int SLICE_MAX = SEG_MAX / 256;
-constexpr int MAXLS = 2048;      // line starts per workgroup kept in the table
-constexpr int STAGE = 32 + SEG_MAX + MAXLINE;  // + up to 15 bytes of alignment in front
-constexpr int STAGE_PADDED = STAGE + (STAGE / 256 + 2) * 16;  // room for word reads past the end
+constexpr int kWaves = kThreads / 64;
+constexpr int UNIT = 4096;         // segments are whole units; lines are counted per unit
+constexpr int SEG_MIN = 8 << 10, SEG_MAX = 40 << 10;  // bytes of line starts per workgroup (chosen per chunk)
+constexpr int MAXLINE = 4096;      // longest line accepted
+constexpr int MAXLS = 2048;        // line starts per workgroup kept in the table
+constexpr int kPast = 32;          // bytes past the text that read as 0xFF
+
+// LDS bytes of the text stage of a segment: up to 31 bytes in front (16 of the
+// stream before it and the alignment), the segment, the longest line and the end mark.
+constexpr int stage_bytes(int seg) { return 32 + seg + MAXLINE + kPast; }
+// Dynamic LDS of the two text kernels: the stage, then the line table.
+constexpr int text_lds(int seg, int maxls) { return stage_bytes(seg) + 2 * maxls; }
+// Bytes of line starts per thread: an odd number of 16-byte vectors, so that
+// the threads' vector reads of their slices fall on different banks.
+constexpr int slice_of(int seg) { return ((seg + 16 * kThreads - 1) / (16 * kThreads) | 1) * 16; }
+constexpr int SLICE_MAX = slice_of(SEG_MAX);
+// Words between the parsed rows of a wave's lines: no multiple of four, against
+// bank conflicts.
+constexpr int row_words(int p) { return p % 4 ? p : p + 1; }
 
 struct Args {
   const char* buf;
@@ -54,41 +71,35 @@ struct Args {
   uint32_t intmask;
   int64_t base_off;  // offset of buf in the caller's stream (for messages)
   int seg;           // bytes of line starts per workgroup: a multiple of 4096, at most SEG_MAX
+  int maxls;         // line starts per workgroup kept in the table, at most MAXLS
   acc::Args acc;
   DevStatus* status;
 };
 
-__device__ inline int pad(int i) { return i + ((i >> 8) << 4); }
+typedef const __attribute__((address_space(3))) unsigned char* lds_text;
 
-
-// Staged text [w0, w0 + n) of the chunk.  The parser works on positions
-// relative to w0 (32-bit); positions at or past lim (min(nend, w0 + n) - w0)
-// read as -1.
+// Staged text of the chunk.  The parser works on positions relative to the
+// stage (32-bit); positions at or past lim read as -1.  The kPast bytes from
+// lim on hold 0xFF, which is no character of a field.
 struct Stage {
-  const unsigned char* s;
-  int64_t w0;  // stream offset of staged byte 0
-  int n;       // staged bytes
-  int lim;     // first relative position that is not text of this chunk
+  lds_text s;
+  int lim;  // first relative position that is not text of this chunk
 };
 
-// A thread's reader of the staged text (one LDS byte per character; the
-// staged bytes are padded 16 per 256 so that threads reading their own slices
-// fall on different banks).
+// A thread's reader of the staged text.
 struct Cur {
   const Stage* S;
   __device__ explicit Cur(const Stage& st) : S(&st) {}
   __device__ inline int at(int pos) const {
     if (pos >= S->lim) return -1;
-    return ((const __attribute__((address_space(3))) unsigned char*)S->s)[pad(pos)];
+    return S->s[pos];
   }
   // The four bytes at pos .. pos + 3 (the first in the low byte), from two
   // aligned LDS words; bytes at or past lim read as 0xFF.  pos >= 0.
   __device__ inline uint32_t word4(int pos) const {
     const int a = pos & ~3;
-    const __attribute__((address_space(3))) unsigned char* b =
-        (const __attribute__((address_space(3))) unsigned char*)S->s;
-    const uint32_t lo = *(const __attribute__((address_space(3))) uint32_t*)(b + pad(a));
-    const uint32_t hi = *(const __attribute__((address_space(3))) uint32_t*)(b + pad(a + 4));
+    const uint32_t lo = *(const __attribute__((address_space(3))) uint32_t*)(S->s + a);
+    const uint32_t hi = *(const __attribute__((address_space(3))) uint32_t*)(S->s + a + 4);
     uint32_t v = __builtin_amdgcn_alignbyte(hi, lo, (uint32_t)(pos & 3));
     const int room = S->lim - pos;
     if (room < 4) v |= room <= 0 ? 0xFFFFFFFFu : (0xFFFFFFFFu << (8 * room));
@@ -402,114 +413,208 @@ __device__ __attribute__((noinline)) Parsed parse_wide(Stage S, int f, bool is_i
 
 // ---- fast path for the common field forms -----------------------------------
 //
-// Bytes [pos, pos + 20) of the staged text in five words (first character in
-// the low byte of w[0]); positions at or past lim read as 0xFF.  pos <= lim,
-// so every word read lies inside the staging buffer.
-__device__ inline void window20(const Cur& C, int pos, uint32_t (&w)[5]) {
-  const __attribute__((address_space(3))) unsigned char* b =
-      (const __attribute__((address_space(3))) unsigned char*)C.S->s;
-  const int a = pos & ~3;
-  uint32_t r[6];
-#pragma unroll
-  for (int j = 0; j < 6; ++j) r[j] = *(const __attribute__((address_space(3))) uint32_t*)(b + pad(a + 4 * j));
-  const uint32_t sh = (uint32_t)(pos & 3);
-#pragma unroll
-  for (int j = 0; j < 5; ++j) w[j] = __builtin_amdgcn_alignbyte(r[j + 1], r[j], sh);
-  const int room = C.S->lim - pos;
-  if (room < 20) {
-#pragma unroll
-    for (int j = 0; j < 5; ++j) {
-      const int rj = room - 4 * j;
-      w[j] |= rj <= 0 ? 0xFFFFFFFFu : (rj < 4 ? (0xFFFFFFFFu << (8 * rj)) : 0u);
-    }
-  }
+// Eight characters per step from aligned LDS words; one copy of the code for
+// all fields of a line, so that it stays in the instruction cache (unrolled over
+// the fields it was 78 KiB at ten columns, and fetching it was most of the time).
+
+// 10^k, 0 <= k <= 8.
+__device__ inline uint32_t pow10_upto8(int k) {
+  const auto upto4 = [](int j) {
+    return j == 4 ? 10000u : (uint32_t)(0x03E80064000A0001ull >> (16 * j)) & 0xFFFFu;
+  };
+  const int j = k < 4 ? k : 4;
+  return __umul24(upto4(j), upto4(k - j));
 }
 
-__device__ inline uint32_t pow10_upto4(int k) {  // 10^k, 0 <= k <= 4, without branches
-  return k == 4 ? 10000u : (uint32_t)(0x03E80064000A0001ull >> (16 * k)) & 0xFFFFu;
+// Value of four digits (the first in the low byte).
+__device__ inline uint32_t four_digits(uint32_t y) {
+  const uint32_t t = (y << 3) + (y << 1) + (y >> 8);  // 10 b0 + b1 in byte 0, 10 b2 + b3 in byte 2
+  return __umul24(t & 0xFFu, 100u) + ((t >> 16) & 0xFFu);
 }
 
-// The leading decimal digits of the 4 NW bytes w[0..NW-1]: their count k
-// (0..4 NW), appended to *val (*val = *val 10^k + their value; wraps modulo
-// 2^64, which only matters past 19 digits), and the byte after them in *term
-// (0xFF when all 4 NW bytes are digits).  Four digits per step (the SWAR step
-// of digit_run); the steps stop when no lane of the wave has digits left.
-template <int NW>
-__device__ inline int lead_digits(const uint32_t (&w)[5], uint64_t* val, uint32_t* term) {
-  uint64_t v = *val;
-  int k = 0;
-  bool done = false;
-  uint32_t t8 = 0xFFu;
-#pragma unroll
-  for (int j = 0; j < NW; ++j) {
-    if (j > 0 && __builtin_amdgcn_ballot_w64(!done) == 0) break;  // wave-uniform
-    const uint32_t x = w[j];
-    const uint32_t m = ((x & 0xF0F0F0F0u) ^ 0x30303030u) | (((x & 0x0F0F0F0Fu) + 0x06060606u) & 0xF0F0F0F0u);
-    const int kw = m ? (__builtin_ctz(m) >> 3) : 4;
-    const int kj = done ? 0 : kw;
-    const uint32_t y = kj ? (x & 0x0F0F0F0Fu) << (8 * (4 - kj)) : 0u;
-    const uint32_t t = y * 10u + (y >> 8);
-    v = v * pow10_upto4(kj) + ((t & 0xFFu) * 100u + ((t >> 16) & 0xFFu));
-    if (!done && kw < 4) t8 = (x >> (8 * kw)) & 0xFFu;
-    k += kj;
-    done |= kw < 4;
-  }
-  *val = v;
-  *term = t8;
+// The leading decimal digits of the eight bytes x0, x1 (first character in the
+// low byte of x0): their number, their value in *val and, when there are fewer
+// than eight, the character after them in *term.
+__device__ inline int digits8(uint32_t x0, uint32_t x1, uint32_t* val, uint32_t* term) {
+  const auto not_digit = [](uint32_t x) {  // a bit in every byte that is no digit
+    return ((x & 0xF0F0F0F0u) ^ 0x30303030u) | (((x & 0x0F0F0F0Fu) + 0x06060606u) & 0xF0F0F0F0u);
+  };
+  const uint32_t m0 = not_digit(x0), m1 = not_digit(x1);
+  const int k = (m0 ? __builtin_ctz(m0) : m1 ? 32 + __builtin_ctz(m1) : 64) >> 3;
+  const uint64_t x = (uint64_t)x1 << 32 | x0;
+  // the digits moved to the top k bytes: leading zero bytes add nothing
+  const uint64_t y = k ? (x & 0x0F0F0F0F0F0F0F0Full) << (64 - 8 * k) : 0ull;
+  *val = __umul24(four_digits((uint32_t)y), 10000u) + four_digits((uint32_t)(y >> 32));
+  *term = (uint32_t)(x >> (8 * (k & 7))) & 0xFFu;
   return k;
 }
 
-// The field at f when it has one of the common forms: [sign] 1..15 digits
-// (integer columns), or [sign] digits [. digits] with 1..19 digits in all and
-// no exponent (decimal columns).  Then it returns true with the terminator's
-// position in *end, its byte in *term (-1 past the text) and the value bits in
-// *bits, exactly as parse_field gives them (the same w, digit count and q go
-// to decimal_value); otherwise false, and parse_field takes the field.
-__device__ inline bool fast_field(const Cur& C, int f, bool is_int, int* end, int* term, uint64_t* bits) {
-  uint32_t w[5];
-  window20(C, f, w);
-  const uint32_t c0 = w[0] & 0xFFu;
+// The eight characters at pos (pos <= lim: every word read lies in the stage).
+__device__ inline void chars8(const Stage& S, int pos, uint32_t* x0, uint32_t* x1) {
+  const __attribute__((address_space(3))) uint32_t* b = (const __attribute__((address_space(3))) uint32_t*)(S.s + (pos & ~3));
+  const uint32_t r0 = b[0], r1 = b[1], r2 = b[2], sh = (uint32_t)(pos & 3);
+  *x0 = __builtin_amdgcn_alignbyte(r1, r0, sh);
+  *x1 = __builtin_amdgcn_alignbyte(r2, r1, sh);
+}
+
+// The same after an optional sign at pos, which is counted in *pos.
+__device__ inline bool signed_chars8(const Stage& S, int* pos, uint32_t* x0, uint32_t* x1) {
+  const __attribute__((address_space(3))) uint32_t* b = (const __attribute__((address_space(3))) uint32_t*)(S.s + (*pos & ~3));
+  const uint32_t r0 = b[0], r1 = b[1], r2 = b[2], r3 = b[3], sh = (uint32_t)(*pos & 3);
+  const uint32_t a0 = __builtin_amdgcn_alignbyte(r1, r0, sh), a1 = __builtin_amdgcn_alignbyte(r2, r1, sh);
+  const uint32_t a2 = __builtin_amdgcn_alignbyte(r3, r2, sh);
+  const uint32_t c0 = a0 & 0xFFu;
   const bool neg = c0 == '-';
-  const uint32_t sg = (c0 == '-' || c0 == '+') ? 1u : 0u;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) w[j] = __builtin_amdgcn_alignbyte(w[j + 1], w[j], sg);
-  uint64_t v = 0;
-  uint32_t t1;
-  const int k1 = lead_digits<4>(w, &v, &t1);
-  if (k1 > 15) return false;
-  int p = f + (int)sg + k1;  // the byte after the digits
-  int c = p >= C.S->lim ? -1 : (int)t1;
-  int nd = k1, q = 0;
-  if (!is_int && c == '.') {
-    // fraction digits appended to v: w = (integer digits)(fraction digits)
-    int k2 = 0;
-    ++p;
-    if (p < C.S->lim) {
-      uint32_t w2[5], t2;
-      window20(C, p, w2);
-      k2 = lead_digits<5>(w2, &v, &t2);
-      if (k1 + k2 > 19) return false;
-      c = p + k2 >= C.S->lim ? -1 : (int)t2;
+  const uint32_t sg = (neg || c0 == '+') ? 1u : 0u;
+  *x0 = __builtin_amdgcn_alignbyte(a1, a0, sg);
+  *x1 = __builtin_amdgcn_alignbyte(a2, a1, sg);
+  *pos += (int)sg;
+  return neg;
+}
+
+// Powers of five for the conversion, -27 <= q <= 27: 5^q = (hi:lo) 2^e with the
+// top bit of the 128-bit (hi:lo) set, rounded up for q < 0, exact otherwise, and
+// e = floor(q log2 5) - 127.
+constexpr int kMaxPow = 27;
+struct Pow5Scaled {
+  uint64_t hi[2 * kMaxPow + 1], lo[2 * kMaxPow + 1];
+};
+constexpr Pow5Scaled make_pow5_scaled() {
+  Pow5Scaled t{};
+  for (int q = -kMaxPow; q <= kMaxPow; ++q) {
+    uint64_t d = 1;
+    for (int k = 0; k < (q < 0 ? -q : q); ++k) d *= 5;
+    int bl = 0;
+    while (bl < 64 && (d >> bl) != 0) ++bl;
+    u128 r = 0;
+    if (q >= 0) {
+      r = (u128)d << (128 - bl);
     } else {
-      c = -1;
+      // ceil(2^(127 + bl) / 5^-q), bit by bit
+      u128 rem = 0;
+      for (int b = 127 + bl; b >= 0; --b) {
+        rem = 2 * rem + (b == 127 + bl ? 1 : 0);
+        r <<= 1;
+        if (rem >= d) {
+          rem -= d;
+          r |= 1;
+        }
+      }
+      r += 1;
     }
-    nd = k1 + k2;
-    q = -k2;
-    p += k2;
+    t.hi[q + kMaxPow] = (uint64_t)(r >> 64);
+    t.lo[q + kMaxPow] = (uint64_t)r;
   }
-  if (nd == 0 || (c != ',' && c != '\n' && c != -1)) return false;
-  if (is_int) {
-    const int64_t x = (int64_t)v;
-    *bits = (uint64_t)(neg ? -x : x);
-  } else {
-    bool bad = false;
-    const double d = decimal_value((u128)v, nd, q, false, neg, &bad);
-    if (bad) return false;
-    *bits = (uint64_t)__double_as_longlong(d);
+  return t;
+}
+__constant__ Pow5Scaled kPow5Scaled = make_pow5_scaled();
+
+// The table in LDS, (hi, lo) of each power side by side: the lanes of a wave read
+// different entries.
+constexpr int kPow5Words = 2 * (2 * kMaxPow + 1);
+__device__ inline void copy_pow5(uint64_t* s) {
+  for (int k = threadIdx.x; k < 2 * kMaxPow + 1; k += kThreads) {
+    s[2 * k] = kPow5Scaled.hi[k];
+    s[2 * k + 1] = kPow5Scaled.lo[k];
   }
-  *end = p;
-  *term = c;
+}
+
+// w 10^q (w != 0, |q| <= kMaxPow) rounded to the nearest FP64 value, ties to
+// even; false when the rounding cannot be told from the 128 bits computed.
+// (The idea of D. Lemire, "Number parsing at a gigabyte per second", 2021: the
+// significand times a scaled power of five; the bounds below are for this
+// table.)  With z = w 2^l (top bit set) and T = (hi:lo), X = z 5^q 2^-e' is the
+// true value scaled like P = floor(z T / 2^64): T exceeds the exact power by
+// less than one unit, so z T / 2^64 lies in [X, X + 1) and P is floor(X) or
+// floor(X) + 1.  Let r be the 74 or 75 bits of P below the 53 kept and h their
+// half.  r < h: X rounds down, also when r = 0 stems from floor(X) ending in
+// ones (then X rounds up to the same value).  r > h + 1: X rounds up.  Only
+// r = h and r = h + 1 are open (an exact tie or not); they are left to the
+// exact division.  All values are normal: 10^-27 <= w 10^q < 2^64 10^27.
+__device__ inline bool scaled_decimal(const uint64_t* pow5, uint64_t w, int q, bool neg, double* out) {
+  const int l = __builtin_clzll(w);
+  const uint64_t z = w << l;
+  const u128 a = (u128)z * pow5[2 * (q + kMaxPow)];
+  const u128 P = a + (uint64_t)(((u128)z * pow5[2 * (q + kMaxPow) + 1]) >> 64);
+  uint64_t hi = (uint64_t)(P >> 64), lo = (uint64_t)P;
+  const int top = (int)(hi >> 63);  // P has 128 bits, or 127
+  const int s = 10 + top;           // bits of hi below the 53 kept
+  const uint64_t m = hi >> s;
+  const uint32_t rh = (uint32_t)hi & ((1u << s) - 1), half = 1u << (s - 1);
+  if (rh == half && lo <= 1) return false;
+  const uint64_t mr = m + (rh >= half ? 1 : 0);
+  // value = m 2^(s + 64 + e), P in units of 2^e, e = floor(q log2 5) - 127 + 64 - l + q
+  const int e = ((q * 152170) >> 16) - 63 - l + q + 64 + s;
+  const uint64_t bits = mr + ((uint64_t)(e + 52 + 1022) << 52);  // m's top bit and a carry of the rounding add to the exponent
+  *out = __longlong_as_double((long long)(bits | (neg ? 1ull << 63 : 0ull)));
   return true;
+}
+
+// Further digits at *p, eight a step, appended to *v (*nd counts them).  Past 19
+// digits the field is not taken, so three steps are enough and *v may wrap.
+__device__ inline void more_digits(const Stage& S, bool more, int* p, int* nd, uint64_t* v, uint32_t* c) {
+  while (more) {
+    uint32_t x0, x1, val;
+    chars8(S, *p, &x0, &x1);
+    const int k = digits8(x0, x1, &val, c);
+    *v = *v * pow10_upto8(k) + val;
+    *nd += k;
+    *p += k;
+    more = k == 8 && *nd < 24;
+  }
+}
+
+// The field at f when it is followed by the byte want and has one of the common
+// forms: [sign] 1..18 digits (integer columns), or [sign] digits [. digits]
+// [e [sign] 1..3 digits] with 1..19 digits before the exponent and a power of
+// ten of at most 10^27 either way (decimal columns).  Then it returns true with
+// the position of want in *end and the value bits in *bits, exactly as
+// parse_field gives them; otherwise false, and parse_field takes the field.
+__device__ inline bool fast_int(const Stage& S, int f, uint32_t want, int* end, uint64_t* bits) {
+  uint32_t x0, x1, val, c;
+  int p = f;
+  const bool neg = signed_chars8(S, &p, &x0, &x1);
+  int nd = digits8(x0, x1, &val, &c);
+  uint64_t v = val;
+  p += nd;
+  more_digits(S, nd == 8, &p, &nd, &v, &c);
+  *bits = neg ? 0ull - v : v;
+  *end = p;
+  return (c == want) & ((uint32_t)(nd - 1) < 18u);
+}
+
+__device__ inline bool fast_decimal_field(const Stage& S, const uint64_t* pow5, int f, uint32_t want, int* end,
+                                          uint64_t* bits) {
+  uint32_t x0, x1, val, c;
+  int p = f;
+  const bool neg = signed_chars8(S, &p, &x0, &x1);
+  int nd = digits8(x0, x1, &val, &c);
+  uint64_t v = val;
+  p += nd;
+  more_digits(S, nd == 8, &p, &nd, &v, &c);
+  int q = 0;
+  if (c == '.') {
+    ++p;
+    q = nd;
+    more_digits(S, true, &p, &nd, &v, &c);
+    q -= nd;
+  }
+  bool ok = (uint32_t)(nd - 1) < 19u;
+  if ((c | 0x20u) == 'e') {
+    uint32_t ex;
+    ++p;
+    const bool eneg = signed_chars8(S, &p, &x0, &x1);
+    const int k = digits8(x0, x1, &ex, &c);
+    ok &= (uint32_t)(k - 1) < 3u;
+    p += k;
+    q += eneg ? -(int)ex : (int)ex;
+  }
+  ok &= (c == want) & ((uint32_t)(q + kMaxPow) <= 2u * kMaxPow);
+  double d = neg ? -0.0 : 0.0;
+  if (ok && v != 0) ok = scaled_decimal(pow5, v, q, neg, &d);
+  *bits = (uint64_t)__double_as_longlong(d);
+  *end = p;
+  return ok;
 }
 
 // parse_field out of line, for the fields fast_field does not take.
@@ -520,56 +625,64 @@ __device__ __attribute__((noinline)) Parsed slow_field(Stage S, int f, bool is_i
   return Parsed{r, bits};
 }
 
-// Parses the line starting at L (P fields) into row[0..P), each field through
-// fast_field first, else parse_field.  Returns the position of its end ('\n'
-// or nend), or -1 - end on a malformed line (*bad_at = the offending field's
-// offset).
-template <int P>
-__device__ inline int parse_line_p(const Args& a, Cur& C, int L, uint64_t (&row)[P], int* bad_at) {
-  int f = L;
-#pragma unroll
+// Parses the line starting at L (P fields), handing (c, value bits) of each field
+// to put.  A field that the fast forms do not cover (a line that ends with the
+// text among them) goes through parse_field.  Returns the position of the line's
+// end ('\n' or nend), or -1 - end on a malformed line (*bad_at = the offending
+// field's offset); the rest of such a line is not looked at, and put gets zeros.
+template <int P, typename Put>
+__device__ inline int parse_line_p(uint32_t intmask, const Stage& S, const uint64_t* pow5, int L, int* bad_at, Put put) {
+  int f = L, r = L, stop = 0;
+  bool bad = false;
+#pragma unroll 1
   for (int c = 0; c < P; ++c) {
-    const bool is_int = (a.intmask >> c) & 1u;
-    uint64_t bits = 0;
-    int r, term;
-    if (!fast_field(C, f, is_int, &r, &term, &bits)) {
-      const Parsed sp = slow_field(*C.S, f, is_int);
-      r = sp.pos;
-      bits = sp.bits;
-      term = r >= 0 ? C.at(r) : 0;
-    }
-    const bool last = c == P - 1;
-    const bool ok = r >= 0 && (last ? (term == '\n' || term == -1) : term == ',');
-    if (!ok) {
-      *bad_at = f;
-      int e = r >= 0 ? r : -1 - r;  // skip to the end of the line
-      for (;;) {
-        const int ch = C.at(e);
-        if (ch == '\n' || ch < 0) break;
-        ++e;
+    const bool is_int = (intmask >> c) & 1u, last = c == P - 1;
+    const uint32_t want = last ? '\n' : ',';
+    uint64_t bits;
+    const bool fast = is_int ? fast_int(S, f, want, &r, &bits) : fast_decimal_field(S, pow5, f, want, &r, &bits);
+    if (!fast) {
+      if (!bad) {
+        const Parsed sp = slow_field(S, f, is_int);
+        r = sp.pos;
+        bits = sp.bits;
+        const int term = r >= 0 ? Cur(S).at(r) : 0;
+        bad = !(r >= 0 && (term == (int)want || (last && term == -1)));
+        if (bad) {
+          *bad_at = f;
+          int e = r >= 0 ? r : -1 - r;  // skip to the end of the line
+          for (;;) {
+            const int ch = Cur(S).at(e);
+            if (ch == '\n' || ch < 0) break;
+            ++e;
+          }
+          stop = e;
+        }
       }
-      return -1 - e;
+      if (bad) {
+        bits = 0;
+        r = stop - 1;
+      }
     }
-    row[c] = bits;
-    if (last) return r;
+    put(c, bits);
     f = r + 1;
   }
-  return f;
+  return bad ? -1 - stop : r;
 }
 
-// Copies the text [w0r, w0r + nr) of buf into LDS (padded 16 bytes per 256)
-// on a 16-byte aligned origin: LDS position i holds stream byte w0r - sh + i,
+// Copies the text [w0r, w0r + nr) of buf into LDS on a
+// 16-byte aligned origin: LDS position i holds stream byte w0r - sh + i,
 // sh = the misalignment of buf + w0r, which is returned.  Every thread issues
 // its aligned 16-byte loads before its first LDS write; the vectors at the
 // two ends are assembled byte by byte so that nothing outside
 // [buf + w0r - (w0r >= 16 ? sh : 0), buf + w0r + nr) is read (positions before
 // w0r hold zeros when w0r < 16, earlier stream bytes otherwise).
-__device__ inline int stage_text(const char* buf, int64_t w0r, int nr, unsigned char* s_buf) {
+__device__ inline int stage_text(const char* buf, int64_t w0r, int nr, __attribute__((address_space(3))) unsigned char* s_buf,
+                                 uint64_t* s_pow5) {
   const int sh = (int)((uintptr_t)(buf + w0r) & 15u);
   const char* base = buf + w0r - sh;
   const int tot = sh + nr;
   const int nv = (tot + 15) >> 4;
-  constexpr int NVT = (STAGE + 15) / 16 / kThreads + 1;
+  constexpr int NVT = (stage_bytes(SEG_MAX) + 15) / 16 / kThreads + 1;
   u32x4 q[NVT];
 #pragma unroll
   for (int u = 0; u < NVT; ++u) {
@@ -590,10 +703,11 @@ __device__ inline int stage_text(const char* buf, int64_t w0r, int nr, unsigned 
       }
     }
   }
+  copy_pow5(s_pow5);
 #pragma unroll
   for (int u = 0; u < NVT; ++u) {
     const int v = (int)threadIdx.x + u * kThreads;
-    if (v < nv) *(__attribute__((address_space(3))) u32x4*)(s_buf + pad(16 * v)) = q[u];
+    if (v < nv) *(__attribute__((address_space(3))) u32x4*)(s_buf + 16 * v) = q[u];
   }
   return sh;
 }
@@ -603,14 +717,13 @@ __device__ inline int stage_text(const char* buf, int64_t w0r, int nr, unsigned 
 // its slice (slice positions, a multiple of 16 up to SLICE_MAX) in one pass
 // of 16-byte LDS reads, keeping them as a bit
 // mask (a '\n' byte is a zero byte of v ^ 0x0a0a0a0a); a workgroup scan of the
-// counts places them in s_ls in stream order when they fit (<= MAXLS).
+// counts places them in s_ls in stream order when they fit (<= maxls).
 // Returns their number; *c0, *c1 receive this thread's slice and *before the
 // number of line starts in earlier slices (the index of its first line).
 // Contains barriers: every thread of the workgroup calls it.
-__device__ inline int line_starts(const unsigned char* s_buf, int64_t w0, int s0r, int s1r, int slice,
-                                  unsigned short* s_ls, int* s_wsum, int* c0_out, int* c1_out,
+__device__ inline int line_starts(lds_text s_buf, int64_t w0, int s0r, int s1r, int slice,
+                                  int maxls, unsigned short* s_ls, int* s_wsum, int* c0_out, int* c1_out,
                                   int* before_out) {
-  static_assert(SLICE * kThreads == SEG && SLICE % 16 == 0 && SLICE_MAX % 16 == 0, "one slice per thread");
   constexpr int NV = SLICE_MAX / 16 + 1;     // 16-byte reads per slice (it may start mid-vector)
   constexpr int NM = (16 * NV + 31) / 32;    // 32-bit mask words
   const int c0 = s0r + (int)threadIdx.x * slice;
@@ -629,15 +742,13 @@ __device__ inline int line_starts(const unsigned char* s_buf, int64_t w0, int s0
     for (int k = 0; k < NV; ++k) {
       const int m16 = mb + 16 * k;
       if (m16 < mhi) {
-        const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(
-            (const __attribute__((address_space(3))) unsigned char*)s_buf + pad(m16));
+        const u32x4 v = *(const __attribute__((address_space(3))) u32x4*)(s_buf + m16);
         uint32_t bits = 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const uint32_t x = v[e] ^ 0x0A0A0A0Au;
           const uint32_t z = ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);  // 0x80 per '\n'
-          // bits 7, 15, 23, 31 -> bits 0..3 (the four shifted copies do not overlap)
-          bits |= (((z >> 7) * 0x204081u) >> 21 & 0xFu) << (4 * e);
+          bits |= __builtin_amdgcn_udot4(z >> 7, 0x08040201u, 0u, false) << (4 * e);
         }
         // keep positions in [mlo, mhi)
         const int b0 = mlo - m16, b1 = mhi - m16;
@@ -664,7 +775,7 @@ __device__ inline int line_starts(const unsigned char* s_buf, int64_t w0, int s0
     if (k < wv) before += s_wsum[k];
     total += s_wsum[k];
   }
-  if (total <= MAXLS && c0 < c1) {
+  if (total <= maxls && c0 < c1) {
     int at = before;
     if (w0 + c0 == 0) s_ls[at++] = (unsigned short)c0;
 #pragma unroll
@@ -689,89 +800,111 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // LDS accesses across it (the rows a wave stages are read by other lanes).
 __device__ inline void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// Products on the FP64 matrix cores: each wave stages the shifted rows of its
-// lanes' lines, 32 at a time, in its own LDS rows; for v_mfma_f64_16x16x4f64
-// a lane then holds column (lane % 16) of staged row 4 m + lane / 16, at once
-// its element of the A operand (column i, row k) and of the B operand (row k,
-// column j), so 8 products give the 32 rows' upper triangle; absent or
-// malformed lines stage zeros.  The column sums are kept per lane.  For
-// integer columns every partial sum is an integer below 2^53 under the guard
-// checked by the merge, so the matrix-core sums are exact; the order of all
-// sums is fixed, so results are bitwise reproducible.
-template <int P>
-__global__ __launch_bounds__(kThreads, 2) void k_text(Args a) {
-  constexpr int T = P * (P + 1) / 2;
-  constexpr int NWV = kThreads / 64;
-  __shared__ __attribute__((aligned(16))) unsigned char s_buf[STAGE_PADDED];
-  __shared__ uint64_t s_rows[NWV][32 * P];  // per wave: 32 staged rows (raw field bits)
-  __shared__ int s_valid[NWV][32];
-  __shared__ uint64_t sKb[P];
-  __shared__ unsigned long long s_n;
-  __shared__ unsigned short s_ls[MAXLS];  // line starts (stage-relative)
-  __shared__ int s_wsum[NWV];
-  static_assert(STAGE_PADDED >= NWV * 5 * 64 * 8, "the final reduction reuses the text stage");
-  const int64_t s0 = (int64_t)blockIdx.x * a.seg;
-  const int64_t s1 = min(s0 + (int64_t)a.seg, a.nend);
+// What the two text kernels share: the stage, the line table and this thread's
+// walk over its lines.  Threads take the lines of the table in turn; when there
+// are more than MAXLS, each takes those that start in its own slice.
+struct Lines {
+  Stage S;
+  int64_t w0;   // stream offset of staged byte 0
+  int total, before;
+  bool table;
+  int idx, Lc, c1;
+};
+
+// Stages this workgroup's segment of the chunk and finds its lines.  Contains
+// barriers, the last one after everything it writes.
+__device__ inline Lines open_lines(const Args& a, __attribute__((address_space(3))) unsigned char* s_buf, uint64_t* s_pow5, unsigned short* s_ls, int* s_wsum) {
+  Lines n;
+  const int64_t s0 = (int64_t)blockIdx.x * a.seg, s1 = min(s0 + (int64_t)a.seg, a.nend);
   const int64_t w0r = s0 >= 16 ? s0 - 16 : 0;  // first stream byte staged
   const int64_t w1 = min(s1 + (int64_t)MAXLINE, a.nbytes);
-  // w0: stream offset of LDS position 0 (the staging origin is aligned)
-  const int64_t w0 = w0r - stage_text(a.buf, w0r, (int)(w1 - w0r), s_buf);
-  const int n = (int)(w1 - w0);
-  if (threadIdx.x == 0) s_n = 0;
+  // the staging origin is aligned
+  n.w0 = w0r - stage_text(a.buf, w0r, (int)(w1 - w0r), s_buf, s_pow5);
+  n.S = Stage{s_buf, (int)(min(a.nend, w1) - n.w0)};
   __syncthreads();
-  const Stage S{s_buf, w0, n, (int)(min(a.nend, w0 + (int64_t)n) - w0)};
-  const int s0r = (int)(s0 - w0), s1r = (int)(s1 - w0);  // relative positions
-  Cur C(S);
+  if (threadIdx.x < kPast) s_buf[n.S.lim + (int)threadIdx.x] = 0xFFu;
+  int c0;
+  n.total = line_starts(s_buf, n.w0, (int)(s0 - n.w0), (int)(s1 - n.w0), slice_of(a.seg), a.maxls, s_ls, s_wsum, &c0, &n.c1, &n.before);
+  n.table = n.total <= a.maxls;
+  n.idx = threadIdx.x;
+  n.Lc = c0;
+  if (!n.table && n.w0 + n.Lc > 0)
+    while (n.Lc < n.c1 && Cur(n.S).at(n.Lc - 1) != '\n') ++n.Lc;
+  return n;
+}
 
-  int c0, c1, before;
-  const int total = line_starts(s_buf, w0, s0r, s1r, a.seg / kThreads, s_ls, s_wsum, &c0, &c1, &before);
-  (void)before;
-  const bool table = total <= MAXLS;
+// This thread's next line: its position in *L (false when it has none left);
+// after parsing it the caller sets Lc to the byte after it.
+__device__ inline bool next_line(Lines& n, const unsigned short* s_ls, int* L) {
+  if (!n.table) {
+    *L = n.Lc;
+    return n.Lc < n.c1;
+  }
+  const bool have = n.idx < n.total;
+  *L = have ? (int)s_ls[n.idx] : 0;
+  n.idx += kThreads;
+  return have;
+}
+
+// Products on the FP64 matrix cores: each wave parses 64 lines into its own LDS
+// rows; for v_mfma_f64_16x16x4f64 a lane then holds column (lane % 16) of row
+// 4 m + lane / 16, at once its element of the A operand (column i, row k) and
+// of the B operand (row k, column j), so 16 products give the 64 rows' upper
+// triangle; absent or malformed lines count as zeros.  The column sums are kept
+// per lane.  For integer columns every partial sum is an integer below 2^53
+// under the guard checked by the merge, so the matrix-core sums are exact; the
+// order of all sums is fixed, so results are bitwise reproducible.
+template <int P>
+__global__ __launch_bounds__(kThreads) void k_text(Args a) {
+  constexpr int T = P * (P + 1) / 2;
+  constexpr int LD = row_words(P);
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_buf[];  // text_lds(a.seg, a.maxls)
+  __shared__ uint64_t s_rows[kWaves * 64 * LD + 16];  // per wave: 64 parsed rows, shifted
+  __shared__ __attribute__((aligned(16))) uint64_t s_pow5[kPow5Words];
+  __shared__ uint64_t sKb[P];
+  __shared__ int s_wsum[kWaves];
+  unsigned short* s_ls = (unsigned short*)(s_buf + stage_bytes(a.seg));  // line starts (stage-relative)
+  static_assert(stage_bytes(SEG_MIN) >= kWaves * 5 * 64 * 8, "the final reduction reuses the text stage");
+  const acc::Args& ra = a.acc;
+  uint64_t* out = ra.rec + (int64_t)blockIdx.x * (2 + 2 * P + T);
+  // this thread's product (register r of lane l holds D[4r + l/16][l%16]) and column in the record, looked up before they are needed
+  static_assert(kThreads == 4 * 64, "one product per thread");
+  const int pi = 4 * (threadIdx.x >> 6) + ((threadIdx.x & 63) >> 4), pj = threadIdx.x & 15;
+  const bool prod = pi <= pj && pj < P;
+  const int pdst = prod ? 2 + P + ra.dst[P + pi * P - pi * (pi - 1) / 2 + (pj - pi)] : 0;
+  const int cdst = threadIdx.x < P ? 2 + P + ra.dst[threadIdx.x] : 0;
+  const int kdst = threadIdx.x < P ? 2 + ra.kdst[threadIdx.x] : 0;
+  Lines n = open_lines(a, (__attribute__((address_space(3))) unsigned char*)s_buf, s_pow5, s_ls, s_wsum);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, rsub = lane >> 4;
-  uint64_t* wr = s_rows[wave];
-  int* wv = s_valid[wave];
+  uint64_t* wr = s_rows + wave * 64 * LD;
   d4 acc = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};  // even and odd steps
   double colsum = 0.0;
-  unsigned long long nrows = 0;
+  int nrows = 0;  // of this wave
   int first_bad = INT32_MAX;
-  // this lane's column of the products and its shift
-  const bool colv = col < P;
-  const bool colint = colv && ((a.intmask >> col) & 1u);
-  double Kc = 0.0;
-  int64_t Kic = 0;
-  // this lane's lines: table entries threadIdx.x, + 256, ...; or, when the
-  // table overflowed, the lines starting in its own slice
-  int idx = threadIdx.x;
-  int Lc = c0;
-  if (!table && w0 + Lc > 0)
-    while (Lc < c1 && C.at(Lc - 1) != '\n') ++Lc;
+  // the value of column c less its shift, as the FP64 number the products take
+  const auto shifted = [&](int c, uint64_t bits) {
+    return ((a.intmask >> c) & 1u) ? (double)((int64_t)bits - (int64_t)sKb[c])
+                                   : __longlong_as_double((long long)bits) - __longlong_as_double((long long)sKb[c]);
+  };
   for (int round = 0;; ++round) {
-    bool have;
     int L;
-    if (table) {
-      have = idx < total;
-      L = have ? (int)s_ls[idx] : 0;
-      idx += kThreads;
-    } else {
-      have = Lc < c1;
-      L = Lc;
-    }
+    const bool have = next_line(n, s_ls, &L);
     // every wave runs round 0 (its barrier); later rounds while a lane has a line
     if (round > 0 && __builtin_amdgcn_ballot_w64(have) == 0) break;
-    uint64_t row[P];
     bool ok = false;
     if (have) {
       int bad_at = INT32_MAX;
-      const int end = parse_line_p<P>(a, C, L, row, &bad_at);
+      const int end = parse_line_p<P>(a.intmask, n.S, s_pow5, L, &bad_at, [&](int c, uint64_t bits) {
+        wr[lane * LD + c] = round > 0 ? (uint64_t)__double_as_longlong(shifted(c, bits)) : bits;
+      });
       ok = end >= 0;
       if (ok) {
-        ++nrows;
-        Lc = end + 1;
+        n.Lc = end + 1;
       } else {
         first_bad = min(first_bad, bad_at);
-        Lc = (-1 - end) + 1;
+        n.Lc = (-1 - end) + 1;
       }
     }
     if (round == 0) {
@@ -779,89 +912,78 @@ __global__ __launch_bounds__(kThreads, 2) void k_text(Args a) {
       // line when the table holds them all), zeros if it does not parse
       if (threadIdx.x == 0) {
 #pragma unroll
-        for (int c = 0; c < P; ++c) sKb[c] = ok ? row[c] : 0;
+        for (int c = 0; c < P; ++c) sKb[c] = ok ? wr[c] : 0;
       }
       __syncthreads();
-      const uint64_t kb = colv ? sKb[col] : 0;
-      Kic = colint ? (int64_t)kb : 0;
-      Kc = colint ? (double)Kic : __longlong_as_double((long long)kb);
+      if (ok)
+#pragma unroll
+        for (int c = 0; c < P; ++c) wr[lane * LD + c] = (uint64_t)__double_as_longlong(shifted(c, wr[lane * LD + c]));
     }
+    const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
+    nrows += __builtin_popcountll(okm);
+    if (!ok)
+      for (int c = 0; c < P; ++c) wr[lane * LD + c] = 0;  // 0.0: adds nothing
+    wave_lds_sync();
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      if ((lane >> 5) == h) {
-        if (ok) {
+    for (int h = 0; h < 4; ++h) {
+      if (((okm >> (16 * h)) & 0xFFFFu) == 0) continue;  // 16 absent rows
 #pragma unroll
-          for (int c = 0; c < P; ++c) wr[(lane & 31) * P + c] = row[c];
-        }
-        wv[lane & 31] = ok;
-      }
-      wave_lds_sync();
-#pragma unroll
-      for (int m = 0; m < 8; ++m) {
-        const int sr = 4 * m + rsub;
-        double v = 0.0;
-        if (colv && wv[sr]) {
-          const uint64_t b = wr[sr * P + col];
-          v = colint ? (double)((int64_t)b - Kic) : __longlong_as_double((long long)b) - Kc;
-        }
+      for (int m = 4 * h; m < 4 * h + 4; ++m) {
+        // lanes of columns P and up hold some other value: only rows and columns
+        // of the product that nobody reads
+        const double v = __longlong_as_double((long long)wr[(4 * m + rsub) * LD + col]);
         colsum += v;
         if (m & 1) acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc2, 0, 0, 0);
         else acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
       }
-      wave_lds_sync();
     }
+    wave_lds_sync();
   }
   if (first_bad != INT32_MAX) {
-    atomicMin(&a.status->parse_off, (unsigned long long)(a.base_off + w0 + first_bad));
+    atomicMin(&a.status->parse_off, (unsigned long long)(a.base_off + n.w0 + first_bad));
     atomicOr(&a.status->bits, ST_PARSE);
   }
-  atomicAdd(&s_n, nrows);
+  if (lane == 0) s_wsum[wave] = nrows;
   __syncthreads();  // the text stage is free: it holds the per-wave sums now
   double* red = (double*)s_buf;  // [wave][4 registers + 1 sum][64 lanes]
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[(wave * 5 + r) * 64 + lane] = acc[r] + acc2[r];
   red[(wave * 5 + 4) * 64 + lane] = colsum;
   __syncthreads();
-  const acc::Args& ra = a.acc;
-  uint64_t* out = ra.rec + (int64_t)blockIdx.x * (2 + 2 * P + T);
-  for (int e = threadIdx.x; e < 4 * 64; e += kThreads) {
-    // register r of lane l holds D[4r + l/16][l%16]
-    const int r = e >> 6, l = e & 63;
-    const int i = 4 * r + (l >> 4), j = l & 15;
-    if (i <= j && j < P) {
-      double v = red[r * 64 + l];
+  if (prod) {
+    double v = red[threadIdx.x];
 #pragma unroll
-      for (int w = 1; w < NWV; ++w) v += red[(w * 5 + r) * 64 + l];
-      const int t = i * P - i * (i - 1) / 2 + (j - i);
-      out[2 + P + ra.dst[P + t]] = (uint64_t)__double_as_longlong(v);
-    }
+    for (int w = 1; w < kWaves; ++w) v += red[w * 5 * 64 + threadIdx.x];
+    out[pdst] = (uint64_t)__double_as_longlong(v);
   }
   if (threadIdx.x < P) {
     const int c = threadIdx.x;
     double v = 0.0;
 #pragma unroll
-    for (int w = 0; w < NWV; ++w)
+    for (int w = 0; w < kWaves; ++w)
 #pragma unroll
       for (int k = 0; k < 4; ++k) v += red[(w * 5 + 4) * 64 + c + 16 * k];
-    out[2 + P + ra.dst[c]] = (uint64_t)__double_as_longlong(v);
+    out[cdst] = (uint64_t)__double_as_longlong(v);
     // the shift word: the int64 value for integer columns, FP64 bits
     // otherwise, i.e. sKb as parsed
-    out[2 + ra.kdst[c]] = sKb[c];
+    out[kdst] = sKb[c];
   }
   if (threadIdx.x == 0) {
-    out[0] = (uint64_t)s_n;
+    uint64_t rows = 0;
+    for (int w = 0; w < kWaves; ++w) rows += s_wsum[w];
+    out[0] = rows;
     out[1] = 0;
   }
 }
 
 // Position after the last '\n' in [0, n), or 0 when there is none; one
-// workgroup scans backwards in SEG-byte windows.
+// workgroup scans backwards in SEG_MAX-byte windows.
 __global__ void k_last_newline(const char* buf, int64_t n, int64_t* out) {
   __shared__ unsigned long long best;
   if (threadIdx.x == 0) best = 0;
   __syncthreads();
-  for (int64_t hi = n; hi > 0; hi -= SEG) {
-    const int64_t lo = hi > SEG ? hi - SEG : 0;
+  for (int64_t hi = n; hi > 0; hi -= SEG_MAX) {
+    const int64_t lo = hi > SEG_MAX ? hi - SEG_MAX : 0;
     for (int64_t i = lo + threadIdx.x; i < hi; i += blockDim.x)
       if (buf[i] == '\n') atomicMax(&best, (unsigned long long)(i + 1));
     __syncthreads();
@@ -897,51 +1019,59 @@ __global__ __launch_bounds__(1024) void k_line_density(const char* buf, int64_t 
 
 // ---- CSV -> fixed-width binary rows ------------------------------------------
 
-// Line starts per segment ([s0, s1) as in k_text), read from global memory as
-// aligned 16-byte vectors (a byte per load ran at 0.8 TB/s, 189 us for 150 MB of
-// text; 32 us so); the bytes before the first vector and after the last one are
-// read singly, so nothing outside the chunk is.
-__global__ __launch_bounds__(kThreads) void k_seg_lines(const char* buf, int64_t nend, int64_t* counts) {
-  __shared__ int s_sum[kThreads / 64];
-  const int64_t s0 = (int64_t)blockIdx.x * SEG;
-  const int64_t s1 = min(s0 + (int64_t)SEG, nend);
-  // newlines at m in [max(s0 - 1, 0), s1 - 1) start the lines after s0
-  const char* b0 = buf + (s0 > 0 ? s0 - 1 : 0);
-  const int n = (int)(buf + (s1 - 1) - b0);
-  const int head = min(n, (int)(-(uintptr_t)b0 & 15u));
-  const int nv = (n - head) >> 4, tail = head + 16 * nv;
+// Line starts per unit, one wave each, read from global memory as aligned
+// 16-byte vectors (a byte per load ran at 0.8 TB/s, 189 us for 150 MB of text;
+// 32 us so); the bytes before the first vector and after the last one are read
+// singly, so nothing outside the chunk is.  first[unit] receives the number of
+// line starts in the earlier units of its group, counts[group] the group's.
+constexpr int kGroup = 16;  // units per workgroup
+__global__ __launch_bounds__(64 * kGroup) void k_unit_lines(const char* buf, int64_t nend, int64_t* counts, int32_t* first) {
+  __shared__ int s_sum[kGroup];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t unit = (int64_t)blockIdx.x * kGroup + wave;
+  const int64_t s0 = unit * UNIT;
+  const int64_t s1 = min(s0 + (int64_t)UNIT, nend);
   int mine = 0;
-  constexpr int NV = SEG / 16 / kThreads + 1;
-  u32x4 q[NV];
+  if (s0 < s1) {
+    // newlines at m in [max(s0 - 1, 0), s1 - 1) start the lines after s0
+    const char* b0 = buf + (s0 > 0 ? s0 - 1 : 0);
+    const int n = (int)(buf + (s1 - 1) - b0);
+    const int head = min(n, (int)(-(uintptr_t)b0 & 15u));
+    const int nv = (n - head) >> 4, tail = head + 16 * nv;
+    constexpr int NV = UNIT / 16 / 64 + 1;
+    u32x4 q[NV];
 #pragma unroll
-  for (int u = 0; u < NV; ++u) {
-    const int v = (int)threadIdx.x + u * kThreads;
-    q[u] = v < nv ? *(const u32x4*)(b0 + head + 16 * v) : (u32x4){0u, 0u, 0u, 0u};
+    for (int u = 0; u < NV; ++u) {
+      const int v = lane + u * 64;
+      q[u] = v < nv ? *(const u32x4*)(b0 + head + 16 * v) : (u32x4){0u, 0u, 0u, 0u};
+    }
+#pragma unroll
+    for (int u = 0; u < NV; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t x = q[u][e] ^ 0x0A0A0A0Au;
+        mine += __builtin_popcount(~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu));  // 0x80 per '\n'
+      }
+    if (lane < head) mine += b0[lane] == '\n';
+    if (lane < n - tail) mine += b0[tail + lane] == '\n';
+    if (s0 == 0 && lane == 0) ++mine;  // the stream's first line
   }
 #pragma unroll
-  for (int u = 0; u < NV; ++u)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const uint32_t x = q[u][e] ^ 0x0A0A0A0Au;
-      mine += __builtin_popcount(~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu));  // 0x80 per '\n'
-    }
-  if ((int)threadIdx.x < head) mine += b0[threadIdx.x] == '\n';
-  if ((int)threadIdx.x < n - tail) mine += b0[tail + threadIdx.x] == '\n';
-  if (s0 == 0 && threadIdx.x == 0 && s1 > 0) ++mine;  // the stream's first line
-#pragma unroll
   for (int d = 32; d >= 1; d >>= 1) mine += __shfl_down(mine, d, 64);
-  if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = mine;
+  if (lane == 0) s_sum[wave] = mine;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int t = 0;
-    for (int k = 0; k < kThreads / 64; ++k) t += s_sum[k];
-    counts[blockIdx.x] = t;
+  if (threadIdx.x < kGroup) {
+    int before = 0;
+    for (int w = 0; w < (int)threadIdx.x; ++w) before += s_sum[w];
+    first[(int64_t)blockIdx.x * kGroup + threadIdx.x] = before;
+    if (threadIdx.x == kGroup - 1) counts[blockIdx.x] = before + s_sum[kGroup - 1];
   }
 }
 
-// Exclusive prefix sum of counts[0 .. n) in place, the total in counts[n]: one
-// workgroup, a run of consecutive counts per thread.
-__global__ __launch_bounds__(1024) void k_scan_counts(int64_t* counts, int64_t n) {
+// Exclusive prefix sum of counts[0 .. n) in place, the total in *total: one
+// workgroup, a run of consecutive counts per thread.  Also clears the
+// conversion's status.
+__global__ __launch_bounds__(1024) void k_scan_counts(int64_t* counts, int64_t n, int64_t* total, DevStatus* status) {
   __shared__ int64_t s_wave[16];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int64_t per = (n + 1023) / 1024, i0 = min(per * (int64_t)threadIdx.x, n), i1 = min(i0 + per, n);
@@ -963,12 +1093,16 @@ __global__ __launch_bounds__(1024) void k_scan_counts(int64_t* counts, int64_t n
     counts[i] = at;
     at += v;
   }
-  if (threadIdx.x == 1023) counts[n] = at;
+  if (threadIdx.x == 1023) {
+    *total = at;
+    *status = DevStatus{0u, 0u, ~0ull};
+  }
 }
 
 struct ConvArgs {
   Args t;                    // text, its line limit, p, integer mask, offsets, status
-  const int64_t* seg_base;   // first output row of each segment
+  const int64_t* group_base;  // first output row of each group of units
+  const int32_t* first;       // rows of a unit's group before it
   char* out[16];             // column c of row r at out[c] + r * stride[c]
   int64_t stride[16];
   int32_t dtype[16];         // STATS_I32 / STATS_I64 / STATS_F64
@@ -999,89 +1133,103 @@ __device__ inline bool store_field(const ConvArgs& a, int c, int64_t r, uint64_t
   }
 }
 
+// Each wave parses 64 lines into its LDS rows, then writes them out with
+// neighbouring lanes on neighbouring columns, so that a row's columns leave in
+// one piece (a lane storing its own row wrote 8 bytes every row stride).
 template <int P>
 __global__ __launch_bounds__(kThreads) void k_text_convert(ConvArgs a) {
-  __shared__ __attribute__((aligned(16))) unsigned char s_buf[STAGE_PADDED];
-  __shared__ unsigned short s_ls[MAXLS];
-  __shared__ int s_wsum[kThreads / 64];
+  constexpr int LD = row_words(P);
+  constexpr int CW = P <= 1 ? 1 : P <= 2 ? 2 : P <= 4 ? 4 : P <= 8 ? 8 : 16;  // lanes per row when writing
+  constexpr int RW = 64 / CW;                                                 // rows per write
+  extern __shared__ __attribute__((aligned(16))) unsigned char s_buf[];  // text_lds(t.seg, t.maxls)
+  __shared__ uint64_t s_rows[kWaves][64 * LD];
+  __shared__ __attribute__((aligned(16))) uint64_t s_pow5[kPow5Words];
+  __shared__ int s_wsum[kWaves];
   const Args& t = a.t;
-  const int64_t s0 = (int64_t)blockIdx.x * SEG;
-  const int64_t s1 = min(s0 + (int64_t)SEG, t.nend);
-  const int64_t w0r = s0 >= 16 ? s0 - 16 : 0;  // first stream byte staged
-  const int64_t w1 = min(s1 + (int64_t)MAXLINE, t.nbytes);
-  // w0: stream offset of LDS position 0 (the staging origin is aligned)
-  const int64_t w0 = w0r - stage_text(t.buf, w0r, (int)(w1 - w0r), s_buf);
-  const int n = (int)(w1 - w0);
-  __syncthreads();
-  const Stage S{s_buf, w0, n, (int)(min(t.nend, w0 + (int64_t)n) - w0)};
-  const int s0r = (int)(s0 - w0), s1r = (int)(s1 - w0);
-  Cur C(S);
-  int c0, c1, before;
-  const int total = line_starts(s_buf, w0, s0r, s1r, SLICE, s_ls, s_wsum, &c0, &c1, &before);
-  const int64_t base = a.seg_base[blockIdx.x];
+  unsigned short* s_ls = (unsigned short*)(s_buf + stage_bytes(t.seg));
+  Lines n = open_lines(t, (__attribute__((address_space(3))) unsigned char*)s_buf, s_pow5, s_ls, s_wsum);
+  const int64_t unit = (int64_t)blockIdx.x * (t.seg / UNIT);
+  const int64_t base = a.group_base[unit / kGroup] + a.first[unit];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int col = lane % CW, rsub = lane / CW;
+  const bool colv = col < P;
+  uint64_t* wr = s_rows[wave];
   int first_bad = INT32_MAX;
-  // parses line L (k-th of the segment) into output row base + k
-  auto put_line = [&](int L, int k) -> int {
-    uint64_t row[P];
-    int bad_at = INT32_MAX;
-    const int end = parse_line_p<P>(t, C, L, row, &bad_at);
-    if (end < 0) {
-      first_bad = min(first_bad, L);  // reported by the line's first byte
-      return -end;  // (-1 - e) + 1: past the offending line
+  int row = n.table ? (int)threadIdx.x : n.before;  // this thread's line among the segment's
+  for (;;) {
+    int L;
+    const bool have = next_line(n, s_ls, &L);
+    if (__builtin_amdgcn_ballot_w64(have) == 0) break;
+    bool ok = false;
+    if (have) {
+      int bad_at = INT32_MAX;
+      const int end = parse_line_p<P>(t.intmask, n.S, s_pow5, L, &bad_at,
+                                      [&](int c, uint64_t bits) { wr[lane * LD + c] = bits; });
+      ok = end >= 0;
+      if (!ok) first_bad = min(first_bad, L);  // reported by the line's first byte
+      n.Lc = (ok ? end : -1 - end) + 1;
     }
-#pragma unroll
-    for (int c = 0; c < P; ++c)
-      if (!store_field(a, c, base + k, row[c], (t.intmask >> c) & 1u)) first_bad = min(first_bad, L);
-    return end + 1;
-  };
-  if (total <= MAXLS) {
-    for (int k = threadIdx.x; k < total; k += kThreads) (void)put_line((int)s_ls[k], k);
-  } else {
-    // too many lines for the table: each thread walks its own slice
-    int L = c0, k = before;
-    if (w0 + L > 0)
-      while (L < c1 && C.at(L - 1) != '\n') ++L;
-    while (L < c1) L = put_line(L, k++);
+    const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
+    wave_lds_sync();
+#pragma unroll 4
+    for (int m = 0; m < CW; ++m) {
+      const int sr = m * RW + rsub;
+      const int k = __shfl(row, sr, 64), Ls = __shfl(L, sr, 64);
+      if (colv && ((okm >> sr) & 1u)) {
+        if (!store_field(a, col, base + k, wr[sr * LD + col], (t.intmask >> col) & 1u)) first_bad = min(first_bad, Ls);
+      }
+    }
+    wave_lds_sync();
+    row += n.table ? kThreads : 1;
   }
   if (first_bad != INT32_MAX) {
-    atomicMin(&t.status->parse_off, (unsigned long long)(t.base_off + w0 + first_bad));
+    atomicMin(&t.status->parse_off, (unsigned long long)(t.base_off + n.w0 + first_bad));
     atomicOr(&t.status->bits, ST_PARSE);
   }
 }
 
 template <int P>
 void launch_convert_p(const ConvArgs& a, int64_t nblocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_text_convert<P>, dim3((unsigned)nblocks), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(k_text_convert<P>, dim3((unsigned)nblocks), dim3(kThreads), text_lds(a.t.seg, a.t.maxls), s, a);
 }
 
 template <int P>
 void launch_text_p(const Args& a, int64_t nblocks, hipStream_t s) {
-  hipLaunchKernelGGL(k_text<P>, dim3((unsigned)nblocks), dim3(kThreads), 0, s, a);
+  hipLaunchKernelGGL(k_text<P>, dim3((unsigned)nblocks), dim3(kThreads), text_lds(a.seg, a.maxls), s, a);
 }
 
 }  // namespace text
 
 using namespace text;
 
-// Segment size of the fused kernel for lines of mean length ell bytes.  A
-// workgroup parses its lines 256 at a time (one per thread); the last round
-// runs with the lanes that still have a line, and the workgroup holds its
-// compute unit until then, so a segment whose line count just passes a
-// multiple of 256 wastes most of a round.  Each multiple of 4096 from 16 KiB
-// to SEG_MAX is scored as the filled share of its rounds (its count taken 3 %
-// high for the spread between segments) times seg / (seg + 4.8 KiB) (the
-// fixed cost of a workgroup: the staged overlap, the line table, the final
-// sums and the record), halved when the lines would overflow the line table
-// (MAXLS; its fallback scans slices); the best one is used.  Without a
-// measurement: 32 KiB.
-static int pick_text_seg(double ell) {
-  if (!(ell > 0.0)) return SEG;
-  int best = SEG;
+// Line starts kept in the table for a segment of lines of mean length ell (a
+// quarter more than expected).
+static int pick_maxls(double ell, int seg) {
+  return ell > 0.0 ? (int)std::min<double>(MAXLS, 64 + 1.25 * seg / ell) & ~7 : MAXLS;
+}
+
+// Segment size of the text kernels for lines of mean length ell bytes and p
+// columns.  A workgroup parses its lines 256 at a time (one per thread); a last
+// round with few lines takes as long as a full one, and the fixed part (staging,
+// line table, final sums, record) about 1.2 rounds.  LDS (text and parsed rows)
+// decides how many workgroups share a compute unit; each further one lengthens
+// the others by about 18 %.  Every whole number of units from SEG_MIN to SEG_MAX is
+// scored by the lines per time of a compute unit in these terms (the line count
+// taken 3 % high for the spread between segments; halved when the lines would
+// overflow the line table, whose fallback scans slices).  Ten Table-1 columns
+// (57 bytes a line, 8 million lines): 24 KiB 598 us a pass, 12, 20, 28 and 40 KiB
+// 703, 671, 824 and 650; thirteen decimal columns (170 bytes): 40 KiB 869,
+// 24 KiB 1304.  Without a measurement: 20 KiB.
+static int pick_text_seg(double ell, int p) {
+  int best = 5 * UNIT;
+  if (!(ell > 0.0)) return best;
   double best_score = -1.0;
-  for (int seg = 16 << 10; seg <= SEG_MAX; seg += 4096) {
+  for (int seg = SEG_MIN; seg <= SEG_MAX; seg += UNIT) {
     const double lines = seg / ell;
     const double rounds = std::ceil(lines * 1.03 / kThreads);
-    const double score = lines / (rounds * kThreads) * seg / (seg + 4915.0) * (lines * 1.03 <= MAXLS ? 1.0 : 0.5);
+    const int lds = text_lds(seg, pick_maxls(ell, seg)) + kThreads * row_words(p) * 8 + 1280;
+    const int wgs = std::min(4, (160 << 10) / lds);
+    const double score = wgs * lines / ((1.2 + rounds) * (1.0 + 0.18 * (wgs - 1))) * (lines * 1.03 <= MAXLS ? 1.0 : 0.5);
     if (score > best_score) {
       best_score = score;
       best = seg;
@@ -1092,7 +1240,7 @@ static int pick_text_seg(double ell) {
 
 static int text_launch(stats_ctx* h, const char* dbuf, int64_t nbytes, int64_t nend, int64_t base_off) {
   const int p = h->p;
-  const int seg = pick_text_seg(h->text_ell);
+  const int seg = pick_text_seg(h->text_ell, p);
   const int64_t nblocks = (nend + seg - 1) / seg;
   if (nblocks == 0) return STATS_OK;
   const int64_t W = rec_words(p);
@@ -1108,6 +1256,7 @@ static int text_launch(stats_ctx* h, const char* dbuf, int64_t nbytes, int64_t n
   a.p = p;
   a.base_off = base_off;
   a.seg = seg;
+  a.maxls = pick_maxls(h->text_ell, seg);
   a.status = h->status_dev;
   uint32_t intmask = 0;
   for (int c = 0; c < p; ++c)
@@ -1252,20 +1401,22 @@ extern "C" int stats_text_to_binary(stats_ctx* h, const char* buf, int64_t nbyte
   } else if (mem_kind != STATS_MEM_DEVICE) {
     return fail(STATS_E_ARG, "unknown mem_kind");
   }
-  const int64_t nseg_max = (nbytes + SEG - 1) / SEG;
-  // scratch: per-segment counts / first rows (nseg + 1), the last line end,
-  // and a status word of its own (the handle's statistics are not touched)
-  const size_t cnt_bytes = (size_t)(nseg_max + 1) * 8;
+  // scratch: line counts, then first rows, of the groups of units, first rows of
+  // the units in them, the last line end, and a status word of its own (the
+  // handle's statistics are not touched)
+  const int64_t ngroups_max = (nbytes + kGroup * UNIT - 1) / (kGroup * UNIT);
+  const size_t cnt_bytes = (size_t)ngroups_max * (8 + 4 * kGroup);
   const size_t need = (cnt_bytes + 255) / 256 * 256 + 256;
   int rc = ensure_dev(h, &h->conv_dev, &h->conv_cap, need);
   if (rc) return rc;
   int64_t* counts = (int64_t*)h->conv_dev;
+  int32_t* first = (int32_t*)(counts + ngroups_max);
   char* tailp = (char*)h->conv_dev + (cnt_bytes + 255) / 256 * 256;
   int64_t* nend_dev = (int64_t*)tailp;
   DevStatus* cst = (DevStatus*)(tailp + 64);
-  static const DevStatus init = {0u, 0u, ~0ull};
-  e = hipMemcpyAsync(cst, &init, sizeof init, hipMemcpyHostToDevice, h->stream);
-  if (e != hipSuccess) return hip_fail(h, e, "clearing the conversion status");
+  rc = ensure_pin(h, &h->pin_out, &h->pin_out_cap, 64);
+  if (rc) return rc;
+  int64_t* pin = (int64_t*)h->pin_out;  // number of lines, then the status
   int64_t nend = nbytes;
   if (!is_last) {
     hipLaunchKernelGGL(k_last_newline, dim3(1), dim3(1024), 0, h->stream, dbuf, nbytes, nend_dev);
@@ -1274,18 +1425,17 @@ extern "C" int stats_text_to_binary(stats_ctx* h, const char* buf, int64_t nbyte
     if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
     if (e != hipSuccess) return hip_fail(h, e, "finding the last line end");
   }
-  const int64_t nseg = (nend + SEG - 1) / SEG;
-  if (nseg == 0) return STATS_OK;
-  hipLaunchKernelGGL(k_seg_lines, dim3((unsigned)nseg), dim3(kThreads), 0, h->stream, dbuf, nend, counts);
+  if (nend == 0) return STATS_OK;
+  const int64_t ngroups = (nend + kGroup * UNIT - 1) / (kGroup * UNIT);
+  hipLaunchKernelGGL(k_unit_lines, dim3((unsigned)ngroups), dim3(64 * kGroup), 0, h->stream, dbuf, nend, counts, first);
   e = hipGetLastError();
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, h->stream, counts, nseg);
+    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, h->stream, counts, ngroups, pin, cst);
     e = hipGetLastError();
   }
-  int64_t total = 0;
-  if (e == hipSuccess) e = hipMemcpyAsync(&total, counts + nseg, 8, hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "counting lines");
+  const int64_t total = pin[0];
   if (total > max_rows)
     return fail(STATS_E_ARG, "the chunk holds " + std::to_string(total) + " lines, the output " +
                                  std::to_string(max_rows) + " rows");
@@ -1297,9 +1447,14 @@ extern "C" int stats_text_to_binary(stats_ctx* h, const char* buf, int64_t nbyte
   a.t.p = p;
   a.t.base_off = h->text_offset;
   a.t.status = cst;
+  const double ell = total > 0 ? (double)nend / (double)total : 0.0;
+  a.t.seg = pick_text_seg(ell, p);
+  a.t.maxls = pick_maxls(ell, a.t.seg);
+  const int64_t nseg = (nend + a.t.seg - 1) / a.t.seg;
   for (int c = 0; c < p; ++c)
     if (h->intf[c]) a.t.intmask |= 1u << c;
-  a.seg_base = counts;
+  a.group_base = counts;
+  a.first = first;
   for (int c = 0; c < p; ++c) {
     const stats_column& col = h->cols[c];
     a.out[c] = (char*)out_planes[col.plane] + col.byte_offset;
@@ -1314,10 +1469,11 @@ extern "C" int stats_text_to_binary(stats_ctx* h, const char* buf, int64_t nbyte
 #undef ST_CASE
   }
   e = hipGetLastError();
-  DevStatus st{};
-  if (e == hipSuccess) e = hipMemcpyAsync(&st, cst, sizeof st, hipMemcpyDeviceToHost, h->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(pin + 1, cst, sizeof(DevStatus), hipMemcpyDeviceToHost, h->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(h->stream);
   if (e != hipSuccess) return hip_fail(h, e, "text conversion");
+  DevStatus st;
+  memcpy(&st, pin + 1, sizeof st);
   h->text_offset += nend;
   if (st.bits & ST_PARSE)
     return fail(STATS_E_PARSE, "malformed or out-of-range field in the line starting at byte offset " +
