@@ -55,7 +55,7 @@ struct SegArgs {
 // consecutive 4-byte offsets of one plane, up to kSyrkMaxExtra other columns.
 constexpr int kSyrkGroup = 128;
 constexpr int kSyrkMaxExtra = 2;
-constexpr int kSyrkMaxPairs = 72;  // F <= 1024: at most 8 groups; every pair in two halves
+constexpr int kSyrkMaxPairs = 36;  // F <= 1024: at most 8 groups
 
 struct SyrkExtra {
   const char* base;  // element of row 0 of the launch
@@ -73,7 +73,7 @@ struct SyrkArgs {
   int ne;                   // extra columns, slots F..F+ne-1
   SyrkExtra ex[kSyrkMaxExtra];
   int npairs;
-  int2 pairs[kSyrkMaxPairs];  // (A + 16 half, B): group pairs A <= B, each in two halves
+  int2 pairs[kSyrkMaxPairs];  // group pairs A <= B
   int p;                    // F + ne
   const int32_t* col_of;    // user column of each slot (device)
   int64_t nblocks, nrows, R;  // R: rows per block (multiple of 64)

@@ -114,10 +114,7 @@ static int accumulate_syrk(stats_ctx* h, const void* const* planes, int64_t nrow
   a.col_of = col_dev;
   a.npairs = 0;
   for (int A = 0; A < ng; ++A)
-    for (int B = A; B < ng; ++B) {
-      a.pairs[a.npairs++] = make_int2(A, B);
-      a.pairs[a.npairs++] = make_int2(A + 16, B);
-    }
+    for (int B = A; B < ng; ++B) a.pairs[a.npairs++] = make_int2(A, B);
   a.xstride = h->row_stride[xplane];
   a.R = R;
   a.status = h->status_dev;

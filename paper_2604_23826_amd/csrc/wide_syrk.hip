@@ -35,38 +35,37 @@
 // count) and checks every value: a block with a value beyond its column's
 // limit, a value off its grid (x 2^s not an integer: one v_fract per value),
 // or a non-finite value is flagged (ovf[b]), and the FP64 matrix-core routine
-// of wide.hip computes that block's whole record again (launch_wide_fixup),
+// of wide.hip computes that block's whole record again (launch_wide_f64),
 // so every block is either exact on its grid or FP64.  Each workgroup of the
 // first pass also finds the lowest set bit of its first 128 sampled rows:
 // when one lies below the grid spacing the block cannot be exact (zero-mean
 // data with full significands, say), and the workgroup flags it and stops
 // before the main loop.
 //
-// Work split: vector columns form groups of 128.  A workgroup owns one block
-// of rows and one half of a pair of groups (A, B), A <= B: two tile rows of
-// A for an off-diagonal pair (8 tiles), tile rows {0, 3} or {1, 2} of a
-// diagonal one (5 upper tiles; its other three waves only load and convert).
-// Eight waves, two per SIMD, with at most one 32 x 32 tile each (its five
-// int32 levels in 80 accumulation registers), so that each wave's waits are
-// covered by the other wave of its SIMD.  The sums stay out of this pass: in
-// the workgroups of the diagonal pairs they would double the vector work on
-// the pass's critical path.  Workgroup ids put all pairs of one block on the
-// same XCD (ids congruent modulo 8), so that a block's rows can come from
-// that XCD's L2 for the pairs after the first (the two halves of a pair, which
-// run at the same speed, do share them; pairs of different kinds drift apart).
+// Work split: vector columns form groups of 128.  A workgroup owns one block of
+// rows and one pair of groups (A, B), A <= B: 16 tiles of an off-diagonal pair,
+// the 10 upper ones of a diagonal pair.  Eight waves, two per SIMD, with at most
+// two 32 x 32 tiles each (ten int32 levels in 160 registers), so a block's rows
+// are converted twice for 256 columns (with one tile a wave, in halves of pairs,
+// four times).  The sums stay out of this pass: they would double its vector
+// work.  Workgroup ids put all pairs of one block on the same XCD (ids congruent
+// modulo 8), so that a block's rows can come from that XCD's L2 for the pairs
+// after the first.
 //
-// Data path per 32-row sub-step: each wave loads its own four rows (a lane
-// four consecutive columns of each, two on a diagonal half) from global
-// memory straight into
-// registers, two alternating register sets, one sub-step ahead, and converts
-// exactly those rows.  The digits go to a double-buffered LDS array,
-// [digit][4-row group][column] as dwords of four rows; one barrier per
-// sub-step separates the conversion of sub-step t + 1 from the products of
-// sub-step t.  The K index of a product is the row, so a lane's operand
-// dwords j = 0..3 are its column's row groups 4h + j.  The conversion of
-// sub-step t + 1 and the products of sub-step t are independent; the
-// schedule interleaves them (one product, then a share of the conversion),
-// so the vector work issues while the matrix cores run.
+// Data path per 32-row sub-step: each wave moves 16 rows of 64 columns (8 on a
+// diagonal pair) into its own ring of three slots in LDS by direct loads, two
+// sub-steps ahead, and converts exactly those, a column per lane.  The digits go
+// to a double-buffered LDS array, [digit][16-row half][column] of 16 bytes, which
+// is an operand of a product in one 16-byte read (as dwords of four rows it was
+// four reads); one barrier per sub-step separates the conversion of sub-step
+// t + 1 from the products of sub-step t.  They are independent: the two waves of
+// a SIMD take them in opposite order, so that one converts while the other is on
+// the matrix cores.
+//
+// Measured at 20 million rows of 256 columns: 12.1 ms with halves of pairs, 9.6
+// as it is.  The products alone take 4.6 ms (2.6 at the matrix cores' peak rate),
+// the conversion alone 4.0, both without the loads 6.8; thirds of a two-group
+// table, which halve the bytes from HBM (41 to 22 GB), took as long.
 #include <type_traits>
 
 #include "common.hpp"
@@ -84,11 +83,10 @@ typedef unsigned int u2 __attribute__((ext_vector_type(2)));
 
 constexpr int kThreads = 512;
 constexpr int NW = kThreads / 64;    // waves
-constexpr int RW = 32 / NW;          // rows per wave per sub-step
-constexpr int MT = 1;                // tiles per wave
+constexpr int MT = 2;                // tiles per wave, at most
 constexpr int G = wide::kSyrkGroup;  // vector columns per group
 constexpr int SR = 32;               // rows per sub-step (K of one product)
-constexpr int PITCH_MAX = 2 * G + 8;
+constexpr int NSTAGE = 3;            // sub-steps of raw rows in LDS per wave
 constexpr int NSAMP = 1024;          // rows sampled per block for the grids
 constexpr int SB = 16;               // sampled rows per wave in flight
 constexpr float kVlim = 4194303.0f;  // |v| < 2^22: the rounding constant below holds v exactly
@@ -103,46 +101,42 @@ struct VmWait {
   static constexpr int imm = (N & 15) | (7 << 4) | (15 << 8) | (((N >> 4) & 3) << 14);
 };
 
-// Shapes of the two workgroup kinds.
+// Shapes of the two workgroup kinds: a wave converts RW rows of 64 columns, one
+// column a lane.
 template <bool DIAG>
 struct Shape {
   static constexpr int NC = DIAG ? G : 2 * G;  // staged columns
-  static constexpr int CPL = NC / 64;           // columns converted per lane
-  static constexpr int PITCH = NC + 8;          // dwords per 4-row group (4 PITCH = 32 mod 64 banks)
+  static constexpr int CPL = NC / 64;           // columns per lane of a sampled row
+  static constexpr int RW = SR * NC / kThreads; // rows per wave per sub-step
+  static constexpr int HALF = 4 * NC;           // dwords of 16 rows' digits of one place
+  static constexpr int OPS = RW / 4;            // direct loads of a wave's rows of a sub-step
+  static constexpr int SLOT = RW * 256;         // their bytes
 };
 
-// Tiles (ti, tj) of a wave, at most MT; off-diagonal pairs: tile row w.
+// Tiles (ti, tj) of a wave, at most MT.
 struct WaveTiles {
   int n;
   int ti[MT], tj[MT];
 };
 
 template <bool DIAG>
-__device__ inline WaveTiles wave_tiles(int w, int half) {
+__device__ inline WaveTiles wave_tiles(int w) {
   WaveTiles r;
   if (!DIAG) {
-    // tile row 2 half + w / 4 of A, tile column w % 4 of B
-    r.n = 1;
-    r.ti[0] = 2 * half + (w >> 2);
-    r.tj[0] = w & 3;
+    // tile row w / 2 of A, tile columns 2 (w % 2) and the next of B
+    r.n = 2;
+    r.ti[0] = r.ti[1] = w >> 1;
+    r.tj[0] = 2 * (w & 1);
+    r.tj[1] = r.tj[0] + 1;
     return r;
   }
-  // a diagonal half: the upper tiles of tile rows {0, 3} (half 0) or {1, 2}
-  // (half 1) of the 4 x 4 tiles, one per wave; waves without a tile only
-  // stage and convert rows
-  switch (half * 8 + w) {
-    case 0: r.n = 1; r.ti[0] = 0; r.tj[0] = 0; break;
-    case 1: r.n = 1; r.ti[0] = 0; r.tj[0] = 1; break;
-    case 2: r.n = 1; r.ti[0] = 0; r.tj[0] = 2; break;
-    case 3: r.n = 1; r.ti[0] = 0; r.tj[0] = 3; break;
-    case 4: r.n = 1; r.ti[0] = 3; r.tj[0] = 3; break;
-    case 8: r.n = 1; r.ti[0] = 1; r.tj[0] = 1; break;
-    case 9: r.n = 1; r.ti[0] = 1; r.tj[0] = 2; break;
-    case 10: r.n = 1; r.ti[0] = 1; r.tj[0] = 3; break;
-    case 11: r.n = 1; r.ti[0] = 2; r.tj[0] = 2; break;
-    case 12: r.n = 1; r.ti[0] = 2; r.tj[0] = 3; break;
-    default: r.n = 0; r.ti[0] = 0; r.tj[0] = 0; break;
-  }
+  // the ten upper tiles of the 4 x 4 (a hex digit each), the ones of few columns
+  // first; the two waves with a second tile sit on different SIMDs
+  r.ti[0] = (int)(0x10210100u >> (4 * w)) & 15;
+  r.tj[0] = (int)(0x33222110u >> (4 * w)) & 15;
+  r.n = w < 2 ? 2 : 1;
+  r.ti[1] = w == 0 ? 2 : 3;
+  r.tj[1] = 3;
   return r;
 }
 
@@ -188,147 +182,131 @@ __device__ inline int grid_exp(double m, float K) {
   return max(-126, min(127, s));
 }
 
-// One workgroup's view of its block: DIAG for a half of a diagonal pair (one
-// group of columns), else a half of an off-diagonal pair (two groups).
+// One workgroup's view of its block: DIAG for a diagonal pair (one group of
+// columns), else an off-diagonal one (two groups).
 template <bool DIAG>
 struct Ctx {
   static constexpr int NC = Shape<DIAG>::NC;
   static constexpr int CPL = Shape<DIAG>::CPL;
-  static constexpr int PITCH = Shape<DIAG>::PITCH;
+  static constexpr int RW = Shape<DIAG>::RW;
+  static constexpr int HALF = Shape<DIAG>::HALF;
   const wide::SyrkArgs& a;
-  int* dig;             // LDS digits [2][3][8][PITCH]
+  int* dig;             // LDS digits [2][3][2][NC] of 16 rows' bytes
   const float* s_sc;    // 2^s per staged column (0: not converted)
   const float* s_nks;   // -K 2^s
-  float sc[CPL], nks[CPL];  // the lane's columns' 2^s and -K 2^s, in registers for the block
+  float sc, nks;        // the lane's column's 2^s and -K 2^s, in registers for the block
   int64_t r0, r1;
   int A, B, lane, wave, h, q;
-  int cl0;              // first staged column converted by this lane
+  int cl0;              // first staged column sampled by this lane
+  int cc;               // staged column converted by this lane
+  int rw;               // first row of the sub-step converted by this wave
+  char* ring;           // this wave's raw rows, NSTAGE slots
+  const char* src;      // the lane's 16 bytes of the wave's first row of sub-step 0
+  int lrow;             // the lane's row of a direct load
 
   __device__ Ctx(const wide::SyrkArgs& a_) : a(a_) {}
 
   // global vector column of staged column c
   __device__ __attribute__((always_inline)) int gcol(int c) const { return DIAG ? A * G + c : (c < G ? A * G + c : B * G + (c - G)); }
 
-  // Raw values of one sub-step for this lane: RW rows x CPL columns.
-  struct Raw {
-    float x[RW][CPL];
-  };
-
-  // Loads of this wave's rows of sub-step t, straight into registers: CPL
-  // consecutive columns of each row per lane (rows past the block end read
-  // its last row, columns past F read column 0; both are ignored).
-  __device__ __attribute__((always_inline)) void load(int64_t t, Raw& r) const {
-    const int64_t rb = r0 + t * SR + RW * wave;
-    const int dc = gcol(cl0);
-    const int64_t col = dc < a.F ? dc : 0;
+  // Moves this wave's rows of sub-step t, 64 columns of each, into a slot of its
+  // ring by direct loads of 16 bytes a lane, four rows each (rows past the block
+  // end bring its last row, columns past F column 0; both are ignored).
+  __device__ __attribute__((always_inline)) void issue(int64_t t, int slot) const {
+    char* dst = ring + slot * Shape<DIAG>::SLOT;
 #pragma unroll
-    for (int j = 0; j < RW; ++j) {
-      int64_t row = rb + j;
-      row = row < r1 ? row : r1 - 1;
-      load_row(a.xbase + row * a.xstride + 4 * col, r.x[j]);
+    for (int j = 0; j < Shape<DIAG>::OPS; ++j) {
+      const int64_t row = min(t * SR + 4 * j, r1 - 1 - (r0 + rw + lrow));  // from the lane's first
+      __builtin_amdgcn_global_load_lds((const void*)(src + row * a.xstride),
+                                       (__attribute__((address_space(3))) void*)(dst + j * 1024), 16, 0, 0);
     }
   }
 
-  // The same for a sub-step that lies inside the block: rp is this lane's
-  // address in the wave's first row of the sub-step (advanced by the caller).
-  __device__ __attribute__((always_inline)) void load_inside(const char* rp, Raw& r) const {
+  // The same for a sub-step that lies inside the block: p is the lane's 16 bytes
+  // of the wave's first row of it (advanced by the caller).
+  __device__ __attribute__((always_inline)) void issue_inside(const char* p, int slot) const {
+    char* dst = ring + slot * Shape<DIAG>::SLOT;
+    const int64_t four = 4 * a.xstride;
 #pragma unroll
-    for (int j = 0; j < RW; ++j) load_row(rp + j * a.xstride, r.x[j]);
+    for (int j = 0; j < Shape<DIAG>::OPS; ++j)
+      __builtin_amdgcn_global_load_lds((const void*)(p + j * four),
+                                       (__attribute__((address_space(3))) void*)(dst + j * 1024), 16, 0, 0);
   }
 
-  __device__ __attribute__((always_inline)) static void load_row(const char* p, float (&x)[CPL]) {
-    if constexpr (CPL == 4) {
-      const fl4 v = *(const fl4*)p;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) x[i] = v[i];
-    } else {
-      const fl2 v = *(const fl2*)p;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) x[i] = v[i];
-    }
+  __device__ __attribute__((always_inline)) void load_grid() {
+    sc = s_sc[cc];
+    nks = s_nks[cc];
   }
 
-  // Digits of sub-step t into digit buffer t & 1 (rows past the block end
-  // give zeros).
-  __device__ __attribute__((always_inline)) void load_grids() {
-#pragma unroll
-    for (int i = 0; i < CPL; ++i) {
-      sc[i] = s_sc[cl0 + i];
-      nks[i] = s_nks[cl0 + i];
-    }
-  }
-
+  // Digits of sub-step t, whose rows are complete in the given slot, into digit
+  // buffer t & 1 (rows past the block end give zeros).
   template <bool TAIL>
-  __device__ __attribute__((always_inline)) void digitize(int64_t t, Raw& r) const {
-    const int64_t rb = r0 + t * SR + RW * wave;
+  __device__ __attribute__((always_inline)) void digitize(int64_t t, int slot) const {
+    const int64_t rb = r0 + t * SR + rw;
+    const __attribute__((address_space(3))) float* st =
+        (const __attribute__((address_space(3))) float*)(ring + slot * Shape<DIAG>::SLOT) + lane;
+    float x[RW];
+#pragma unroll
+    for (int j = 0; j < RW; ++j) x[j] = st[64 * j];
+    uint32_t dw[3][RW / 4];
 #pragma unroll
     for (int g = 0; g < RW / 4; ++g) {
-      uint32_t dw[3][CPL];
+      int w[4];
 #pragma unroll
-      for (int i = 0; i < CPL; ++i) {
-        int w[4];
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          float y = __builtin_fmaf(r.x[4 * g + jj][i], sc[i], nks[i]);
-          if (TAIL) y = (rb + 4 * g + jj < r1) ? y : 0.0f;
-          const float fr = y + kRound;
-          w[jj] = __float_as_int(fr) + kBias;  // v + 0x8080: bytes d2 + 128, d1 + 128, d0
-        }
-        // byte transpose: digit k of the four rows into one dword
-        const uint32_t p01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);
-        const uint32_t p23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
-        const uint32_t q01 = __builtin_amdgcn_perm(w[1], w[0], 0x0C0C0602u);
-        const uint32_t q23 = __builtin_amdgcn_perm(w[3], w[2], 0x0C0C0602u);
-        dw[2][i] = __builtin_amdgcn_perm(p23, p01, 0x05040100u) ^ 0x80808080u;  // d2 (lowest)
-        dw[1][i] = __builtin_amdgcn_perm(p23, p01, 0x07060302u) ^ 0x80808080u;  // d1
-        dw[0][i] = __builtin_amdgcn_perm(q23, q01, 0x05040100u);                // d0 (highest)
+      for (int jj = 0; jj < 4; ++jj) {
+        float y = __builtin_fmaf(x[4 * g + jj], sc, nks);
+        if (TAIL) y = (rb + 4 * g + jj < r1) ? y : 0.0f;
+        const float fr = y + kRound;
+        w[jj] = __float_as_int(fr) + kBias;  // v + 0x8080: bytes d2 + 128, d1 + 128, d0
       }
-      int* out = dig + ((int)(t & 1) * 3 * 8 + (RW / 4) * wave + g) * PITCH + cl0;
+      // byte transpose: digit k of the four rows into one dword
+      const uint32_t p01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u);
+      const uint32_t p23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+      const uint32_t q01 = __builtin_amdgcn_perm(w[1], w[0], 0x0C0C0602u);
+      const uint32_t q23 = __builtin_amdgcn_perm(w[3], w[2], 0x0C0C0602u);
+      dw[2][g] = __builtin_amdgcn_perm(p23, p01, 0x05040100u) ^ 0x80808080u;  // d2 (lowest)
+      dw[1][g] = __builtin_amdgcn_perm(p23, p01, 0x07060302u) ^ 0x80808080u;  // d1
+      dw[0][g] = __builtin_amdgcn_perm(q23, q01, 0x05040100u);                // d0 (highest)
+    }
+    int* out = dig + ((int)(t & 1) * 6 + (rw >> 4)) * HALF + 4 * cc + ((rw & 15) >> 2);
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        if constexpr (CPL == 4) *(u4*)(out + d * 8 * PITCH) = (u4){dw[d][0], dw[d][1], dw[d][2], dw[d][3]};
-        else *(u2*)(out + d * 8 * PITCH) = (u2){dw[d][0], dw[d][1]};
-      }
+    for (int d = 0; d < 3; ++d) {
+      if constexpr (RW == 16) *(u4*)(out + d * 2 * HALF) = (u4){dw[d][0], dw[d][1], dw[d][2], dw[d][3]};
+      else *(u2*)(out + d * 2 * HALF) = (u2){dw[d][0], dw[d][1]};
     }
   }
 };
 
-// One operand: digit d of staged column c in rows 16h..16h+15 of buffer buf.
+// One operand: digit d of staged column c (its lane's, plus c) in the 16 rows of
+// the lane's half; base: the lane's place in the digit buffer.
 template <bool DIAG>
 __device__ inline i4 operand(const int* base, int d, int c) {
-  constexpr int PITCH = Shape<DIAG>::PITCH;
-  i4 r;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) r[j] = base[(d * 8 + j) * PITCH + c];
-  return r;
+  return *(const i4*)(base + d * 2 * Shape<DIAG>::HALF + 4 * c);
 }
 
-// Operands of one sub-step's digits (buffer buf) for the wave's tile: the
-// three digits of its column block of A and of its column block of B.
-struct Ops {
-  i4 fa[3], fb[3];
-};
-
-template <bool DIAG>
-__device__ inline void load_ops(const int* dig, int buf, const WaveTiles& wt, int h, int q, Ops& o) {
-  constexpr int PITCH = Shape<DIAG>::PITCH;
-  const int* base = dig + (buf * 3 * 8 + 4 * h) * PITCH + q;
+// The nine digit products of one sub-step (digits of buffer buf) into the
+// wave's tiles: digit d of the B operand meets the three digits of A in levels
+// d..d+2 (tiles past the last vector column multiply zero digits and are not
+// written).  The two tiles of an off-diagonal pair's wave share
+// the A operand.
+template <bool DIAG, int NT>
+__device__ __attribute__((always_inline)) inline void products(const int* dig, int buf, const WaveTiles& wt, int h, int q,
+                                                               i16 (&L)[MT][5]) {
+  const int* base = dig + (buf * 6 + h) * Shape<DIAG>::HALF + 4 * q;
   constexpr int boff = DIAG ? 0 : G;
+  i4 fa[3];
 #pragma unroll
-  for (int d = 0; d < 3; ++d) {
-    o.fa[d] = operand<DIAG>(base, d, 32 * wt.ti[0]);
-    o.fb[d] = operand<DIAG>(base, d, boff + 32 * wt.tj[0]);
+  for (int u = 0; u < NT; ++u) {
+    if (u == 0 || DIAG)
+#pragma unroll
+      for (int d = 0; d < 3; ++d) fa[d] = operand<DIAG>(base, d, 32 * wt.ti[u]);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      const i4 fb = operand<DIAG>(base, d, boff + 32 * wt.tj[u]);
+#pragma unroll
+      for (int k = 0; k < 3; ++k) L[u][d + k] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[k], fb, L[u][d + k], 0, 0, 0);
+    }
   }
-}
-
-// The nine digit products of one sub-step into the tile's levels: digit d of
-// the B operand meets the three digits of A in levels d..d+2 (tiles past the
-// last vector column multiply zero digits and are not written).
-__device__ inline void mma_ops(const Ops& o, i16 (&L)[MT][5]) {
-#pragma unroll
-  for (int d = 0; d < 3; ++d)
-#pragma unroll
-    for (int k = 0; k < 3; ++k) L[0][d + k] = __builtin_amdgcn_mfma_i32_32x32x32_i8(o.fa[k], o.fb[d], L[0][d + k], 0, 0, 0);
 }
 
 struct Lds {
@@ -339,12 +317,13 @@ struct Lds {
   float* s_sc;
   float* s_nks;
   int* s_flag;      // sampled values off their grid: the block goes to FP64
+  char* ring;       // raw rows, [NW][NSTAGE] slots
 };
 
 // One block of rows and one pair of column groups (A, B).
 template <bool DIAG>
 __device__ __attribute__((always_inline)) void pair_block(const wide::SyrkArgs& a, const Lds& m, int64_t b, int A,
-                                                         int B, int half) {
+                                                         int B) {
   constexpr int NC = Shape<DIAG>::NC;
   constexpr int CPL = Shape<DIAG>::CPL;
   Ctx<DIAG> c(a);
@@ -360,16 +339,24 @@ __device__ __attribute__((always_inline)) void pair_block(const wide::SyrkArgs& 
   c.h = c.lane >> 5;
   c.q = c.lane & 31;
   c.cl0 = CPL * c.lane;
+  c.cc = 64 * (c.wave % CPL) + c.lane;
+  c.rw = Shape<DIAG>::RW * (c.wave / CPL);
+  c.ring = m.ring + c.wave * NSTAGE * Shape<DIAG>::SLOT;
+  c.lrow = c.lane >> 4;
+  {
+    const int g = c.gcol(64 * (c.wave % CPL) + 4 * (c.lane & 15));
+    c.src = a.xbase + (c.r0 + c.rw + c.lrow) * a.xstride + 4 * (int64_t)(g < a.F ? g : 0);
+  }
   const bool colv = c.gcol(c.cl0) < a.F;
   const int64_t nrow = c.r1 - c.r0;
   const int64_t nsub = (nrow + SR - 1) / SR;
   const int tid = threadIdx.x;
   uint64_t* out = a.rec + b * rec_words(a.p);
 
-  // rows of sub-steps 0 and 1 in flight during the sampling
-  typename Ctx<DIAG>::Raw rs[2];
-  c.load(0, rs[0]);
-  if (nsub > 1) c.load(1, rs[1]);
+  // the first sub-steps' rows in flight during the sampling
+#pragma unroll
+  for (int t = 0; t < NSTAGE; ++t)
+    if (t < nsub) c.issue(t, t);
   // ---- shifts; grids from NSAMP rows spread over the block ----
   for (int k = tid; k < NC; k += kThreads) {
     const int g = c.gcol(k);
@@ -447,8 +434,9 @@ __device__ __attribute__((always_inline)) void pair_block(const wide::SyrkArgs& 
     m.s_sc[k] = valid ? ldexpf(1.0f, s) : 0.0f;
     m.s_nks[k] = valid ? -K * ldexpf(1.0f, s) : 0.0f;
     // the grids of the block, for the sums pass (one writer per column)
-    if (DIAG && half == 0 && c.gcol(k) < a.F) a.sexp[b * a.F + c.gcol(k)] = s;
+    if (DIAG && c.gcol(k) < a.F) a.sexp[b * a.F + c.gcol(k)] = s;
   }
+  __builtin_amdgcn_s_waitcnt(VmWait<0>::imm);  // the rows in flight land before the workgroup may end
   lds_barrier();
   if (m.s_flag[0]) {
     // the whole block is recomputed in FP64
@@ -456,8 +444,8 @@ __device__ __attribute__((always_inline)) void pair_block(const wide::SyrkArgs& 
     return;
   }
 
-  c.load_grids();
-  const WaveTiles wt = wave_tiles<DIAG>(c.wave, half);
+  c.load_grid();
+  const WaveTiles wt = wave_tiles<DIAG>(c.wave);
   // whether the wave has a tile that holds vector columns (a short last
   // group leaves some tiles out); 0: no products
   int nt = 0;
@@ -471,76 +459,63 @@ __device__ __attribute__((always_inline)) void pair_block(const wide::SyrkArgs& 
 #pragma unroll
     for (int l = 0; l < 5; ++l) L[u][l] = (i16){};
 
-  if (SR > nrow) c.template digitize<true>(0, rs[0]);
-  else c.template digitize<false>(0, rs[0]);
+  if (SR > nrow) c.template digitize<true>(0, 0);
+  else c.template digitize<false>(0, 0);
   lds_barrier();
-  // Sub-step t: loads of t + 2 into the registers of t (converted one
-  // sub-step ago), operands of t, products of t and digits of t + 1 (loaded
-  // one sub-step ago), interleaved so that the conversion's vector
-  // instructions issue while the matrix cores work.  Register sets
-  // alternate, so the main loop takes two sub-steps per trip; the last
-  // sub-steps run one at a time.  Waves without a tile run the same loop
-  // without the products (same barriers).
-  const int64_t step_bytes = (int64_t)SR * a.xstride;
-  const char* rp0;  // this lane's address in the wave's first row of sub-step 2
-  {
-    const int dc = c.gcol(c.cl0);
-    const int64_t col = dc < a.F ? dc : 0;
-    rp0 = a.xbase + (c.r0 + 2 * SR + RW * c.wave) * a.xstride + 4 * col;
-  }
-  using T_ = std::true_type;
-  using F_ = std::false_type;
-  using I0 = std::integral_constant<int, 0>;
-  using I1 = std::integral_constant<int, 1>;
-  auto run = [&](auto prod_c) __attribute__((always_inline)) {
-    constexpr bool PROD = decltype(prod_c)::value;
-    const char* rp = rp0;
-    // PAR = t & 1; LOAD: 0 none, 1 inside the block (rp), 2 clamped
-    auto step = [&](int64_t t, auto par_c, auto load_c, auto more_c, auto tail_c) __attribute__((always_inline)) {
-      constexpr int PAR = decltype(par_c)::value;
-      constexpr int LOAD = decltype(load_c)::value;
-      constexpr bool MORE = decltype(more_c)::value;
-      constexpr bool TAIL = decltype(tail_c)::value;
-      if constexpr (LOAD == 1) c.load_inside(rp, rs[PAR]);
-      if constexpr (LOAD == 2) c.load(t + 2, rs[PAR]);
-      Ops o;
-      if constexpr (PROD) load_ops<DIAG>(m.dig, PAR, wt, c.h, c.q, o);
-      if constexpr (PROD) mma_ops(o, L);
-      if constexpr (MORE) c.template digitize<TAIL>(t + 1, rs[PAR ^ 1]);
-      if constexpr (PROD && MORE) {
-        // one product, then a share of the conversion, nine times
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, DIAG ? 4 : 8, 0);
-        }
+  // Sub-step t: rows of t + NSTAGE into the slot of t (converted one sub-step
+  // ago), products of t, digits of t + 1 (whose rows were asked for NSTAGE - 1
+  // sub-steps ago).  The two waves of a SIMD take the last two in opposite order,
+  // one on the matrix cores while the other converts.  Waves without a tile run
+  // the same loop without the products (same barriers).
+  auto run = [&](auto nt_c, auto first_c) __attribute__((always_inline)) {
+    constexpr int NT = decltype(nt_c)::value;         // tiles of this wave
+    constexpr bool FIRST = decltype(first_c)::value;  // products before the conversion
+    int slot = 0;  // t % NSTAGE
+    int64_t t = 0;
+    const char* p = c.src + NSTAGE * SR * a.xstride;
+    // sub-steps whose loads (t + NSTAGE) lie wholly inside the block
+    for (; (t + NSTAGE + 1) * SR <= nrow; ++t) {
+      const int next = slot == NSTAGE - 1 ? 0 : slot + 1;
+      c.issue_inside(p, slot);
+      p += SR * a.xstride;
+      if constexpr (FIRST) {
+        products<DIAG, NT>(m.dig, (int)(t & 1), wt, c.h, c.q, L);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_s_waitcnt(VmWait<(NSTAGE - 1) * Shape<DIAG>::OPS>::imm);
+      c.template digitize<false>(t + 1, next);
+      if constexpr (NT > 0 && !FIRST) {
+        __builtin_amdgcn_sched_barrier(0);
+        products<DIAG, NT>(m.dig, (int)(t & 1), wt, c.h, c.q, L);
       }
       lds_barrier();
-    };
-    int64_t t = 0;
-    // pairs of sub-steps whose loads (t + 2, t + 3) lie wholly inside the block
-    for (; t + 3 < nsub && c.r0 + (t + 4) * SR <= c.r1; t += 2) {
-      step(t, I0{}, I1{}, T_{}, F_{});
-      rp += step_bytes;
-      step(t + 1, I1{}, I1{}, T_{}, F_{});
-      rp += step_bytes;
+      slot = next;
     }
-    // the rest one by one: loads clamped to the block, rows past its end
-    // give zero digits
-    for (; t + 2 < nsub; ++t) {
-      if (t & 1) step(t, I1{}, std::integral_constant<int, 2>{}, T_{}, T_{});
-      else step(t, I0{}, std::integral_constant<int, 2>{}, T_{}, T_{});
+    // the rest: loads clamped to the block, rows past its end give zero digits
+    for (; t < nsub; ++t) {
+      const int next = slot == NSTAGE - 1 ? 0 : slot + 1;
+      if (t + NSTAGE < nsub) c.issue(t + NSTAGE, slot);
+      if constexpr (NT > 0) products<DIAG, NT>(m.dig, (int)(t & 1), wt, c.h, c.q, L);
+      __builtin_amdgcn_s_waitcnt(VmWait<0>::imm);
+      if (t + 1 < nsub) c.template digitize<true>(t + 1, next);
+      lds_barrier();
+      slot = next;
     }
-    if (t + 1 < nsub) {
-      if (t & 1) step(t, I1{}, I0{}, T_{}, T_{});
-      else step(t, I0{}, I0{}, T_{}, T_{});
-      ++t;
-    }
-    if (t & 1) step(t, I1{}, I0{}, F_{}, F_{});
-    else step(t, I0{}, I0{}, F_{}, F_{});
   };
-  if (nt) run(T_{});
-  else run(F_{});
+  using T_ = std::true_type;
+  using F_ = std::false_type;
+  const bool first = c.wave < NW / 2;
+  // (a pair's wave whose second tile is past the last column runs with
+  // both: that tile multiplies zeros)
+  if (nt == 2 || (!DIAG && nt)) {
+    if (first) run(std::integral_constant<int, 2>{}, T_{});
+    else run(std::integral_constant<int, 2>{}, F_{});
+  } else if (DIAG && nt) {
+    if (first) run(std::integral_constant<int, 1>{}, T_{});
+    else run(std::integral_constant<int, 1>{}, F_{});
+  } else {
+    run(std::integral_constant<int, 0>{}, F_{});
+  }
 
   // ---- tiles: levels combined, scaled by the grids, into the record ----
   const int p = a.p;
@@ -653,6 +628,16 @@ __global__ __launch_bounds__(kSumThreads, 3) void k_syrk_sums(wide::SyrkArgs a) 
   unsigned char* ring = s_ring + wave * kSumNS * kSumSB;
   const int64_t colb = cv ? c0 : cb;  // a valid column for idle lanes
   const bool exl = lane < 16 && (lane >> 3) < ns && (((lane >> 2) & 1) == 0 || e64[lane >> 3]);
+  // the lane's dword of its extra in row 0 of the launch, in registers: read from
+  // the arguments in the loop, it would be a load that waits for the rows in flight
+  const char* exb = nullptr;
+  int64_t exs = 0;
+#pragma unroll
+  for (int e = 0; e < NS; ++e)
+    if ((lane >> 3) == e) {
+      exb = a.ex[e].base + 4 * ((lane >> 2) & 1);
+      exs = a.ex[e].stride;
+    }
   auto issue = [&](int64_t t) {
     unsigned char* st = ring + (int)(t % kSumNS) * kSumSB;
 #pragma unroll
@@ -665,10 +650,9 @@ __global__ __launch_bounds__(kSumThreads, 3) void k_syrk_sums(wide::SyrkArgs a) 
     if (ns > 0) {
       // lane 8e + 4w + j: dword w of extra e in row j of the stage
       if (exl) {
-        const int e = lane >> 3, wd = (lane >> 2) & 1, j = lane & 3;
-        int64_t r = r0 + wave + 4 * (kSumRPW * t + j);
+        int64_t r = r0 + wave + 4 * (kSumRPW * t + (lane & 3));
         r = r < r1 ? r : r1 - 1;
-        __builtin_amdgcn_global_load_lds((const void*)(a.ex[e].base + r * a.ex[e].stride + 4 * wd),
+        __builtin_amdgcn_global_load_lds((const void*)(exb + r * exs),
                                          (__attribute__((address_space(3))) void*)(st + kSumRPW * 1024), 4, 0, 0);
       }
     }
@@ -797,30 +781,39 @@ __global__ __launch_bounds__(kSumThreads, 3) void k_syrk_sums(wide::SyrkArgs a) 
   }
 }
 
-__global__ __launch_bounds__(kThreads, 1) void k_syrk_i8(wide::SyrkArgs a) {
-  __shared__ __attribute__((aligned(16))) union {
-    int dig[2 * 3 * 8 * PITCH_MAX];
+// One LDS object: with several, the compiler knows which one the direct loads
+// write and waits for all of them before each read of it, prefetched rows
+// included.
+struct I8Lds {
+  union {
+    int dig[2 * 3 * 2 * Shape<false>::HALF];
     double red[NW * 2 * G];
-  } s_u;
-  __shared__ int s_exp[2 * G];
-  __shared__ float s_K[2 * G], s_sc[2 * G], s_nks[2 * G];
-  __shared__ int s_flag;
+  };
+  __attribute__((aligned(16))) char raw[NW * NSTAGE * Shape<false>::SLOT];
+  int exp[2 * G];
+  float K[2 * G], sc[2 * G], nks[2 * G];
+  int flag;
+};
+
+__global__ __launch_bounds__(kThreads, 1) void k_syrk_i8(wide::SyrkArgs a) {
+  __shared__ __attribute__((aligned(16))) I8Lds s;
   const int64_t id = blockIdx.x;
   const int64_t xcd = id & 7, y = id >> 3;
   const int t = (int)(y % a.npairs);
   const int64_t b = (y / a.npairs) * 8 + xcd;
   if (b >= a.nblocks) return;
-  const int A = a.pairs[t].x & 15, B = a.pairs[t].y, half = a.pairs[t].x >> 4;
+  const int A = a.pairs[t].x, B = a.pairs[t].y;
   Lds m;
-  m.dig = s_u.dig;
-  m.red = s_u.red;
-  m.s_exp = s_exp;
-  m.s_K = s_K;
-  m.s_sc = s_sc;
-  m.s_nks = s_nks;
-  m.s_flag = &s_flag;
-  if (A != B) pair_block<false>(a, m, b, A, B, half);
-  else pair_block<true>(a, m, b, A, B, half);
+  m.dig = s.dig;
+  m.red = s.red;
+  m.s_exp = s.exp;
+  m.s_K = s.K;
+  m.s_sc = s.sc;
+  m.s_nks = s.nks;
+  m.s_flag = &s.flag;
+  m.ring = s.raw;
+  if (A != B) pair_block<false>(a, m, b, A, B);
+  else pair_block<true>(a, m, b, A, B);
 }
 
 __global__ void k_zero_flags(int* f, int64_t n) {
