@@ -8,7 +8,7 @@ Motivation", Table 1), 10 columns A..H, cotC, I stored as nine int32 planes
 and one FP64 plane (44 bytes per row, 88 GB), generated in HBM before timing.
 One step is the whole path: reset, accumulate the rows in 2^28-row chunks
 (fused shift + column sums + upper-triangle X^T X, in-block reduction, exact
-/ Chan merge), then finalize (mean, covariance, correlation, FP64 Jacobi PCA)
+/ Chan merge), then finalize (mean, covariance, correlation, FP64 PCA)
 and copy the results to the host.
 
 Prints one JSON line: rows/s, the dominant kernel's achieved bandwidth (or

@@ -293,7 +293,7 @@ int stats_raw(stats_ctx* h, int64_t* n, stats_i128* s_int, double* s_f64, stats_
  * Table 3).  cov = centred co-moment / (N - ddof), correctly
  * rounded for integer pairs; corr = cov_ij / sqrt(cov_ii cov_jj) with a unit
  * diagonal (NaN where a variance is zero); eigenpairs of corr (or cov) by
- * FP64 Jacobi on the GPU, eigenvalues descending, eigvec row k = component k
+ * FP64 eigensolver on the GPU, eigenvalues descending, eigvec row k = component k
  * with unit norm and its largest-magnitude entry positive (lowest index on
  * ties); var_pct = 100 lambda / sum(lambda); cum_pct its running sum.
  * Arrays: mean p', cov / corr / eigvec p' x p', eigval / var_pct / cum_pct p'.
