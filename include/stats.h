@@ -295,7 +295,8 @@ int stats_raw(stats_ctx* h, int64_t* n, stats_i128* s_int, double* s_f64, stats_
  * diagonal (NaN where a variance is zero); eigenpairs of corr (or cov) by
  * FP64 eigensolver on the GPU, eigenvalues descending, eigvec row k = component k
  * with unit norm and its largest-magnitude entry positive (lowest index on
- * ties); var_pct = 100 lambda / sum(lambda); cum_pct its running sum.
+ * ties; entries within 32 * 2^-52 of the largest are ties, and are returned
+ * equal in magnitude); var_pct = 100 lambda / sum(lambda); cum_pct its running sum.
  * Arrays: mean p', cov / corr / eigvec p' x p', eigval / var_pct / cum_pct p'.
  * Any output pointer may be NULL.  N <= ddof gives STATS_E_STATE. */
 int stats_finalize(stats_ctx* h, const stats_finalize_opts* opts, int32_t* p_out, double* mean,

@@ -12,6 +12,13 @@ constexpr int kNB = 4;     // 2 x 2 blocks per thread and batch
 constexpr int kNV = 4;     // V row pairs per thread and batch
 constexpr int kMaxSweeps = 60;
 
+// Entries of an eigenvector within kTie of its largest magnitude are ties: they
+// differ by the solver's rounding only (the all-equal vector of collinear columns,
+// say; up to 17 units of 2^-52 at 24 columns).  They are returned equal, and the
+// one of lowest index decides the vector's sign, which so does not hang on that
+// rounding.
+constexpr double kTie = 1.0 - 32 * 2.220446049250313e-16;
+
 // Round-robin schedule on m (even) players: player at position pos in round
 // r (0 <= pos < m, 0 <= r < m - 1).
 __device__ inline int rr_player(int pos, int r, int m) {

@@ -663,12 +663,8 @@ __global__ __launch_bounds__(kJThreads) void k_correct(const double* __restrict_
 // ---- outputs -----------------------------------------------------------------------
 
 // A wave per eigenpair k: its rank (descending, ties by index), sign (entry of
-// largest magnitude positive, lowest index on ties), eigenvalue and vector.
-// Entries within kTie of the largest differ from it by the solver's rounding
-// only (the all-equal vector of collinear columns, say): they are ties, and are
-// returned equal, so that the sign does not hang on that rounding.
+// largest magnitude positive, lowest index on ties, see kTie), eigenvalue and vector.
 // Eigenvalue j at lam + j ls, component j of vector k at V + j vj + k vk.
-constexpr double kTie = 1.0 - 8 * kEps;
 __global__ __launch_bounds__(kJThreads) void k_pairs(const double* __restrict__ lam, int ls,
                                                      const double* __restrict__ V, int64_t vj, int64_t vk, int q,
                                                      int want_vectors, double* out, const unsigned* jc) {

@@ -8,15 +8,15 @@
 // N C_ij - s_i s_j (256-bit) divided once with correct rounding, other pairs
 // the merged centred co-moment M2 / (N - ddof).
 // Section "Principal Component Analysis Results": eigenpairs of the (small,
-// dense) correlation or covariance matrix; here a cyclic Jacobi method in
-// FP64 with the round-robin (Brent-Luk) ordering, so that in every round
-// q/2 disjoint rotations are computed and applied in parallel.  Output as in
+// dense) correlation or covariance matrix in FP64.  Output as in
 // Table 3: eigenvalues descending, variance %, cumulative %, loadings (one
 // row per component).
 //
-// One workgroup does the whole job with the matrices in LDS up to kQlQ columns of
-// a correlation matrix (by Householder reduction and implicit QL, see below) and
-// up to kLdsQ columns of a covariance matrix (by Jacobi); eigen_wide.hip takes
+// One workgroup does the whole job with the matrices in LDS: a correlation matrix
+// of 3 to kQlQ columns by Householder reduction and implicit QL (see below), a
+// smaller one, or a covariance matrix of up to kLdsQ columns, by the cyclic Jacobi
+// method with the round-robin (Brent-Luk) ordering, in every round of which q/2
+// disjoint rotations are computed and applied in parallel.  eigen_wide.hip takes
 // the rest.
 #include "common.hpp"
 #include "eigen.hpp"
@@ -44,6 +44,10 @@ struct Args {
 // covariance matrix.  A template parameter, so that a launch fetches only the
 // code it runs.
 enum { kQl = 0, kLdsJacobi = 1 };
+// Correlation matrices of at most this many columns take Jacobi: their equal
+// diagonal makes its one rotation exact, so both entries of either vector are equal
+// at any correlation (QL, whose shift is rounded, left them 1e-8 apart at 1e-8).
+constexpr int kOneRotation = 2;
 
 // End of a sweep (after its last barrier): true when no pair would rotate,
 // i.e. the next sweep would change nothing, so stopping now gives the same
@@ -189,7 +193,7 @@ __device__ inline void finalize_body(const Args& f) {
   const int64_t n = (int64_t)st[0];
   const int q = f.q;
   const int tid = threadIdx.x;
-  const int nth = blockDim.x;  // 64 .. kThreads, chosen by the launcher from q
+  const int nth = blockDim.x;  // 64 or kQlThreads, chosen by the launcher from q
   double* mean = f.out;
   double* cov = mean + q;
   double* corr = cov + (int64_t)q * q;
@@ -403,37 +407,40 @@ __device__ inline void finalize_body(const Args& f) {
   }
 
   // ---- sort descending (ties: lower index first), sign rule, percentages ----
-  // component j of eigenvector k at V + j vj + k vk; sorted eigenvalues and their
-  // sources (complemented where the vector changes sign) in LDS that is free now
+  // component j of eigenvector k at V + j vj + k vk; sorted eigenvalues, the largest
+  // magnitude of their vectors and their sources (complemented where the vector
+  // changes sign) in LDS that is free now
   const int vj = METHOD == kQl ? 1 : q, vk = METHOD == kQl ? ld : 1;
   double* lam = METHOD == kQl ? s_dyn + q : s_dyn;
   double* var = METHOD == kQl ? s_dyn + 2 * q : s_dyn + q;
   int* src = (int*)(s_dyn + (METHOD == kQl ? 3 : 2) * q);
+  double* top = METHOD == kQl ? s_dyn + 4 * q : V + qq;
   for (int k = tid; k < q; k += nth) {
     const double lk = METHOD == kQl ? s_dyn[k] : A[(int64_t)k * q + k];
     int rank = 0;
+    double best = 0.0;
     for (int j = 0; j < q; ++j) {
       const double lj = METHOD == kQl ? s_dyn[j] : A[(int64_t)j * q + j];
       rank += (lj > lk) || (lj == lk && j < k);
+      best = fmax(best, fabs(V[(int64_t)j * vj + (int64_t)k * vk]));
     }
     // eigenvector k's sign: largest |entry| positive (lowest index on ties)
-    double best = -1.0, top = 0.0;
-    for (int j = 0; j < q; ++j) {
+    double lead = 0.0;
+    for (int j = q - 1; j >= 0; --j) {
       const double x = V[(int64_t)j * vj + (int64_t)k * vk];
-      if (fabs(x) > best) {
-        best = fabs(x);
-        top = x;
-      }
+      if (fabs(x) >= kTie * best) lead = x;
     }
     lam[rank] = lk;
-    src[rank] = top < 0.0 ? ~k : k;
+    top[rank] = best;
+    src[rank] = lead < 0.0 ? ~k : k;
   }
   __syncthreads();
   if (f.want_vectors) {
-    for (int idx = tid; idx < q * q; idx += nth) {
+    for (int idx = tid; idx < qq; idx += nth) {
       const int r = idx / q, j = idx % q;
       const int k = src[r] < 0 ? ~src[r] : src[r];
-      const double x = V[(int64_t)j * vj + (int64_t)k * vk];
+      double x = V[(int64_t)j * vj + (int64_t)k * vk];
+      if (fabs(x) >= kTie * top[r]) x = copysign(top[r], x);
       evec[idx] = src[r] < 0 ? -x : x;
     }
   }
@@ -520,12 +527,12 @@ hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
   a.status = F.status;
   a.host = F.host;
   const size_t q = (size_t)F.q;
-  if (!F.pca_on) {
+  if (!F.pca_on && F.q > kOneRotation) {
     const size_t shm = (256 + (3 + 2 * ((q + 1) | 1)) * q) * sizeof(double);
     hipLaunchKernelGGL(k_finalize<kQl>, dim3(1), dim3(kQlThreads), shm, s, a);
   } else {
     // one wave for the small matrices (its barriers cost nothing)
-    const size_t shm = (5 * ((q + 1) / 2) + 2 * q * q) * sizeof(double);
+    const size_t shm = (5 * ((q + 1) / 2) + 2 * q * q + q) * sizeof(double);
     hipLaunchKernelGGL(k_finalize<kLdsJacobi>, dim3(1), dim3(F.q <= 16 ? 64 : kQlThreads), shm, s, a);
   }
   return hipGetLastError();
