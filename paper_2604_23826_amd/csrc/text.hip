@@ -47,7 +47,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int UNIT = 4096;         // segments are whole units; lines are counted per unit
 constexpr int SEG_MIN = 8 << 10, SEG_MAX = 40 << 10;  // bytes of line starts per workgroup (chosen per chunk)
 constexpr int MAXLINE = 4096;      // longest line accepted
-constexpr int MAXLS = 2048;        // line starts per workgroup kept in the table
+constexpr int MAXLS = 18 * kThreads;  // line starts in the table at a time, at most (8 KiB of two-byte lines)
 constexpr int kPast = 32;          // bytes past the text that read as 0xFF
 
 // LDS bytes of the text stage of a segment: up to 31 bytes in front (16 of the
@@ -71,7 +71,7 @@ struct Args {
   uint32_t intmask;
   int64_t base_off;  // offset of buf in the caller's stream (for messages)
   int seg;           // bytes of line starts per workgroup: a multiple of 4096, at most SEG_MAX
-  int maxls;         // line starts per workgroup kept in the table, at most MAXLS
+  int maxls;         // line starts in the table at a time, at most MAXLS
   acc::Args acc;
   DevStatus* status;
 };
@@ -717,13 +717,11 @@ __device__ inline int stage_text(const char* buf, int64_t w0r, int nr, __attribu
 // its slice (slice positions, a multiple of 16 up to SLICE_MAX) in one pass
 // of 16-byte LDS reads, keeping them as a bit
 // mask (a '\n' byte is a zero byte of v ^ 0x0a0a0a0a); a workgroup scan of the
-// counts places them in s_ls in stream order when they fit (<= maxls).
-// Returns their number; *c0, *c1 receive this thread's slice and *before the
-// number of line starts in earlier slices (the index of its first line).
+// counts places lines base .. base + maxls - 1 of them in s_ls in stream order.
+// Returns the number of all line starts.
 // Contains barriers: every thread of the workgroup calls it.
-__device__ inline int line_starts(lds_text s_buf, int64_t w0, int s0r, int s1r, int slice,
-                                  int maxls, unsigned short* s_ls, int* s_wsum, int* c0_out, int* c1_out,
-                                  int* before_out) {
+__device__ inline int line_starts(lds_text s_buf, int64_t w0, int s0r, int s1r, int slice, int base,
+                                  int maxls, unsigned short* s_ls, int* s_wsum) {
   constexpr int NV = SLICE_MAX / 16 + 1;     // 16-byte reads per slice (it may start mid-vector)
   constexpr int NM = (16 * NV + 31) / 32;    // 32-bit mask words
   const int c0 = s0r + (int)threadIdx.x * slice;
@@ -775,22 +773,23 @@ __device__ inline int line_starts(lds_text s_buf, int64_t w0, int s0r, int s1r, 
     if (k < wv) before += s_wsum[k];
     total += s_wsum[k];
   }
-  if (total <= maxls && c0 < c1) {
-    int at = before;
-    if (w0 + c0 == 0) s_ls[at++] = (unsigned short)c0;
+  int at = before - base;
+  if (c0 < c1 && at < maxls && at + mine > 0) {
+    auto place = [&](int pos) {
+      if ((unsigned)at < (unsigned)maxls) s_ls[at] = (unsigned short)pos;
+      ++at;
+    };
+    if (w0 + c0 == 0) place(c0);
 #pragma unroll
     for (int j = 0; j < NM; ++j) {
       uint32_t m = nl[j];
       while (m) {
-        s_ls[at++] = (unsigned short)(mb + 32 * j + __builtin_ctz(m) + 1);
+        place(mb + 32 * j + __builtin_ctz(m) + 1);
         m &= m - 1;
       }
     }
   }
   __syncthreads();
-  *c0_out = c0;
-  *c1_out = c1;
-  *before_out = before;
   return total;
 }
 
@@ -800,20 +799,18 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 // LDS accesses across it (the rows a wave stages are read by other lanes).
 __device__ inline void wave_lds_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// What the two text kernels share: the stage, the line table and this thread's
-// walk over its lines.  Threads take the lines of the table in turn; when there
-// are more than MAXLS, each takes those that start in its own slice.
+// What the two text kernels share: the stage and where the segment lies in it.
+// Threads take the lines of the table in turn; a segment of more lines than the
+// table holds refills it, window by window.
 struct Lines {
   Stage S;
-  int64_t w0;   // stream offset of staged byte 0
-  int total, before;
-  bool table;
-  int idx, Lc, c1;
+  int64_t w0;    // stream offset of staged byte 0
+  int s0r, s1r;  // the segment, stage-relative
 };
 
-// Stages this workgroup's segment of the chunk and finds its lines.  Contains
-// barriers, the last one after everything it writes.
-__device__ inline Lines open_lines(const Args& a, __attribute__((address_space(3))) unsigned char* s_buf, uint64_t* s_pow5, unsigned short* s_ls, int* s_wsum) {
+// Stages this workgroup's segment of the chunk.  Contains a barrier, and writes
+// the end mark after it (line_starts does not read that far and ends in one).
+__device__ inline Lines open_lines(const Args& a, __attribute__((address_space(3))) unsigned char* s_buf, uint64_t* s_pow5) {
   Lines n;
   const int64_t s0 = (int64_t)blockIdx.x * a.seg, s1 = min(s0 + (int64_t)a.seg, a.nend);
   const int64_t w0r = s0 >= 16 ? s0 - 16 : 0;  // first stream byte staged
@@ -821,29 +818,11 @@ __device__ inline Lines open_lines(const Args& a, __attribute__((address_space(3
   // the staging origin is aligned
   n.w0 = w0r - stage_text(a.buf, w0r, (int)(w1 - w0r), s_buf, s_pow5);
   n.S = Stage{s_buf, (int)(min(a.nend, w1) - n.w0)};
+  n.s0r = (int)(s0 - n.w0);
+  n.s1r = (int)(s1 - n.w0);
   __syncthreads();
   if (threadIdx.x < kPast) s_buf[n.S.lim + (int)threadIdx.x] = 0xFFu;
-  int c0;
-  n.total = line_starts(s_buf, n.w0, (int)(s0 - n.w0), (int)(s1 - n.w0), slice_of(a.seg), a.maxls, s_ls, s_wsum, &c0, &n.c1, &n.before);
-  n.table = n.total <= a.maxls;
-  n.idx = threadIdx.x;
-  n.Lc = c0;
-  if (!n.table && n.w0 + n.Lc > 0)
-    while (n.Lc < n.c1 && Cur(n.S).at(n.Lc - 1) != '\n') ++n.Lc;
   return n;
-}
-
-// This thread's next line: its position in *L (false when it has none left);
-// after parsing it the caller sets Lc to the byte after it.
-__device__ inline bool next_line(Lines& n, const unsigned short* s_ls, int* L) {
-  if (!n.table) {
-    *L = n.Lc;
-    return n.Lc < n.c1;
-  }
-  const bool have = n.idx < n.total;
-  *L = have ? (int)s_ls[n.idx] : 0;
-  n.idx += kThreads;
-  return have;
 }
 
 // Products on the FP64 matrix cores: each wave parses 64 lines into its own LDS
@@ -874,7 +853,8 @@ __global__ __launch_bounds__(kThreads) void k_text(Args a) {
   const int pdst = prod ? 2 + P + ra.dst[P + pi * P - pi * (pi - 1) / 2 + (pj - pi)] : 0;
   const int cdst = threadIdx.x < P ? 2 + P + ra.dst[threadIdx.x] : 0;
   const int kdst = threadIdx.x < P ? 2 + ra.kdst[threadIdx.x] : 0;
-  Lines n = open_lines(a, (__attribute__((address_space(3))) unsigned char*)s_buf, s_pow5, s_ls, s_wsum);
+  __attribute__((address_space(3))) unsigned char* const text = (__attribute__((address_space(3))) unsigned char*)s_buf;
+  const Lines n = open_lines(a, text, s_pow5);
 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int col = lane & 15, rsub = lane >> 4;
@@ -888,56 +868,57 @@ __global__ __launch_bounds__(kThreads) void k_text(Args a) {
     return ((a.intmask >> c) & 1u) ? (double)((int64_t)bits - (int64_t)sKb[c])
                                    : __longlong_as_double((long long)bits) - __longlong_as_double((long long)sKb[c]);
   };
-  for (int round = 0;; ++round) {
-    int L;
-    const bool have = next_line(n, s_ls, &L);
-    // every wave runs round 0 (its barrier); later rounds while a lane has a line
-    if (round > 0 && __builtin_amdgcn_ballot_w64(have) == 0) break;
-    bool ok = false;
-    if (have) {
-      int bad_at = INT32_MAX;
-      const int end = parse_line_p<P>(a.intmask, n.S, s_pow5, L, &bad_at, [&](int c, uint64_t bits) {
-        wr[lane * LD + c] = round > 0 ? (uint64_t)__double_as_longlong(shifted(c, bits)) : bits;
-      });
-      ok = end >= 0;
-      if (ok) {
-        n.Lc = end + 1;
-      } else {
-        first_bad = min(first_bad, bad_at);
-        n.Lc = (-1 - end) + 1;
+  bool first = true;  // this wave's first round: the shift is not yet known
+  for (int base = 0;; base += a.maxls) {
+    const int total = line_starts(text, n.w0, n.s0r, n.s1r, slice_of(a.seg), base, a.maxls, s_ls, s_wsum);
+    const int here = min(total - base, a.maxls);  // lines in the table
+    for (int idx = threadIdx.x;; idx += kThreads) {
+      const bool have = idx < here;
+      // every wave runs the first round (its barrier); later rounds while a lane has a line
+      if (!first && __builtin_amdgcn_ballot_w64(have) == 0) break;
+      bool ok = false;
+      if (have) {
+        int bad_at = INT32_MAX;
+        const int end = parse_line_p<P>(a.intmask, n.S, s_pow5, (int)s_ls[idx], &bad_at, [&](int c, uint64_t bits) {
+          wr[lane * LD + c] = first ? bits : (uint64_t)__double_as_longlong(shifted(c, bits));
+        });
+        ok = end >= 0;
+        if (!ok) first_bad = min(first_bad, bad_at);
       }
-    }
-    if (round == 0) {
-      // block shift: the row of thread 0's first line (the workgroup's first
-      // line when the table holds them all), zeros if it does not parse
-      if (threadIdx.x == 0) {
+      if (first) {
+        // block shift: the row of the workgroup's first line, zeros if it does not parse
+        if (threadIdx.x == 0) {
 #pragma unroll
-        for (int c = 0; c < P; ++c) sKb[c] = ok ? wr[c] : 0;
+          for (int c = 0; c < P; ++c) sKb[c] = ok ? wr[c] : 0;
+        }
+        __syncthreads();
+        if (ok)
+#pragma unroll
+          for (int c = 0; c < P; ++c) wr[lane * LD + c] = (uint64_t)__double_as_longlong(shifted(c, wr[lane * LD + c]));
+        first = false;
       }
-      __syncthreads();
-      if (ok)
+      const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
+      nrows += __builtin_popcountll(okm);
+      if (!ok)
+        for (int c = 0; c < P; ++c) wr[lane * LD + c] = 0;  // 0.0: adds nothing
+      wave_lds_sync();
 #pragma unroll
-        for (int c = 0; c < P; ++c) wr[lane * LD + c] = (uint64_t)__double_as_longlong(shifted(c, wr[lane * LD + c]));
-    }
-    const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
-    nrows += __builtin_popcountll(okm);
-    if (!ok)
-      for (int c = 0; c < P; ++c) wr[lane * LD + c] = 0;  // 0.0: adds nothing
-    wave_lds_sync();
+      for (int h = 0; h < 4; ++h) {
+        if (((okm >> (16 * h)) & 0xFFFFu) == 0) continue;  // 16 absent rows
 #pragma unroll
-    for (int h = 0; h < 4; ++h) {
-      if (((okm >> (16 * h)) & 0xFFFFu) == 0) continue;  // 16 absent rows
-#pragma unroll
-      for (int m = 4 * h; m < 4 * h + 4; ++m) {
-        // lanes of columns P and up hold some other value: only rows and columns
-        // of the product that nobody reads
-        const double v = __longlong_as_double((long long)wr[(4 * m + rsub) * LD + col]);
-        colsum += v;
-        if (m & 1) acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc2, 0, 0, 0);
-        else acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
+        for (int m = 4 * h; m < 4 * h + 4; ++m) {
+          // lanes of columns P and up hold some other value: only rows and columns
+          // of the product that nobody reads
+          const double v = __longlong_as_double((long long)wr[(4 * m + rsub) * LD + col]);
+          colsum += v;
+          if (m & 1) acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc2, 0, 0, 0);
+          else acc = __builtin_amdgcn_mfma_f64_16x16x4f64(v, v, acc, 0, 0, 0);
+        }
       }
+      wave_lds_sync();
     }
-    wave_lds_sync();
+    if (base + a.maxls >= total) break;
+    __syncthreads();  // every wave is done with the table
   }
   if (first_bad != INT32_MAX) {
     atomicMin(&a.status->parse_off, (unsigned long long)(a.base_off + n.w0 + first_bad));
@@ -1147,7 +1128,8 @@ __global__ __launch_bounds__(kThreads) void k_text_convert(ConvArgs a) {
   __shared__ int s_wsum[kWaves];
   const Args& t = a.t;
   unsigned short* s_ls = (unsigned short*)(s_buf + stage_bytes(t.seg));
-  Lines n = open_lines(t, (__attribute__((address_space(3))) unsigned char*)s_buf, s_pow5, s_ls, s_wsum);
+  __attribute__((address_space(3))) unsigned char* const text = (__attribute__((address_space(3))) unsigned char*)s_buf;
+  const Lines n = open_lines(t, text, s_pow5);
   const int64_t unit = (int64_t)blockIdx.x * (t.seg / UNIT);
   const int64_t base = a.group_base[unit / kGroup] + a.first[unit];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -1155,32 +1137,36 @@ __global__ __launch_bounds__(kThreads) void k_text_convert(ConvArgs a) {
   const bool colv = col < P;
   uint64_t* wr = s_rows[wave];
   int first_bad = INT32_MAX;
-  int row = n.table ? (int)threadIdx.x : n.before;  // this thread's line among the segment's
-  for (;;) {
-    int L;
-    const bool have = next_line(n, s_ls, &L);
-    if (__builtin_amdgcn_ballot_w64(have) == 0) break;
-    bool ok = false;
-    if (have) {
-      int bad_at = INT32_MAX;
-      const int end = parse_line_p<P>(t.intmask, n.S, s_pow5, L, &bad_at,
-                                      [&](int c, uint64_t bits) { wr[lane * LD + c] = bits; });
-      ok = end >= 0;
-      if (!ok) first_bad = min(first_bad, L);  // reported by the line's first byte
-      n.Lc = (ok ? end : -1 - end) + 1;
-    }
-    const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
-    wave_lds_sync();
-#pragma unroll 4
-    for (int m = 0; m < CW; ++m) {
-      const int sr = m * RW + rsub;
-      const int k = __shfl(row, sr, 64), Ls = __shfl(L, sr, 64);
-      if (colv && ((okm >> sr) & 1u)) {
-        if (!store_field(a, col, base + k, wr[sr * LD + col], (t.intmask >> col) & 1u)) first_bad = min(first_bad, Ls);
+  for (int w = 0;; w += t.maxls) {
+    const int total = line_starts(text, n.w0, n.s0r, n.s1r, slice_of(t.seg), w, t.maxls, s_ls, s_wsum);
+    const int here = min(total - w, t.maxls);  // lines in the table
+    for (int idx = threadIdx.x;; idx += kThreads) {
+      const bool have = idx < here;
+      if (__builtin_amdgcn_ballot_w64(have) == 0) break;
+      const int L = have ? (int)s_ls[idx] : 0;
+      const int row = w + idx;  // this thread's line among the segment's
+      bool ok = false;
+      if (have) {
+        int bad_at = INT32_MAX;
+        const int end = parse_line_p<P>(t.intmask, n.S, s_pow5, L, &bad_at,
+                                        [&](int c, uint64_t bits) { wr[lane * LD + c] = bits; });
+        ok = end >= 0;
+        if (!ok) first_bad = min(first_bad, L);  // reported by the line's first byte
       }
+      const uint64_t okm = __builtin_amdgcn_ballot_w64(ok);
+      wave_lds_sync();
+#pragma unroll 4
+      for (int m = 0; m < CW; ++m) {
+        const int sr = m * RW + rsub;
+        const int k = __shfl(row, sr, 64), Ls = __shfl(L, sr, 64);
+        if (colv && ((okm >> sr) & 1u)) {
+          if (!store_field(a, col, base + k, wr[sr * LD + col], (t.intmask >> col) & 1u)) first_bad = min(first_bad, Ls);
+        }
+      }
+      wave_lds_sync();
     }
-    wave_lds_sync();
-    row += n.table ? kThreads : 1;
+    if (w + t.maxls >= total) break;
+    __syncthreads();  // every wave is done with the table
   }
   if (first_bad != INT32_MAX) {
     atomicMin(&t.status->parse_off, (unsigned long long)(t.base_off + n.w0 + first_bad));
@@ -1202,10 +1188,14 @@ void launch_text_p(const Args& a, int64_t nblocks, hipStream_t s) {
 
 using namespace text;
 
-// Line starts kept in the table for a segment of lines of mean length ell (a
-// quarter more than expected).
+// Rounds of 256 lines of a segment of lines of mean length ell (the line count
+// taken 3 % high for the spread between segments).
+static double text_rounds(double ell, int seg) { return std::ceil(seg / ell * 1.03 / kThreads); }
+
+// Line starts in the table at a time: those of the rounds expected.  Segments of
+// shorter lines than the mean go through it window by window, in whole rounds.
 static int pick_maxls(double ell, int seg) {
-  return ell > 0.0 ? (int)std::min<double>(MAXLS, 64 + 1.25 * seg / ell) & ~7 : MAXLS;
+  return ell > 0.0 ? (int)std::min<double>(MAXLS, kThreads * text_rounds(ell, seg)) : MAXLS;
 }
 
 // Segment size of the text kernels for lines of mean length ell bytes and p
@@ -1214,9 +1204,9 @@ static int pick_maxls(double ell, int seg) {
 // line table, final sums, record) about 1.2 rounds.  LDS (text and parsed rows)
 // decides how many workgroups share a compute unit; each further one lengthens
 // the others by about 18 %.  Every whole number of units from SEG_MIN to SEG_MAX is
-// scored by the lines per time of a compute unit in these terms (the line count
-// taken 3 % high for the spread between segments; halved when the lines would
-// overflow the line table, whose fallback scans slices).  Ten Table-1 columns
+// scored by the lines per time of a compute unit in these terms (less where a
+// segment has more than 2048 lines: filling the table, a slice per thread, takes
+// over then).  Ten Table-1 columns
 // (57 bytes a line, 8 million lines): 24 KiB 598 us a pass, 12, 20, 28 and 40 KiB
 // 703, 671, 824 and 650; thirteen decimal columns (170 bytes): 40 KiB 869,
 // 24 KiB 1304.  Without a measurement: 20 KiB.
@@ -1226,10 +1216,10 @@ static int pick_text_seg(double ell, int p) {
   double best_score = -1.0;
   for (int seg = SEG_MIN; seg <= SEG_MAX; seg += UNIT) {
     const double lines = seg / ell;
-    const double rounds = std::ceil(lines * 1.03 / kThreads);
+    const double rounds = text_rounds(ell, seg);
     const int lds = text_lds(seg, pick_maxls(ell, seg)) + kThreads * row_words(p) * 8 + 1280;
     const int wgs = std::min(4, (160 << 10) / lds);
-    const double score = wgs * lines / ((1.2 + rounds) * (1.0 + 0.18 * (wgs - 1))) * (lines * 1.03 <= MAXLS ? 1.0 : 0.5);
+    const double score = wgs * lines / ((1.2 + rounds) * (1.0 + 0.18 * (wgs - 1))) * std::min(1.0, 2048 / (lines * 1.03));
     if (score > best_score) {
       best_score = score;
       best = seg;
