@@ -13,7 +13,7 @@
  *
  * Numerics (section "Numerical Considerations": X^T X and N mu mu^T must not
  * be formed separately and subtracted in floating point):
- *  - rows are reduced in blocks shifted by the block's first row; integer
+ *  - rows are reduced in blocks shifted by a row at or before the block's start; integer
  *    columns are reduced exactly and kept as 128-bit integers, so their sums,
  *    cross products and covariances are exact (covariance correctly rounded);
  *  - pairs involving a floating-point column are combined by the pairwise
@@ -144,7 +144,7 @@ int stats_open(const stats_config* cfg, stats_ctx** out);
 
 /* Adds nrows rows: the single streaming pass of section "Data
  * Representation and Sufficient Statistics" (column sums and X^T X of a
- * chunk, shifted by each block's first row as section "Numerical
+ * chunk, each block shifted by a row as section "Numerical
  * Considerations" requires), merged into the handle.  Chunks streamed from
  * host memory follow section "System Overview" (storage -> host memory ->
  * GPU).  planes[k] is the base of plane k (device address for

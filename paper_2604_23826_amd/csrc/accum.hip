@@ -68,6 +68,7 @@ int64_t launch_accum_small_p(const AccumLaunch& L, hipStream_t s) {
     }
   a.nrows = L.nrows;
   a.R = L.block_rows;
+  a.shift_low = L.shift_low;
   a.rec = L.rec;
   if (kind != ACC_PLANES && (kind == ACC_GENERIC || L.nrows <= kLaneRows) && interleaved(L)) {
     launch_rows(a, p, nblocks, s);

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kThreads, (P <= 12 ? 2 : 1)) void k_aos_dma(Args a)
   int64_t Ki[P];
 #pragma unroll
   for (int c = 0; c < P; ++c) {
-    K[c] = shift_of<double>(base + r0 * RS + 8 * c);
+    K[c] = shift_of<double>(base + shift_row(r0, a.shift_low) * RS + 8 * c);
     Ki[c] = 0;
   }
   Acc<P> A;

@@ -3,7 +3,8 @@
 // One workgroup reduces one block of R consecutive rows (section "Data
 // Representation and Sufficient Statistics": column sums and X^T X in one
 // streaming pass; each worker reduces a disjoint subset of rows).  Every
-// value is shifted by the block's first row K before it is accumulated, so the
+// value is shifted by the block's shift row K (its first row; in short blocks of a
+// small chunk the one of shift_row) before it is accumulated, so the
 // block statistics are S = sum (x - K) and Q = sum (x - K)(x - K)^T (upper
 // triangle).  For integer columns these are exact integers in FP64 as long as
 // sum (x - K)^2 < 2^53 (checked when the records are merged); the merge turns
@@ -42,6 +43,7 @@ struct Args {
   uint32_t intmask;         // slots: integer column
   int64_t nrows;
   int64_t R;
+  int64_t shift_low;        // see shift_row
   uint64_t* rec;
   int16_t dst[16 + 136];    // record position (relative to S) of slot entry e
   int8_t kdst[16];          // record column of slot c
@@ -72,7 +74,7 @@ __device__ inline uint64_t uniform64(uint64_t v) {
   return ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
 }
 
-// Shift of slot c: the value in row r0 (uniform; kept in SGPRs).  For int64
+// Shift of slot c: the value in row r0, the block's shift row (uniform; kept in SGPRs).  For int64
 // columns the exact integer goes to Ki.
 __device__ inline void load_shift(const Args& a, int c, int64_t r0, double& K, int64_t& Ki) {
   const char* p0 = a.colbase[c] + r0 * a.colstride[c];
@@ -208,7 +210,7 @@ __device__ inline void prologue(const Args& a, int64_t& r0, int64_t& r1, double 
   r0 = (int64_t)blockIdx.x * a.R;
   r1 = min(r0 + a.R, a.nrows);
 #pragma unroll
-  for (int c = 0; c < P; ++c) load_shift(a, c, r0, K[c], Ki[c]);
+  for (int c = 0; c < P; ++c) load_shift(a, c, shift_row(r0, a.shift_low), K[c], Ki[c]);
 }
 
 // Uniform FP64 shift of a column whose values are read as T (int32 / FP64).

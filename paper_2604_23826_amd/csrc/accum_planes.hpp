@@ -11,12 +11,12 @@ namespace acc {
 template <int P, int NI>
 __global__ __launch_bounds__(kThreads, (P <= 12 ? 2 : 1)) void k_planes(Args a) {
   const int64_t r0 = (int64_t)blockIdx.x * a.R;
-  const int64_t r1 = min(r0 + a.R, a.nrows);
+  const int64_t r1 = min(r0 + a.R, a.nrows), rk = shift_row(r0, a.shift_low);
   double K[P];
   int64_t Ki[P];
 #pragma unroll
   for (int c = 0; c < P; ++c) {
-    K[c] = c < NI ? shift_of<int32_t>(a.colbase[c] + r0 * 4) : shift_of<double>(a.colbase[c] + r0 * 8);
+    K[c] = c < NI ? shift_of<int32_t>(a.colbase[c] + rk * 4) : shift_of<double>(a.colbase[c] + rk * 8);
     Ki[c] = 0;
   }
   Acc<P> A;

@@ -386,8 +386,9 @@ static int layout_kind(const stats_ctx* h, const void* const* planes) {
 static int64_t auto_block_rows(int64_t nrows) {
   // few rows: about 256 blocks, so that the reduction of a small chunk is spread
   // over the chip (4000 ten-column FP64 rows: 7 us in 256-row blocks of the
-  // column-per-lane kernel, 22 us in one 4096-row block; 250,000: 10 us at 1024)
-  if (nrows <= kLaneRows) return std::max<int64_t>(256, (nrows + 65535) / 65536 * 256);
+  // column-per-lane kernel, 22 us in one 4096-row block; 250,000: 10 us at 1024);
+  // powers of two, so that each lies in one run of kShiftRows rows
+  if (nrows <= kLaneRows) return nrows <= 65536 ? 256 : nrows <= 131072 ? 512 : 1024;
   // target ~2048 blocks per launch, between 4096 rows and 2^17 rows per block;
   // below 4096 rows per block the per-block reduction and pipeline start
   // dominate (10^6 FP64 rows of 80 bytes: 22 us with 4096-row blocks, 31 us
@@ -461,7 +462,7 @@ int accumulate_rows(stats_ctx* h, const void* const* planes, int64_t nrows, int6
     a.R = R;
     a.rec = h->rec;
     a.status = h->status_dev;
-    wide::SegArgs g{nullptr, nullptr, counter, R, rows};
+    wide::SegArgs g{nullptr, nullptr, counter, R, rows, RS ? shift_low_for(h, R) : 0};
     {
       Timer t;
       t.begin(h, STATS_K_ACCUM);
@@ -510,6 +511,12 @@ int64_t block_rows_for(const stats_ctx* h, int64_t nrows) {
   return h->block_rows ? h->block_rows : auto_block_rows(nrows);
 }
 
+// shift_row's argument for blocks of R rows from block_rows_for: blocks of a
+// configured height are shifted by their own first row.
+int64_t shift_low_for(const stats_ctx* h, int64_t R) {
+  return !h->block_rows && R < kShiftRows ? kShiftRows - 1 : 0;
+}
+
 // Reduce nrows device-resident rows (plane bases already offset to the first
 // row) into the handle state.  Small p only (p <= 16).
 int accumulate_device_small(stats_ctx* h, const void* const* planes, int64_t nrows) {
@@ -530,6 +537,7 @@ int accumulate_device_small(stats_ctx* h, const void* const* planes, int64_t nro
     for (int c = 0; c < p; ++c) b.colbase[c] = a.colbase[c] + done * a.colstride[c];
     b.nrows = rows;
     b.block_rows = R;
+    b.shift_low = shift_low_for(h, R);
     b.rec = h->rec;
     {
       Timer t;
@@ -558,7 +566,7 @@ int accumulate_device(stats_ctx* h, const void* const* planes, int64_t nrows) {
   if (h->flags & STATS_CFG_PAIRWISE) return accumulate_pairwise(h, planes, nrows);
   if (h->p <= 16) return accumulate_device_small(h, planes, nrows);
   if (h->p <= 32 && h->precision != STATS_PREC_SPLIT && aos_rows_layout(h, planes, 256))
-    return accumulate_rows(h, planes, nrows, h->block_rows ? h->block_rows : auto_block_rows(nrows), 256);
+    return accumulate_rows(h, planes, nrows, block_rows_for(h, nrows), 256);
   return accumulate_device_wide(h, planes, nrows);
 }
 

@@ -53,7 +53,7 @@ struct Layout {
 
 // Block record written by the reduction kernels, in 64-bit words:
 //   [0] n_b   [1] flags (bit c: integer column c held a non-integer value)
-//   K[p]      shift = the block's first row (int64 for integer columns,
+//   K[p]      shift row (see shift_row; int64 for integer columns,
 //             FP64 bits otherwise)
 //   S[p]      sum of (x - K)            (FP64; exact integers for int columns)
 //   Q[T]      sum of (x - K)(x - K)^T   (FP64; exact integers for int pairs)
@@ -413,6 +413,15 @@ __device__ inline T load_global(const char* p) {
 // (80-byte rows, 250,000: 10 against 13 us; 1,000,000: 22 against 21 us).
 constexpr int64_t kLaneRows = (int64_t)1 << 18;
 
+// A block's shift is a row of its chunk: its own first row, or, where a small chunk
+// is cut into blocks shorter than kShiftRows rows, the first row of the kShiftRows
+// ones it lies in (shift_low = kShiftRows - 1, else 0).  A block's sum of squares is
+// then no more than the one that rows shifted together have, so the 2^53 guard of
+// integer columns accepts what it does in blocks of kShiftRows rows: an outlier in
+// the first row of a short block would otherwise count once for every row of it.
+constexpr int64_t kShiftRows = 4096;
+__host__ __device__ inline int64_t shift_row(int64_t r0, int64_t shift_low) { return r0 & ~shift_low; }
+
 struct AccumLaunch {
   const char* colbase[16];  // address of column c in row 0
   int64_t colstride[16];    // bytes between rows of column c
@@ -422,6 +431,7 @@ struct AccumLaunch {
   int kind;  // 0 generic, 1 AoS FP64 (contiguous), 2 dense planes
   int64_t nrows;
   int64_t block_rows;
+  int64_t shift_low;  // see shift_row
   uint64_t* rec;  // nblocks records
 };
 

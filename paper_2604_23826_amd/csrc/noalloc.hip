@@ -87,6 +87,7 @@ extern "C" int stats_accumulate_noalloc(stats_ctx* h, const void* const* planes,
     for (int c = 0; c < p; ++c) b.colbase[c] = a.colbase[c] + done * a.colstride[c];
     b.nrows = rows;
     b.block_rows = R;
+    b.shift_low = shift_low_for(h, R);
     b.rec = rec;
     launch_accum_small_p(b, h->stream);
     hipError_t e = hipGetLastError();

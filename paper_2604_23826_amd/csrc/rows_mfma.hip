@@ -88,8 +88,8 @@ __device__ inline double value(const Col& c, typename Raw<KIND>::type x) {
 }
 
 template <int KIND>
-__device__ inline void set_shift(Col& c, int64_t r0) {
-  const typename Raw<KIND>::type x = load_raw<KIND>(c, c.base + r0 * c.stride);
+__device__ inline void set_shift(Col& c, int64_t rk) {
+  const typename Raw<KIND>::type x = load_raw<KIND>(c, c.base + rk * c.stride);
   c.Ki = 0;
   if constexpr (KIND == K_MIX) {
     if (c.dt == STATS_I64) {
@@ -108,11 +108,11 @@ struct Smem {
   double s[4][64][NT];           // per wave and lane: column sums
 };
 
-// Record of rows [r0, r1), r0 < r1, at out.  Every thread of the workgroup.
+// Record of rows [r0, r1), r0 < r1, shifted by row rk, at out.  Every thread of the workgroup.
 // A non-integer value of a checked column sets the record's flag word and, with
 // status, the handle's status.
 template <int KIND, int NT, int PK>
-__device__ inline void rows_block(Col (&col)[NT], int p, int64_t r0, int64_t r1, uint64_t* out,
+__device__ inline void rows_block(Col (&col)[NT], int p, int64_t r0, int64_t r1, int64_t rk, uint64_t* out,
                                   Smem<NT>& sm, DevStatus* status) {
   static_assert(NT == 1 || PK == 1, "row groups share a product only within 16 columns");
   typedef typename Raw<KIND>::type T;
@@ -172,7 +172,7 @@ __device__ inline void rows_block(Col (&col)[NT], int p, int64_t r0, int64_t r1,
   T xa[kU][NT], xb[kU][NT];
   if (nst > 0) load(xa);
 #pragma unroll
-  for (int h = 0; h < NT; ++h) set_shift<KIND>(col[h], r0);
+  for (int h = 0; h < NT; ++h) set_shift<KIND>(col[h], rk);
   for (int64_t t = 0; t < nst; t += 2) {
     if (t + 1 < nst) load(xb);
     use(xa, kAll);
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_rows(wide::Args a, wide::SegAr
       r0 = tile.r0;
       r1 = tile.r1;
     }
-    rows_block<KIND, NT, PK>(col, a.p, r0, r1, a.rec + item * rec_words(a.p), sm, a.status);
+    rows_block<KIND, NT, PK>(col, a.p, r0, r1, shift_row(r0, g.shift_low), a.rec + item * rec_words(a.p), sm, a.status);
   }
 }
 
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(kThreads) void k_rows(acc::Args a, int p) {
   Col col[1] = {Col{a.colbase[cc], a.colstride[cc], a.dtype[cc], c < p, c < p && ((a.chkmask >> cc) & 1u),
                     (bool)((a.intmask >> cc) & 1u), 0.0, 0}};
   const int64_t r0 = (int64_t)blockIdx.x * a.R, r1 = min(r0 + a.R, a.nrows);
-  rows_block<KIND, 1, PK>(col, p, r0, r1, a.rec + (int64_t)blockIdx.x * rec_words(p), sm, nullptr);
+  rows_block<KIND, 1, PK>(col, p, r0, r1, shift_row(r0, a.shift_low), a.rec + (int64_t)blockIdx.x * rec_words(p), sm, nullptr);
 }
 
 }  // namespace rowsm

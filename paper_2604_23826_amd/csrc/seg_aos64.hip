@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_aos64(wide::Args a, wide::SegA
       r0 = tile.r0;
       r1 = tile.r1;
     }
-    if (tid < p) sm.K[tid] = *(const double*)(base + r0 * kRS + 8 * tid);
+    if (tid < p) sm.K[tid] = *(const double*)(base + shift_row(r0, g.shift_low) * kRS + 8 * tid);
     __syncthreads();
     const bool v0ok = c0 < p, v1ok = kTwo && c1 < p;
     const double K0 = v0ok ? sm.K[c0] : 0.0, K1 = v1ok ? sm.K[c1] : 0.0;

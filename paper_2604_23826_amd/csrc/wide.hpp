@@ -49,6 +49,7 @@ struct SegArgs {
   unsigned long long* counter;        // work queue head (device word)
   int64_t tile_rows = 0;              // > 0: no table; item k is rows [k tile_rows,
   int64_t total_rows = 0;             //   min((k + 1) tile_rows, total_rows))
+  int64_t shift_low = 0;              // see shift_row
 };
 
 // FP32 matrix on the int8 matrix cores (wide_syrk.hip): F vector columns at
