@@ -438,6 +438,8 @@ struct AccumLaunch {
 // Small-p (p <= 16) fused shift + colsum + upper-triangle X^T X + in-block
 // reduction.  Returns the number of blocks written.
 int64_t launch_accum_small_p(const AccumLaunch& a, hipStream_t s);
+// Whether the column-per-lane kernel takes the layout at any number of rows.
+bool lane_kernel(const AccumLaunch& a);
 
 // Merge nblocks records into the state: cur -> next (double-buffered).
 // With part (merge_slice_words(nblocks, p) words of device memory, when that

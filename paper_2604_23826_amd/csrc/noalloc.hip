@@ -70,7 +70,8 @@ extern "C" int stats_accumulate_noalloc(stats_ctx* h, const void* const* planes,
   if (!rec) return STATS_E_HIP;
 
   const int p = h->p;
-  const int64_t R = block_rows_for(h, nrows);
+  const AccumLaunch a = accum_launch_of(h, planes);
+  const int64_t R = block_rows_for(h, nrows, lane_kernel(a));
   const int64_t W = rec_words(p);
   // blocks per launch: their records fit the array; at most 16384 (the merge
   // tree's depth stays at most 14) and 2^28 rows (32-bit plane offsets)
@@ -78,7 +79,6 @@ extern "C" int stats_accumulate_noalloc(stats_ctx* h, const void* const* planes,
   const int64_t max_blocks = std::min<int64_t>(fit, 16384);
   const int64_t max_rows = std::max<int64_t>(R, std::min<int64_t>(max_blocks * R, ((int64_t)1 << 28) / R * R));
   if (fit < 1) return fail(STATS_E_ARG, "stats_accumulate_noalloc: one block's record exceeds the fixed scratch");
-  const AccumLaunch a = accum_launch_of(h, planes);
   int64_t done = 0;
   while (done < nrows) {
     const int64_t rows = std::min(nrows - done, max_rows);
