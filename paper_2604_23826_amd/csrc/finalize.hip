@@ -179,6 +179,109 @@ __device__ inline void implicit_ql(double* Zt, int ld, int q, double* dv, const 
   if (lane < q) dv[lane] = d;
 }
 
+// Pair idx of the q (q - 1) / 2 pairs k < l: the triangle as a rectangle, as for the
+// covariances below.
+__device__ inline void pair_of(int q, int idx, int& k, int& l) {
+  const int len = (q - 1) | 1, r = idx / len, c = idx % len, n = q - 1;  // n rows of n .. 1 pairs
+  k = c < n - r ? r : n - r - 1 + (n & 1);
+  l = (c < n - r ? r + c : k + c - (n - r)) + 1;
+}
+
+// One refinement step (as in eigen_wide.hip) of the eigenvectors in the rows of
+// V, by the whole workgroup: QL's rotations, a rounded root each, leave them two to
+// three times as far off as Jacobi's (9 x 9: 1.0e-15 against 7.1e-16 on average).
+// R = I - V V^T and S = V F V^T with F = M - I, whose diagonal is zero exactly, so
+// that the products' rounding is small against the gaps also where M is near I.
+// Eigenvectors i and j exchange x_ij = (mu_j R_ij + S_ij) / (mu_j - mu_i), mu the
+// Rayleigh quotients on F (to d); where that is no small rotation, or the eigenvalues
+// are too close to tell, only orthogonality is restored.  Returns whether an x was
+// too large for its square to vanish in rounding (another step is due: gaps below
+// some 1e-7).  W is scratch like V.  Every thread.
+template <int C>
+__device__ inline bool refine(const double* M, double* V, double* W, int ld, int q, double* d, int tid) {
+  constexpr int kPairs = (16 * C * C / 2 + kQlThreads - 1) / kQlThreads;  // q <= 4 C
+  constexpr int kElems = 16 * C * C / kQlThreads;
+  const int qq = q * q, np = q * (q - 1) / 2;
+  for (int idx = tid; idx < qq; idx += kQlThreads) {
+    const int k = idx / q, j = idx % q;
+    double s = 0.0;
+    for (int i = 0; i < q; ++i) s = __builtin_fma(V[k * ld + i], i == j ? 0.0 : M[i * q + j], s);
+    W[k * ld + j] = s;
+  }
+  __syncthreads();
+  auto dots = [&](int k, int l, double& p, double& s) {
+    p = s = 0.0;
+    for (int j = 0; j < q; ++j) {
+      const double v = V[l * ld + j];
+      p = __builtin_fma(V[k * ld + j], v, p);
+      s = __builtin_fma(W[k * ld + j], v, s);
+    }
+  };
+  double pk = 0.0, sk = 0.0;
+  if (tid < q) {
+    dots(tid, tid, pk, sk);
+    d[tid] = sk / pk;
+  }
+  __syncthreads();
+  double top = 0.0;  // the spread of mu bounds |F|
+  for (int k = 0; k < q; ++k) top = fmax(top, fabs(d[k]));
+  double x[kPairs], y[kPairs];
+  int large = 0;
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    const int idx = tid + u * kQlThreads;
+    x[u] = y[u] = 0.0;
+    if (idx < np) {
+      int k, l;
+      pair_of(q, idx, k, l);
+      double p, s;
+      dots(k, l, p, s);
+      const double gap = d[l] - d[k];
+      x[u] = y[u] = -0.5 * p;
+      if (fabs(gap) > 1e-7 * top) {
+        const double a = __builtin_fma(-d[l], p, s) / gap, b = __builtin_fma(-d[k], p, s) / -gap;
+        const double m = fmax(fabs(a), fabs(b));
+        if (m <= 0x1p-10) {
+          x[u] = a;  // of vector k in l
+          y[u] = b;  // of vector l in k
+          large |= m > 0x1p-28;
+        }
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kPairs; ++u) {
+    const int idx = tid + u * kQlThreads;
+    if (idx < np) {
+      int k, l;
+      pair_of(q, idx, k, l);
+      W[k * ld + l] = x[u];
+      W[l * ld + k] = y[u];
+    }
+  }
+  if (tid < q) W[tid * ld + tid] = 0.5 * (1.0 - pk);
+  __syncthreads();
+  double v[kElems];
+#pragma unroll
+  for (int u = 0; u < kElems; ++u) {
+    const int idx = tid + u * kQlThreads;
+    v[u] = 0.0;
+    if (idx < qq) {
+      const int l = idx / q, j = idx % q;
+      for (int k = 0; k < q; ++k) v[u] = __builtin_fma(W[k * ld + l], V[k * ld + j], v[u]);
+      v[u] += V[l * ld + j];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < kElems; ++u) {
+    const int idx = tid + u * kQlThreads;
+    if (idx < qq) V[(idx / q) * ld + idx % q] = v[u];
+  }
+  return __syncthreads_or(large);
+}
+
 // N and the status word behind the outputs.
 __device__ inline void put_tail(double* to, const uint64_t* state, const DevStatus* status) {
   to[0] = __longlong_as_double((long long)state[0]);
@@ -289,6 +392,10 @@ __device__ inline void finalize_body(const Args& f) {
       tridiagonalize<8, false>(M, V, A, ld, q, d, e, beta, xp, tid);
     }
     if (tid < 64) implicit_ql(V, ld, q, d, e, tid);
+    __syncthreads();
+    for (int step = 0; step < 3; ++step)
+      if (!(q <= 16 ? refine<4>(M, V, A, ld, q, d, tid) : refine<8>(M, V, A, ld, q, d, tid))) break;
+    if (tid < q) d[tid] += 1.0;
     __syncthreads();
   } else {
   // ---- cyclic Jacobi, round-robin ordering: q/2 disjoint rotations per round ----
