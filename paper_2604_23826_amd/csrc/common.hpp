@@ -481,6 +481,8 @@ int64_t finalize_scratch_words(int q);
 // sweep where the Jacobi method runs.
 hipError_t launch_finalize(const FinalizeLaunch& f, hipStream_t s);
 hipError_t launch_finalize_wide(const FinalizeLaunch& f, hipStream_t s);
+// A correlation matrix of up to 60 columns in one workgroup.
+hipError_t launch_finalize_ql(const FinalizeLaunch& f, hipStream_t s);
 
 // Raw statistics as FP64: s_f64[p], C_f64[p*p] (full) from a state.
 void launch_raw(const uint64_t* state, int p, const uint8_t* intflags_dev, double* out,

@@ -12,6 +12,15 @@ constexpr int kNB = 4;     // 2 x 2 blocks per thread and batch
 constexpr int kNV = 4;     // V row pairs per thread and batch
 constexpr int kMaxSweeps = 60;
 
+// Largest correlation matrix that one workgroup decomposes by QL (finalize.hip) at
+// once.  The rotation chain grows with q^2, the launches of eigen_wide.hip with little
+// more than a constant: a whole finalize call takes 180 us at 24 columns by QL and 183
+// at 25 by the launches; at 28 QL took 251 against 220, at 60 791 against 333.
+constexpr int kQlQ = 24;
+// Largest matrix decomposed in one workgroup's LDS: covariance matrices by Jacobi, and
+// correlation matrices that eigen_wide.hip hands back, by QL.
+constexpr int kLdsQ = 60;
+
 // Entries of an eigenvector within kTie of its largest magnitude are ties: they
 // differ by the solver's rounding only (the all-equal vector of collinear columns,
 // say; up to 17 units of 2^-52 at 24 columns).  They are returned equal, and the

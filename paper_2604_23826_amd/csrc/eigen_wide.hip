@@ -21,10 +21,11 @@
 //   5. One refinement step (Ogita and Aishima, "Iterative refinement for
 //      symmetric eigenvalue decomposition", 2018) with products on the FP64
 //      matrix cores: R = I - V^T V and S = V^T A V correct V to
-//      orthogonality and eigenvector accuracy of a few ulps and give the
-//      eigenvalues as Rayleigh quotients.  It is also the check: a correction
-//      above 1e-7, or a coupling within a cluster above rounding, rejects the
-//      result and the Jacobi method below takes the matrix.
+//      orthogonality and eigenvector accuracy of a few ulps (over the gap) and give
+//      the eigenvalues as Rayleigh quotients.  It is also the check: a correction
+//      above 1e-7, or a coupling between close eigenvalues above 10 q u ||T|| (u =
+//      2^-53), rejects the result, and QL in one workgroup takes matrices of up to
+//      60 columns, the Jacobi method below the others.
 // Covariance matrix (may be graded): the cyclic Jacobi method, one kernel pair
 // per round, until a sweep rotates nothing.  It was the only method before:
 // 256 x 256 takes 2550 rounds of two launches, 27 ms.
@@ -43,6 +44,14 @@ constexpr double kEps = 2.220446049250313e-16;
 constexpr double kCluster = 1e-6;  // gap, of ||T||, below which vectors are orthogonalised together
 constexpr double kNear = 1e-7;     // gap below which the refinement leaves a pair's mixture alone
 constexpr double kAccept = 1e-7;   // largest correction of a refinement that squares it away
+// Largest cluster that k_orth takes: one workgroup orthogonalises it vector by vector.
+// Clusters of 256 take it 69 ms of 512 columns and 134 of 1024, where a whole call by
+// Jacobi takes 113 and 322; of 512 columns' 511 205 ms against 65, of 1024's 1023
+// 2456 against 208.  Nor does it take all but one of the vectors, as of an identity or an
+// equicorrelation matrix, which the fallback decomposes in a step or two (256 columns:
+// 36 ms against 1.9 and 10.8; of collinear columns 35 against 27).
+constexpr int kMaxCluster = 256;
+static_assert(kMaxCluster <= kJThreads, "a thread per gap in k_orth");
 
 // Words of FinalizeLaunch::jc.
 enum { J_ROT = 0, J_NONE = 1, J_LEFT = 2, J_REJECT = 3 };
@@ -222,7 +231,9 @@ __device__ inline double row16_sum(double v) {
 // barriers a step.
 constexpr int kTailThreads = 512;
 __global__ __launch_bounds__(kTailThreads) void k_tri_tail(const double* __restrict__ A, int q, int o, double* H,
-                                                           double* beta, double* d, double* e, const double* p_in) {
+                                                           double* beta, double* d, double* e, const double* p_in,
+                                                           const unsigned* jc) {
+  if (jc[J_NONE]) return;
   __shared__ double sv[kTail], sw[kTail], s_x[2][kTail], s_p[2][kTail], buf[kTailThreads / 64];
   const int tid = threadIdx.x, r = tid >> 4, c = tid & 15, m = q - o;
   {
@@ -358,7 +369,8 @@ __device__ inline Bounds bounds_of(const double* d, const double* e, int q, doub
 // Eigenvalue k (ascending) of T per wave, to about 2^-53 of the bounds: the
 // interval shrinks 65-fold per pass.  lam[q] and, from workgroup 0, scale.
 __global__ __launch_bounds__(kJThreads) void k_bisect(const double* __restrict__ d, const double* __restrict__ e,
-                                                      int q, double* lam, double* scale) {
+                                                      int q, double* lam, double* scale, const unsigned* jc) {
+  if (jc[J_NONE]) return;
   extern __shared__ double2 s_t[];  // d / scale, (e / scale)^2 of the coupling before it
   __shared__ double buf[2][kJThreads / 64];
   const Bounds B = bounds_of(d, e, q, buf);
@@ -431,7 +443,8 @@ constexpr int kBatch = 16;  // steps of a substitution whose operands are loaded
 template <bool FIRST>
 __global__ __launch_bounds__(64) void k_invit(const double* __restrict__ d, const double* __restrict__ e, int q,
                                               const double* __restrict__ lam, const double* __restrict__ scale, Lu f,
-                                              double* __restrict__ X) {
+                                              double* __restrict__ X, const unsigned* jc) {
+  if (jc[J_NONE]) return;
   const int col = blockIdx.x * 64 + threadIdx.x;
   extern __shared__ double2 s_t[];  // d, e of T, two zero rows behind (FIRST)
   if constexpr (FIRST) {
@@ -504,12 +517,20 @@ __global__ __launch_bounds__(64) void k_invit(const double* __restrict__ d, cons
 }
 
 // Classical Gram-Schmidt, twice, within the cluster that starts at eigenvalue
-// blockIdx.x, if one does.
+// blockIdx.x, if one does; a result with a cluster too large for it is rejected.
 __global__ __launch_bounds__(kJThreads) void k_orth(const double* __restrict__ lam, const double* __restrict__ scale,
-                                                    int q, double* X) {
+                                                    int q, double* X, unsigned* jc) {
+  if (jc[J_NONE]) return;
   const double tol = kCluster * *scale;
   const int s = blockIdx.x;
   if (!(s + 1 < q && lam[s + 1] - lam[s] <= tol) || (s > 0 && lam[s] - lam[s - 1] <= tol)) return;
+  {
+    const int most = min(kMaxCluster, q - 2), t = threadIdx.x;
+    if (__syncthreads_and(s + most < q && (t >= most || lam[s + t + 1] - lam[s + t] <= tol))) {
+      if (t == 0) atomicOr(&jc[J_REJECT], 1u);
+      return;
+    }
+  }
   extern __shared__ double s_x[];  // the vector, then its products with the earlier ones
   double* s_c = s_x + q;
   __shared__ double buf[2][kJThreads / 64];
@@ -555,7 +576,9 @@ __global__ __launch_bounds__(kJThreads) void k_orth(const double* __restrict__ l
 
 template <int NL>
 __global__ __launch_bounds__(64) void k_back(const double* __restrict__ X, const double* __restrict__ H,
-                                             const double* __restrict__ beta, int q, double* __restrict__ Vt) {
+                                             const double* __restrict__ beta, int q, double* __restrict__ Vt,
+                                             const unsigned* jc) {
+  if (jc[J_NONE]) return;
   const int col = blockIdx.x, lane = threadIdx.x;
   double x[NL];
   double n2 = 0.0;
@@ -640,7 +663,7 @@ __global__ __launch_bounds__(kJThreads) void k_correct(const double* __restrict_
                                                        int q, const double* __restrict__ scale, double* __restrict__ E,
                                                        double* __restrict__ lam, unsigned* jc) {
   bool ok = true;
-  const double near = kNear * *scale, noise = 64.0 * q * kEps * *scale;
+  const double near = kNear * *scale, noise = 5.0 * q * kEps * *scale;
   for (int idx = blockIdx.x * kJThreads + threadIdx.x; idx < q * q; idx += gridDim.x * kJThreads) {
     const int i = idx / q, j = idx % q;
     const double r = (i == j ? 1.0 : 0.0) - 0.5 * (P[idx] + P[j * q + i]);
@@ -787,7 +810,7 @@ __global__ __launch_bounds__(kJThreads) void k_japply(double* A, double* V, int 
 }  // namespace
 
 int64_t finalize_scratch_words(int q) {
-  if (q <= 24) return 0;  // one workgroup, in LDS
+  if (q <= kQlQ) return 0;  // one workgroup, in LDS
   const int64_t qq = (int64_t)q * q;
   // A, V (rows of eigenvectors or Jacobi's V), H, X, four LU arrays, row
   // exchanges, vectors (d, e, beta, lam, two products, rotation tables), flags
@@ -829,15 +852,15 @@ hipError_t launch_finalize_wide(const FinalizeLaunch& F, hipStream_t s) {
         hipLaunchKernelGGL(k_house<decltype(nl)::value>, dim3((q - k - 1 + 3) / 4), block, 0, s, A, q, k, H, beta, d, e,
                            k & 1 ? p1 : p0, k & 1 ? p0 : p1);
     });
-    hipLaunchKernelGGL(k_tri_tail, dim3(1), dim3(kTailThreads), 0, s, A, q, o, H, beta, d, e, o & 1 ? p1 : p0);
+    hipLaunchKernelGGL(k_tri_tail, dim3(1), dim3(kTailThreads), 0, s, A, q, o, H, beta, d, e, o & 1 ? p1 : p0, jc);
     const size_t sh_t = sizeof(double2) * (size_t)((q + 7) & ~7), sh_2 = 2 * sizeof(double) * (size_t)q;
-    hipLaunchKernelGGL(k_bisect, dim3((q + 3) / 4), block, sh_t, s, d, e, q, lam, scale);
-    hipLaunchKernelGGL(k_invit<true>, dim3((q + 63) / 64), dim3(64), sizeof(double2) * (size_t)(q + 2), s, d, e, q, lam, scale, lu, X);
-    hipLaunchKernelGGL(k_orth, dim3(q), block, sh_2, s, lam, scale, q, X);
-    hipLaunchKernelGGL(k_invit<false>, dim3((q + 63) / 64), dim3(64), 0, s, d, e, q, lam, scale, lu, X);
-    hipLaunchKernelGGL(k_orth, dim3(q), block, sh_2, s, lam, scale, q, X);
+    hipLaunchKernelGGL(k_bisect, dim3((q + 3) / 4), block, sh_t, s, d, e, q, lam, scale, jc);
+    hipLaunchKernelGGL(k_invit<true>, dim3((q + 63) / 64), dim3(64), sizeof(double2) * (size_t)(q + 2), s, d, e, q, lam, scale, lu, X, jc);
+    hipLaunchKernelGGL(k_orth, dim3(q), block, sh_2, s, lam, scale, q, X, jc);
+    hipLaunchKernelGGL(k_invit<false>, dim3((q + 63) / 64), dim3(64), 0, s, d, e, q, lam, scale, lu, X, jc);
+    hipLaunchKernelGGL(k_orth, dim3(q), block, sh_2, s, lam, scale, q, X, jc);
     by_width([&](auto nl) {
-      hipLaunchKernelGGL(k_back<decltype(nl)::value>, dim3(q), dim3(64), 0, s, X, H, beta, q, V);
+      hipLaunchKernelGGL(k_back<decltype(nl)::value>, dim3(q), dim3(64), 0, s, X, H, beta, q, V, jc);
     });
     // W = V A and P = V V^T, S = W V^T, E, V' = V + E^T V (rows of V: vectors)
     double *W = lu.u0, *P = lu.u1, *S = lu.u2, *E = lu.l;
@@ -853,6 +876,7 @@ hipError_t launch_finalize_wide(const FinalizeLaunch& F, hipStream_t s) {
     if (err == hipSuccess) err = hipStreamSynchronize(s);
     if (err != hipSuccess) return err;
     done = w[J_NONE] || !w[J_REJECT];
+    if (!done && q <= kLdsQ) return launch_finalize_ql(F, s);
   }
   if (!done) {
     hipLaunchKernelGGL(k_jinit, grid, block, 0, s, F.pca_on ? nullptr : F.out + q + qq, A, V, q);

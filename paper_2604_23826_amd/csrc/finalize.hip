@@ -24,8 +24,6 @@
 namespace st {
 namespace {
 
-constexpr int kLdsQ = 60;  // Jacobi: A and V in LDS up to this size (2 q^2 doubles <= 57.6 KiB)
-
 struct Args {
   const uint64_t* state;
   int p;
@@ -42,8 +40,8 @@ struct Args {
 
 // The method: Householder and QL for a correlation matrix, Jacobi for a
 // covariance matrix.  A template parameter, so that a launch fetches only the
-// code it runs.
-enum { kQl = 0, kLdsJacobi = 1 };
+// code it runs (kQlLarge: the matrices above kQlQ that eigen_wide.hip hands back).
+enum { kQl = 0, kLdsJacobi = 1, kQlLarge = 2 };
 // Correlation matrices of at most this many columns take Jacobi: their equal
 // diagonal makes its one rotation exact, so both entries of either vector are equal
 // at any correlation (QL, whose shift is rounded, left them 1e-8 apart at 1e-8).
@@ -79,10 +77,6 @@ __device__ inline bool converged(const double* A, int q, int tid, int nth, int* 
 // Jacobi round (about 5 q of them) is three divisions, three square roots and
 // two barriers.  Whole kernel, 9 x 9: 89 -> 38 us; 15 x 15: 168 -> 72 us.
 constexpr int kQlThreads = 256;
-// The rotation chain grows with q^2, the launches of eigen_wide.hip with little
-// more than a constant: a whole finalize call takes 168 and 189 us at 20 columns,
-// 201 and 200 at 24, 251 and 220 at 28, 791 and 333 at 60.
-constexpr int kQlQ = 24;
 
 // Tridiagonal form of the symmetric matrix M (q x q, global or LDS) and the
 // orthogonal factor, transposed, in Zt (column j of it at Zt + j ld).  d[q],
@@ -291,6 +285,7 @@ __device__ inline void put_tail(double* to, const uint64_t* state, const DevStat
 
 template <int METHOD>
 __device__ inline void finalize_body(const Args& f) {
+  constexpr bool QL = METHOD != kLdsJacobi;
   const Layout L = Layout::make(f.p);
   const uint64_t* st = f.state;
   const int64_t n = (int64_t)st[0];
@@ -316,9 +311,9 @@ __device__ inline void finalize_body(const Args& f) {
   // (QL: d, e, beta, q each, and 256 words of exchange in their place, and rows
   // padded to an odd length above q)
   double* A;
-  if constexpr (METHOD == kQl) A = s_dyn + 3 * q + 256;
+  if constexpr (QL) A = s_dyn + 3 * q + 256;
   else A = s_dyn + 5 * npairs;
-  const int ld = METHOD == kQl ? (q + 1) | 1 : q;
+  const int ld = QL ? (q + 1) | 1 : q;
   double* V = A + (int64_t)q * ld;
 
   // covariance undefined (the host reports it); nothing is computed, and the
@@ -369,7 +364,7 @@ __device__ inline void finalize_body(const Args& f) {
     const double v = M[idx];
     if (!isfinite(v)) bad = 1;
     const int i = idx / q, j = idx % q;
-    if constexpr (METHOD != kQl) {
+    if constexpr (!QL) {
       A[i * ld + j] = v;
       V[idx] = i == j ? 1.0 : 0.0;
     }
@@ -383,18 +378,24 @@ __device__ inline void finalize_body(const Args& f) {
     }
     return;
   }
-  if constexpr (METHOD == kQl) {
+  if constexpr (QL) {
     double *d = s_dyn, *e = d + q, *beta = e + q, *xp = beta + q;
-    if (q <= 16) {  // one wave holds a quad per row
+    static_assert(kQlQ <= 32 && kLdsQ <= 64, "eight or sixteen columns per lane of a quad, a quad per row");
+    if constexpr (METHOD == kQlLarge) {
+      tridiagonalize<16, false>(M, V, A, ld, q, d, e, beta, xp, tid);
+    } else if (q <= 16) {  // one wave holds a quad per row
       if (tid < 64) tridiagonalize<4, true>(M, V, A, ld, q, d, e, beta, xp, tid);
     } else {
-      static_assert(kQlQ <= 32, "eight columns per lane of a quad");
       tridiagonalize<8, false>(M, V, A, ld, q, d, e, beta, xp, tid);
     }
     if (tid < 64) implicit_ql(V, ld, q, d, e, tid);
     __syncthreads();
-    for (int step = 0; step < 3; ++step)
-      if (!(q <= 16 ? refine<4>(M, V, A, ld, q, d, tid) : refine<8>(M, V, A, ld, q, d, tid))) break;
+    for (int step = 0; step < 3; ++step) {
+      bool again;
+      if constexpr (METHOD == kQlLarge) again = refine<16>(M, V, A, ld, q, d, tid);
+      else again = q <= 16 ? refine<4>(M, V, A, ld, q, d, tid) : refine<8>(M, V, A, ld, q, d, tid);
+      if (!again) break;
+    }
     if (tid < q) d[tid] += 1.0;
     __syncthreads();
   } else {
@@ -517,17 +518,17 @@ __device__ inline void finalize_body(const Args& f) {
   // component j of eigenvector k at V + j vj + k vk; sorted eigenvalues, the largest
   // magnitude of their vectors and their sources (complemented where the vector
   // changes sign) in LDS that is free now
-  const int vj = METHOD == kQl ? 1 : q, vk = METHOD == kQl ? ld : 1;
-  double* lam = METHOD == kQl ? s_dyn + q : s_dyn;
-  double* var = METHOD == kQl ? s_dyn + 2 * q : s_dyn + q;
-  int* src = (int*)(s_dyn + (METHOD == kQl ? 3 : 2) * q);
-  double* top = METHOD == kQl ? s_dyn + 4 * q : V + qq;
+  const int vj = QL ? 1 : q, vk = QL ? ld : 1;
+  double* lam = QL ? s_dyn + q : s_dyn;
+  double* var = QL ? s_dyn + 2 * q : s_dyn + q;
+  int* src = (int*)(s_dyn + (QL ? 3 : 2) * q);
+  double* top = QL ? s_dyn + 4 * q : V + qq;
   for (int k = tid; k < q; k += nth) {
-    const double lk = METHOD == kQl ? s_dyn[k] : A[(int64_t)k * q + k];
+    const double lk = QL ? s_dyn[k] : A[(int64_t)k * q + k];
     int rank = 0;
     double best = 0.0;
     for (int j = 0; j < q; ++j) {
-      const double lj = METHOD == kQl ? s_dyn[j] : A[(int64_t)j * q + j];
+      const double lj = QL ? s_dyn[j] : A[(int64_t)j * q + j];
       rank += (lj > lk) || (lj == lk && j < k);
       best = fmax(best, fabs(V[(int64_t)j * vj + (int64_t)k * vk]));
     }
@@ -619,8 +620,7 @@ __global__ void k_raw(const uint64_t* st, int p, const uint8_t* intf, double* ou
 
 }  // namespace
 
-hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
-  if (F.q > (F.pca_on ? kLdsQ : kQlQ)) return launch_finalize_wide(F, s);
+static Args args_of(const FinalizeLaunch& F) {
   Args a;
   a.state = F.state;
   a.p = F.p;
@@ -633,15 +633,22 @@ hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
   a.out = F.out;
   a.status = F.status;
   a.host = F.host;
-  const size_t q = (size_t)F.q;
-  if (!F.pca_on && F.q > kOneRotation) {
-    const size_t shm = (256 + (3 + 2 * ((q + 1) | 1)) * q) * sizeof(double);
-    hipLaunchKernelGGL(k_finalize<kQl>, dim3(1), dim3(kQlThreads), shm, s, a);
-  } else {
-    // one wave for the small matrices (its barriers cost nothing)
-    const size_t shm = (5 * ((q + 1) / 2) + 2 * q * q + q) * sizeof(double);
-    hipLaunchKernelGGL(k_finalize<kLdsJacobi>, dim3(1), dim3(F.q <= 16 ? 64 : kQlThreads), shm, s, a);
-  }
+  return a;
+}
+
+hipError_t launch_finalize_ql(const FinalizeLaunch& F, hipStream_t s) {
+  const size_t q = (size_t)F.q, shm = (256 + (3 + 2 * ((q + 1) | 1)) * q) * sizeof(double);
+  if (F.q <= kQlQ) hipLaunchKernelGGL(k_finalize<kQl>, dim3(1), dim3(kQlThreads), shm, s, args_of(F));
+  else hipLaunchKernelGGL(k_finalize<kQlLarge>, dim3(1), dim3(kQlThreads), shm, s, args_of(F));
+  return hipGetLastError();
+}
+
+hipError_t launch_finalize(const FinalizeLaunch& F, hipStream_t s) {
+  if (F.q > (F.pca_on ? kLdsQ : kQlQ)) return launch_finalize_wide(F, s);
+  if (!F.pca_on && F.q > kOneRotation) return launch_finalize_ql(F, s);
+  // one wave for the small matrices (its barriers cost nothing)
+  const size_t q = (size_t)F.q, shm = (5 * ((q + 1) / 2) + 2 * q * q + q) * sizeof(double);
+  hipLaunchKernelGGL(k_finalize<kLdsJacobi>, dim3(1), dim3(F.q <= 16 ? 64 : kQlThreads), shm, s, args_of(F));
   return hipGetLastError();
 }
 
