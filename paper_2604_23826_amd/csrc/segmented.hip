@@ -576,7 +576,7 @@ extern "C" int stats_accumulate_segmented(stats_ctx* h, const void* const* plane
   if (!dg.ok) return fail(STATS_E_HIP, "hipSetDevice failed");
   const int p = h->p;
   std::vector<int2> sts;
-  wide_pairs(p, wide::kWideGroup, &sts);
+  wide_pairs(p, wide_group(p, 0), &sts);
 
   // tile height and occupancy: configured, known to the handle, cached, or tuned now
   const bool aos64 = seg_aos64_layout(h, planes);

@@ -9,14 +9,14 @@
 // merged by the same kernels.  Exact for integer columns under the same 2^53
 // guard as the narrow path.  Split mode (BF16): see wide_split.hip.
 //
-// Tiling: columns form groups of ST = 128, cut into 16-column strips.  A
-// workgroup owns one block of rows and one pair of groups (A, B), A <= B: the
-// upper 16 x 16 tiles of a diagonal pair (at most 36, dealt over eight waves so
-// that the two waves of a SIMD share them evenly), or a strip of A per wave
-// against all strips of B.  Every product's accumulator stays in registers for
-// the whole block, so a row is read once for p <= 128.  The next 32 rows' values are in flight to registers while the
-// staged ones are multiplied; they are shifted into the other half of a double
-// LDS buffer, one barrier per 32 rows.  A thread stages one column, so
+// Tiling: columns form groups of ST = 64 or 128 (wide_group), cut into 16-column
+// strips.  A workgroup owns one block of rows and one pair of groups (A, B), A <= B:
+// the upper 16 x 16 tiles of a diagonal pair (at most 36, dealt over eight waves so
+// that the two waves of a SIMD share them evenly), or a strip of A per wave (64: per
+// two waves) against the strips of B.  Every product's accumulator stays in registers
+// for the whole block, so a row is read once for p <= 128.  The next 32 rows' values
+// are in flight to registers while the staged ones are multiplied; they are shifted
+// into the other half of a double LDS buffer, one barrier per 32 rows.  A thread stages one column, so
 // neighbouring lanes read neighbouring columns.
 //
 // Bound: the matrix cores (64 cycles of a SIMD per 16 x 16 x 4 product; the
@@ -35,12 +35,19 @@ namespace wide {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-constexpr int ST = kWideGroup;
 constexpr int kFThreads = 512;
-constexpr int kRowStep = kFThreads / ST;   // rows staged per pass
-constexpr int kPerThr = KR / kRowStep;     // rows of its column a thread stages
-constexpr int kStrips = ST / 16;
-constexpr int kDiagMax = 5;                // tiles per wave of a diagonal pair
+constexpr int kFWaves = kFThreads / 64;
+
+// Groups of ST columns (64 or 128).
+template <int ST>
+struct Shape {
+  static constexpr int kRowStep = kFThreads / ST;   // rows staged per pass
+  static constexpr int kPerThr = KR / kRowStep;     // rows of its column a thread stages
+  static constexpr int kStrips = ST / 16;
+  // tiles per wave, at most: of a diagonal pair, of another one
+  static constexpr int kDiagMax = (kStrips * (kStrips + 1) / 2 + kFWaves - 1) / kFWaves;
+  static constexpr int kOffMax = kStrips * kStrips / kFWaves;
+};
 
 // A thread's column of one group: element of row r at base + r stride.  KIND: the
 // STATS_* type of every column of the launch (0: each column has its own).
@@ -75,8 +82,9 @@ __device__ inline Col<KIND> load_col(const Args& a, int c, int64_t r0) {
 
 // Raw values of kPerThr rows, the first at p, step bytes apart (TAIL: rows at or
 // past `left` as row left - 1; left > 0).
-template <bool TAIL, int KIND>
-__device__ inline void load_raw(const Col<KIND>& c, const char* p, int64_t step, int left, uint64_t (&x)[kPerThr]) {
+template <int ST, bool TAIL, int KIND>
+__device__ inline void load_raw(const Col<KIND>& c, const char* p, int64_t step, int left, uint64_t (&x)[Shape<ST>::kPerThr]) {
+  constexpr int kRowStep = Shape<ST>::kRowStep, kPerThr = Shape<ST>::kPerThr;
   auto at = [&](int i) { return p + (TAIL ? (int64_t)min(kRowStep * i, left - 1) * c.stride : i * step); };
   if (c.type() == STATS_F64 || c.type() == STATS_I64) {
 #pragma unroll
@@ -89,9 +97,10 @@ __device__ inline void load_raw(const Col<KIND>& c, const char* p, int64_t step,
 
 // Shifted values to LDS (TAIL: rows at or past `left` as zeros), added to the
 // column's sum.
-template <int NC, bool TAIL, int KIND>
-__device__ inline void stage(const Col<KIND>& c, const uint64_t (&x)[kPerThr], int left, double* out, double& sum,
-                             uint32_t& bad) {
+template <int ST, int NC, bool TAIL, int KIND>
+__device__ inline void stage(const Col<KIND>& c, const uint64_t (&x)[Shape<ST>::kPerThr], int left, double* out,
+                             double& sum, uint32_t& bad) {
+  constexpr int kRowStep = Shape<ST>::kRowStep, kPerThr = Shape<ST>::kPerThr;
   double v[kPerThr];
   auto put = [&](auto value) {
     if (c.chk) {
@@ -128,12 +137,13 @@ __device__ inline uint64_t shift_word(const Args& a, int c, const Col<KIND>& col
 // One block of rows [r0, r1) and pair of groups (A, B), DIAG: A == B: this
 // pair's part of the record at out.  lds: 2 KR NC doubles, NC = ST (DIAG) or
 // 2 ST.  Every thread of the workgroup.
-template <bool DIAG, int KIND>
+template <int ST, bool DIAG, int KIND>
 __device__ inline void wide_f64_block(const Args& a, uint64_t* out, int64_t r0, int64_t r1, int A, int B,
                                       double* lds) {
   constexpr int NC = DIAG ? ST : 2 * ST;
   constexpr int NG = DIAG ? 1 : 2;
-  constexpr int NT = DIAG ? kDiagMax : kStrips;
+  constexpr int kRowStep = Shape<ST>::kRowStep, kPerThr = Shape<ST>::kPerThr, kStrips = Shape<ST>::kStrips;
+  constexpr int NT = DIAG ? Shape<ST>::kDiagMax : Shape<ST>::kOffMax;
   const int tid = threadIdx.x, lane = tid & 63, p = a.p;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int my_c = tid % ST, my_r = tid / ST;
@@ -151,7 +161,7 @@ __device__ inline void wide_f64_block(const Args& a, uint64_t* out, int64_t r0, 
     int t = 0;
     for (int i = 0; i < sa; ++i)
       for (int j = i; j < sa; ++j, ++t)
-        if (t % 4 == wave % 4 && t / 4 % 2 == wave / 4) {
+        if (t % kFWaves == wave) {
 #pragma unroll
           for (int u = 0; u < NT; ++u)
             if (u == nt) {
@@ -161,11 +171,12 @@ __device__ inline void wide_f64_block(const Args& a, uint64_t* out, int64_t r0, 
           ++nt;
         }
   } else {
-    nt = wave < sa ? sb : 0;
+    const int b0 = wave / kStrips * NT;  // 64 columns: two waves a strip of A
+    nt = wave % kStrips < sa ? max(min(sb - b0, NT), 0) : 0;
 #pragma unroll
     for (int u = 0; u < NT; ++u) {
-      ta[u] = wave;
-      tb[u] = u;
+      ta[u] = wave % kStrips;
+      tb[u] = b0 + u;
     }
   }
   d4 acc[NT];
@@ -185,14 +196,14 @@ __device__ inline void wide_f64_block(const Args& a, uint64_t* out, int64_t r0, 
     for (int g = 0; g < NG; ++g) {
       // a thread with no row left re-reads the block's last one
       const char* p = TAIL && left <= 0 ? col[g].base + (r1 - 1) * col[g].stride : pn[g];
-      load_raw<TAIL>(col[g], p, kRowStep * col[g].stride, max(left, 1), x[g]);
+      load_raw<ST, TAIL>(col[g], p, kRowStep * col[g].stride, max(left, 1), x[g]);
       pn[g] += KR * col[g].stride;
     }
   };
   auto put = [&](auto tail, int h) {
 #pragma unroll
     for (int g = 0; g < NG; ++g)
-      stage<NC, decltype(tail)::value>(col[g], x[g], left, st0 + h * KR * NC + g * ST, sum[g], bad);
+      stage<ST, NC, decltype(tail)::value>(col[g], x[g], left, st0 + h * KR * NC + g * ST, sum[g], bad);
   };
   constexpr std::false_type whole{};
   constexpr std::true_type tail{};
@@ -239,7 +250,11 @@ __device__ inline void wide_f64_block(const Args& a, uint64_t* out, int64_t r0, 
     }
   };
   using std::integral_constant;
-  if constexpr (DIAG) {
+  if constexpr (NT == 2) {
+    if (nt == 0) run(integral_constant<int, 0>{});
+    else if (nt == 1) run(integral_constant<int, 1>{});
+    else run(integral_constant<int, 2>{});
+  } else if constexpr (DIAG) {
     switch (nt) {
       case 0: run(integral_constant<int, 0>{}); break;
       case 1: run(integral_constant<int, 1>{}); break;
@@ -296,8 +311,8 @@ __device__ inline bool block_of_id(int64_t nblocks, int nt, int64_t* b, int* t) 
 
 // The diagonal pairs (tiles[0 .. ng)) or the others (tiles[ng .. ntiles)) of
 // every block; with ovf only of the flagged blocks.
-template <bool DIAG, int KIND>
-__global__ __launch_bounds__(kFThreads, DIAG ? 4 : 2) void k_wide_f64(Args a, const int* ovf) {
+template <int ST, bool DIAG, int KIND>
+__global__ __launch_bounds__(kFThreads, DIAG || ST == 64 ? 4 : 2) void k_wide_f64(Args a, const int* ovf) {
   extern __shared__ double s_lds[];
   const int ng = (a.p + ST - 1) / ST;
   int64_t b;
@@ -305,12 +320,13 @@ __global__ __launch_bounds__(kFThreads, DIAG ? 4 : 2) void k_wide_f64(Args a, co
   if (!block_of_id(a.nblocks, DIAG ? ng : a.ntiles - ng, &b, &t) || (ovf && !ovf[b])) return;
   const int2 tile = a.tiles[DIAG ? t : ng + t];
   const int64_t r0 = b * a.R, r1 = min(r0 + a.R, a.nrows);
-  wide_f64_block<DIAG, KIND>(a, a.rec + b * rec_words(a.p), r0, r1, tile.x, tile.y, s_lds);
+  wide_f64_block<ST, DIAG, KIND>(a, a.rec + b * rec_words(a.p), r0, r1, tile.x, tile.y, s_lds);
 }
 
 // Persistent variant for batched groups: workgroups take (row tile, pair)
 // items from an atomic queue until it is empty; record slots are indexed by
 // row tile, so results do not depend on which workgroup ran what.
+template <int ST>
 __global__ __launch_bounds__(kFThreads) void k_seg_f64(Args a, SegArgs g) {
   extern __shared__ double s_lds[];
   __shared__ int64_t s_item;
@@ -325,8 +341,9 @@ __global__ __launch_bounds__(kFThreads) void k_seg_f64(Args a, SegArgs g) {
     const int2 pair = a.tiles[item % a.ntiles];
     const SegTile tile = g.rowtiles[rt];
     uint64_t* out = a.rec + rt * rec_words(a.p);
-    if (pair.x == pair.y) wide_f64_block<true, 0>(a, out, tile.r0, tile.r1, pair.x, pair.y, s_lds);
-    else wide_f64_block<false, 0>(a, out, tile.r0, tile.r1, pair.x, pair.y, s_lds);
+    // (a table of groups of 128 is one group: wide_group)
+    if (ST == 128 || pair.x == pair.y) wide_f64_block<ST, true, 0>(a, out, tile.r0, tile.r1, pair.x, pair.y, s_lds);
+    else if constexpr (ST == 64) wide_f64_block<ST, false, 0>(a, out, tile.r0, tile.r1, pair.x, pair.y, s_lds);
   }
 }
 
@@ -342,38 +359,62 @@ void wide_pairs(int p, int group, std::vector<int2>* tiles) {
     for (int B = A + 1; B < ng; ++B) tiles->push_back(make_int2(A, B));
 }
 
+// Column groups of the FP64 kernel.  65 to 128 columns are one group of 128 (every row
+// read once).  Up to 64, half of such a group's threads would stage nothing (a call on
+// 10^6 x 33 FP64 306 us, 156 in groups of 64).  Above 128, groups of 64 spread a block
+// over more workgroups, each with a shorter chain of products, and pad less where
+// their number is odd (5000 x 200 444 and 280 us, 4*10^6 x 160 4.6 and 3.3 ms); with as
+// much padding and workgroups in plenty, groups of 128 read less (4*10^6 x 200 FP32 6.4
+// and 6.7 ms, 200,000 x 1000 6.0 and 6.5).
+int wide_group(int p, int64_t nblocks) {
+  const int n64 = (p + 63) / 64, n128 = (p + 127) / 128;
+  if (n64 == 2) return 128;
+  return n64 % 2 || nblocks * n128 * (n128 + 1) / 2 <= 1024 ? 64 : 128;
+}
+
 // LDS of a pair: two stages of one group (diagonal) or two.
-static constexpr size_t kDiagLds = sizeof(double) * 2 * wide::KR * wide::ST, kPairLds = 2 * kDiagLds;
+static constexpr size_t diag_lds(int group) { return sizeof(double) * 2 * wide::KR * group; }
 
 static hipError_t allow_lds(const void* fn, size_t bytes) {
   return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-template <int KIND>
+template <int ST, int KIND>
 static void go_wide(const wide::Args& a, const int* ovf, hipStream_t s) {
   const int64_t nb8 = (a.nblocks + 7) / 8 * 8;
-  const int ng = (a.p + wide::ST - 1) / wide::ST;
+  const int ng = (a.p + ST - 1) / ST;
   const dim3 block(wide::kFThreads);
-  hipLaunchKernelGGL((wide::k_wide_f64<true, KIND>), dim3((unsigned)(nb8 * ng)), block, kDiagLds, s, a, ovf);
+  hipLaunchKernelGGL((wide::k_wide_f64<ST, true, KIND>), dim3((unsigned)(nb8 * ng)), block, diag_lds(ST), s, a, ovf);
   if (a.ntiles > ng) {
-    (void)allow_lds((const void*)wide::k_wide_f64<false, KIND>, kPairLds);
-    hipLaunchKernelGGL((wide::k_wide_f64<false, KIND>), dim3((unsigned)(nb8 * (a.ntiles - ng))), block, kPairLds, s, a, ovf);
+    (void)allow_lds((const void*)wide::k_wide_f64<ST, false, KIND>, 2 * diag_lds(ST));
+    hipLaunchKernelGGL((wide::k_wide_f64<ST, false, KIND>), dim3((unsigned)(nb8 * (a.ntiles - ng))), block, 2 * diag_lds(ST), s, a, ovf);
   }
 }
 
 // kind: the STATS_* type of every column, or 0.  FP64 tables have an instance
 // of their own (types told apart per thread cost the registers of a second
 // workgroup per compute unit).
-void launch_wide_f64(const wide::Args& a, int kind, const int* ovf, hipStream_t s) {
-  if (kind == STATS_F64) go_wide<STATS_F64>(a, ovf, s);
-  else go_wide<0>(a, ovf, s);
+void launch_wide_f64(const wide::Args& a, int group, int kind, const int* ovf, hipStream_t s) {
+  if (group == 64) {
+    if (kind == STATS_F64) go_wide<64, STATS_F64>(a, ovf, s);
+    else go_wide<64, 0>(a, ovf, s);
+  } else {
+    if (kind == STATS_F64) go_wide<128, STATS_F64>(a, ovf, s);
+    else go_wide<128, 0>(a, ovf, s);
+  }
 }
 
 void launch_seg(const wide::Args& a, const wide::SegArgs& g, int nwg, hipStream_t s) {
-  const size_t lds = a.p > wide::ST ? kPairLds : kDiagLds;
-  (void)allow_lds((const void*)wide::k_seg_f64, lds);
+  const int group = wide_group(a.p, 0);
+  const size_t lds = diag_lds(group) * (a.p > group ? 2 : 1);
   hipLaunchKernelGGL(wide::k_zero_counter, dim3(1), dim3(1), 0, s, g.counter);
-  hipLaunchKernelGGL(wide::k_seg_f64, dim3(nwg), dim3(wide::kFThreads), lds, s, a, g);
+  if (group == 64) {
+    (void)allow_lds((const void*)wide::k_seg_f64<64>, lds);
+    hipLaunchKernelGGL(wide::k_seg_f64<64>, dim3(nwg), dim3(wide::kFThreads), lds, s, a, g);
+  } else {
+    (void)allow_lds((const void*)wide::k_seg_f64<128>, lds);
+    hipLaunchKernelGGL(wide::k_seg_f64<128>, dim3(nwg), dim3(wide::kFThreads), lds, s, a, g);
+  }
 }
 
 }  // namespace st

@@ -9,7 +9,6 @@ namespace wide {
 
 constexpr int kThreads = 256;
 constexpr int KR = 32;  // rows staged per step
-constexpr int kWideGroup = 128;  // columns per group of the FP64 kernels
 
 enum { MODE_FP64 = 0, MODE_SPLIT = 1 };
 
@@ -89,9 +88,11 @@ struct SyrkArgs {
 void launch_syrk_split(const wide::SyrkArgs& a, hipStream_t s);
 // FP64 records (p > 32, or any p with ovf).  With ovf only of the blocks whose
 // flag is set (a.rec, a.R, a.nrows, a.nblocks as for the launch that set them).
-// a.tiles as wide_pairs(p, kWideGroup) lists them; kind: the STATS_* type of
-// every column, or 0.
-void launch_wide_f64(const wide::Args& a, int kind, const int* ovf, hipStream_t s);
+// a.tiles as wide_pairs(p, group) lists them, group = wide_group(p, a.nblocks); kind:
+// the STATS_* type of every column, or 0.
+void launch_wide_f64(const wide::Args& a, int group, int kind, const int* ovf, hipStream_t s);
+// Columns per group of the FP64 kernels (of k_seg_f64: for nblocks = 0).
+int wide_group(int p, int64_t nblocks);
 
 // Pairs (A, B), A <= B, of groups of `group` columns: the diagonal ones first.
 void wide_pairs(int p, int group, std::vector<int2>* tiles);

@@ -84,13 +84,14 @@ static int accumulate_syrk(stats_ctx* h, const void* const* planes, int64_t nrow
   // records of one launch stay below ~1 GB
   const int64_t max_blocks = std::max<int64_t>(1, ((int64_t)1 << 30) / (W * 8));
   // FP64 pairs of the blocks that are computed again
+  const int64_t nb_max = std::min<int64_t>(max_blocks, (nrows + R - 1) / R);
+  const int group = wide_group(p, nb_max);
   std::vector<int2> tiles;
-  wide_pairs(p, wide::kWideGroup, &tiles);
+  wide_pairs(p, group, &tiles);
   auto up = [](size_t n) { return (n + 255) / 256 * 256; };
   const size_t col_bytes = up(sizeof(int32_t) * (size_t)p);
   const size_t tile_bytes = up(sizeof(int2) * tiles.size());
   const size_t slot_bytes = up(sizeof(wide::SlotInfo) * (size_t)p);
-  const int64_t nb_max = std::min<int64_t>(max_blocks, (nrows + R - 1) / R);
   const size_t ovf_bytes = up(sizeof(int) * (size_t)nb_max);
   const size_t sexp_bytes = up(sizeof(int) * (size_t)nb_max * (size_t)F);  // grid exponents
   int rc = ensure_dev(h, &h->aux3_dev, &h->aux3_cap, col_bytes + tile_bytes + slot_bytes + ovf_bytes + sexp_bytes);
@@ -172,7 +173,7 @@ static int accumulate_syrk(stats_ctx* h, const void* const* planes, int64_t nrow
     }
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "matrix-core kernel launch");
-    launch_wide_f64(f, 0, ovf_dev, h->stream);
+    launch_wide_f64(f, group, 0, ovf_dev, h->stream);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "FP64 block launch");
     {
@@ -200,16 +201,18 @@ int accumulate_device_wide(stats_ctx* h, const void* const* planes, int64_t nrow
   }
   const int mode = h->precision == STATS_PREC_SPLIT ? wide::MODE_SPLIT : wide::MODE_FP64;
   if (mode == wide::MODE_FP64 && p <= 32) return accumulate_rows(h, planes, nrows, wide_block_rows(h, nrows), 0);
-  const int ST = p <= 32 ? 32 : 64;  // groups of the split kernel
-  std::vector<int2> tiles;
-  wide_pairs(p, mode == wide::MODE_FP64 ? wide::kWideGroup : ST, &tiles);
-  int kind = h->cols[0].dtype;  // of every column, or 0
-  for (const auto& c : h->cols)
-    if (c.dtype != kind) kind = 0;
   const int64_t R = wide_block_rows(h, nrows);
   const int64_t W = rec_words(p);
   // records of one launch stay below ~256 MB
   const int64_t max_blocks = std::max<int64_t>(1, ((int64_t)256 << 20) / (W * 8));
+  // columns per group: of the FP64 kernel, or of the split one
+  const int group = mode == wide::MODE_FP64 ? wide_group(p, std::min<int64_t>(max_blocks, (nrows + R - 1) / R))
+                                            : (p <= 32 ? 32 : 64);
+  std::vector<int2> tiles;
+  wide_pairs(p, group, &tiles);
+  int kind = h->cols[0].dtype;  // of every column, or 0
+  for (const auto& c : h->cols)
+    if (c.dtype != kind) kind = 0;
   const size_t slot_bytes = sizeof(wide::SlotInfo) * (size_t)p;
   const size_t tile_bytes = sizeof(int2) * tiles.size();
   int rc = ensure_dev(h, &h->aux3_dev, &h->aux3_cap, tile_bytes + slot_bytes + 256);
@@ -251,8 +254,8 @@ int accumulate_device_wide(stats_ctx* h, const void* const* planes, int64_t nrow
     {
       Timer t;
       t.begin(h, STATS_K_SYRK);
-      if (mode == wide::MODE_FP64) launch_wide_f64(a, kind, nullptr, h->stream);
-      else launch_wide_split(a, ST, h->stream);
+      if (mode == wide::MODE_FP64) launch_wide_f64(a, group, kind, nullptr, h->stream);
+      else launch_wide_split(a, group, h->stream);
       t.end();
     }
     e = hipGetLastError();
