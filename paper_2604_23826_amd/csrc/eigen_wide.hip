@@ -417,11 +417,12 @@ __global__ __launch_bounds__(kJThreads) void k_bisect(const double* __restrict__
 // ---- 3: eigenvectors of T -------------------------------------------------------
 
 __device__ inline double start_value(uint32_t i, uint32_t col) {  // in [-1, 1), from an integer hash
-  uint32_t h = i * 0x9E3779B1u ^ (col + 0x85EBCA77u) * 0xC2B2AE3Du;
+  // multipliers: fractional bits of the square roots of 2, 3, 5 and 7, made odd
+  uint32_t h = i * 0x6A09E667u ^ (col + 1u) * 0xBB67AE85u;
   h ^= h >> 15;
-  h *= 0x2C1B3C6Du;
+  h *= 0x3C6EF373u;
   h ^= h >> 12;
-  h *= 0x297A2D39u;
+  h *= 0xA54FF53Bu;
   h ^= h >> 15;
   return (double)(int32_t)h * 0x1p-31;
 }
