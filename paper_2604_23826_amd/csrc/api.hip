@@ -477,7 +477,7 @@ int accumulate_rows(stats_ctx* h, const void* const* planes, int64_t nrows, int6
       Timer t;
       t.begin(h, STATS_K_MERGE);
       launch_merge_records(h->rec, nblocks, p, h->intf_dev, h->state[h->cur], h->state[h->cur ^ 1],
-                           h->status_dev, h->stream, h->rec + nblocks * W);
+                           h->status_dev, h->stream, h->rec + nblocks * W, RS ? shift_run(h, R) : 1);
       t.end();
     }
     e = hipGetLastError();
@@ -523,6 +523,9 @@ int64_t shift_low_for(const stats_ctx* h, int64_t R) {
   return !h->block_rows && R < kShiftRows ? kShiftRows - 1 : 0;
 }
 
+// Records of R rows that share a shift row.
+int shift_run(const stats_ctx* h, int64_t R) { return shift_low_for(h, R) ? (int)(kShiftRows / R) : 1; }
+
 // Reduce nrows device-resident rows (plane bases already offset to the first
 // row) into the handle state.  Small p only (p <= 16).
 int accumulate_device_small(stats_ctx* h, const void* const* planes, int64_t nrows) {
@@ -558,7 +561,7 @@ int accumulate_device_small(stats_ctx* h, const void* const* planes, int64_t nro
       Timer t;
       t.begin(h, STATS_K_MERGE);
       launch_merge_records(h->rec, nblocks, p, h->intf_dev, h->state[h->cur], h->state[h->cur ^ 1],
-                           h->status_dev, h->stream, h->rec + nblocks * W);
+                           h->status_dev, h->stream, h->rec + nblocks * W, shift_run(h, R));
       t.end();
     }
     e = hipGetLastError();

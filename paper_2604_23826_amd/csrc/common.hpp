@@ -445,9 +445,11 @@ bool lane_kernel(const AccumLaunch& a);
 // With part (merge_slice_words(nblocks, p) words of device memory, when that
 // is not 0) many records are folded in slices by several workgroups per
 // entry, then the slice totals in order; without it, in one pass per entry.
+// run: records that share a shift row and are folded as one block, a power of
+// two up to 16 (one pass per entry above 1: such launches have up to 768 records).
 void launch_merge_records(const uint64_t* rec, int64_t nblocks, int p, const uint8_t* intflags_dev,
                           const uint64_t* cur, uint64_t* next, DevStatus* status, hipStream_t s,
-                          uint64_t* part = nullptr);
+                          uint64_t* part = nullptr, int run = 1);
 int64_t merge_slice_words(int64_t nblocks, int p);
 
 // dst status |= src status (stream-ordered; see k_status_or).

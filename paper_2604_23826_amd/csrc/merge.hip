@@ -165,31 +165,46 @@ __device__ void tree_reduce(Tree& S) {
   }
 }
 
-// One block record's words (n_b, flags, K_i, K_j, S_i, S_j, Q_ij) folded
-// into an entry's running total.
+// One block record's words: n_b, flags, K_i, K_j, S_i, S_j, Q_ij.
+struct Sums {
+  double n, si, sj, q;
+};
+
+__device__ inline Sums sums_of(const uint64_t* wd) {
+  return Sums{(double)(int64_t)wd[0], __longlong_as_double((long long)wd[4]),
+              __longlong_as_double((long long)wd[5]), __longlong_as_double((long long)wd[6])};
+}
+
+__device__ inline Chan centred(const Sums& b, const uint64_t* wd, const Entry& E) {
+  Chan blk;
+  blk.n = b.n;
+  blk.mi = kval(wd[2], E.ii) + b.si / b.n;
+  blk.mj = kval(wd[3], E.ij) + b.sj / b.n;
+  blk.m2 = E.is_col ? 0.0 : b.q - b.si * (b.sj / b.n);
+  return blk;
+}
+
+// A record's exact sum and its guard (see kExactQ).
+__device__ inline void fold_exact(const uint64_t* wd, const Sums& b, const Entry& E, i128& exact,
+                                  uint32_t& inexact) {
+  const i128 nb = (int64_t)wd[0];
+  if (E.is_col && E.ii) {
+    const int64_t K = (int64_t)wd[2];
+    if (wd[1] != 0 || !(b.q < kExactQ) || K >= kMaxShift || K <= -kMaxShift) inexact = 1;
+    exact += (i128)(int64_t)b.si + nb * (i128)K;
+  } else if (!E.is_col && E.ii && E.ij) {
+    const i128 Ki = (i128)(int64_t)wd[2], Kj = (i128)(int64_t)wd[3];
+    exact += (i128)(int64_t)b.q + Ki * (i128)(int64_t)b.sj + (i128)(int64_t)b.si * Kj + nb * Ki * Kj;
+  }
+}
+
+// One record folded into an entry's running total.
 __device__ inline void fold_one(const uint64_t* wd, const Entry& E, Chan& acc, i128& exact,
                                 uint32_t& inexact) {
-  const int64_t nb = (int64_t)wd[0];
-  if (nb == 0) return;
-  const double nbd = (double)nb;
-  const uint64_t Kiw = wd[2], Kjw = wd[3];
-  const double Si = __longlong_as_double((long long)wd[4]);
-  const double Sj = __longlong_as_double((long long)wd[5]);
-  const double Qij = __longlong_as_double((long long)wd[6]);
-  Chan blk;
-  blk.n = nbd;
-  blk.mi = kval(Kiw, E.ii) + Si / nbd;
-  blk.mj = kval(Kjw, E.ij) + Sj / nbd;
-  blk.m2 = E.is_col ? 0.0 : Qij - Si * (Sj / nbd);
-  chan_add(acc, blk);
-  if (E.is_col && E.ii) {
-    const int64_t K = (int64_t)Kiw;
-    if (wd[1] != 0 || !(Qij < kExactQ) || K >= kMaxShift || K <= -kMaxShift) inexact = 1;
-    exact += (i128)(int64_t)Si + (i128)nb * (i128)K;
-  } else if (!E.is_col && E.ii && E.ij) {
-    const i128 Ki = (i128)(int64_t)Kiw, Kj = (i128)(int64_t)Kjw;
-    exact += (i128)(int64_t)Qij + Ki * (i128)(int64_t)Sj + (i128)(int64_t)Si * Kj + (i128)nb * Ki * Kj;
-  }
+  if (wd[0] == 0) return;
+  const Sums b = sums_of(wd);
+  chan_add(acc, centred(b, wd, E));
+  fold_exact(wd, b, E, exact, inexact);
 }
 
 __device__ inline void load_rec_words(const uint64_t* r, int p, const Entry& E, uint64_t* wd) {
@@ -234,6 +249,63 @@ __device__ void fold_records(const uint64_t* __restrict__ rec, int64_t lo, int64
   tree_reduce(S);
 }
 
+// The same over all records of blocks shorter than kShiftRows rows, `run` of which
+// (a power of two up to 16) share their shift row and are added up, as the one
+// block that they were cut from, before it is folded: no short block's mean, whose
+// rounding is that of the column's own, enters a covariance (12 columns of 10^12 +-
+// 300 in 1000 rows: errors of 1e-8 of the variance, else 1e-15), and an infinity
+// gives what it gives in one block.  Run r goes to slot r % 256, which one thread
+// alone writes, so the totals are those of blocks of kShiftRows rows.
+__device__ void fold_runs(const uint64_t* __restrict__ rec, int64_t nblocks, int p, const Entry& E,
+                          DevStatus* status, Tree& S, int run) {
+  const int64_t W = rec_words(p);
+  const int tid = threadIdx.x;
+  i128 exact = 0;
+  uint32_t inexact = 0;
+  S.n[tid] = S.mi[tid] = S.mj[tid] = S.m2[tid] = 0.0;
+  __syncthreads();
+  constexpr int kU = 4;
+  for (int64_t b0 = 0; b0 < nblocks; b0 += kTreeThreads * kU) {
+    uint64_t wd[kU][7];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t b = b0 + u * kTreeThreads + tid;
+      const uint64_t* r = rec + (b < nblocks ? b : 0) * W;
+      wd[u][0] = b < nblocks ? r[0] : 0;
+      load_rec_words(r, p, E, wd[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int64_t b = b0 + u * kTreeThreads + tid;
+      if (b - (tid & 63) >= nblocks) break;  // none in this wave
+      const bool has = wd[u][0] != 0;
+      const Sums one = sums_of(wd[u]);
+      Sums sum = has ? one : Sums{0.0, 0.0, 0.0, 0.0};
+      for (int d = 1; d < run && d < nblocks; d <<= 1) {
+        sum.n += __shfl_xor(sum.n, d, 64);
+        sum.si += __shfl_xor(sum.si, d, 64);
+        sum.sj += __shfl_xor(sum.sj, d, 64);
+        sum.q += __shfl_xor(sum.q, d, 64);
+      }
+      if (!has) continue;
+      fold_exact(wd[u], one, E, exact, inexact);
+      if (b % run) continue;
+      const int k = (int)(b / run % kTreeThreads);
+      Chan acc = {S.n[k], S.mi[k], S.mj[k], S.m2[k]};
+      chan_add(acc, centred(sum, wd[u], E));
+      S.n[k] = acc.n;
+      S.mi[k] = acc.mi;
+      S.mj[k] = acc.mj;
+      S.m2[k] = acc.m2;
+    }
+  }
+  if (inexact) atomicOr(&status->bits, ST_INEXACT);
+  S.lo[tid] = (uint64_t)(u128)exact;
+  S.hi[tid] = (uint64_t)((u128)exact >> 64);
+  __syncthreads();
+  tree_reduce(S);
+}
+
 // next = cur followed by the records' total (add, add_exact) for entry e.
 __device__ void finish_entry(int p, int64_t e, const Entry& E, const Chan& add, i128 add_exact,
                              const uint64_t* __restrict__ cur, uint64_t* __restrict__ next) {
@@ -255,16 +327,18 @@ __device__ void finish_entry(int p, int64_t e, const Entry& E, const Chan& add, 
 }
 
 // One pass over all records per entry (few records, or many entries).
+template <bool RUN>
 __global__ __launch_bounds__(kTreeThreads) void k_merge_tree(const uint64_t* __restrict__ rec,
                                                              int64_t nblocks, int p,
                                                              const uint8_t* __restrict__ intf,
                                                              const uint64_t* __restrict__ cur,
                                                              uint64_t* __restrict__ next,
-                                                             DevStatus* status) {
+                                                             DevStatus* status, int run) {
   __shared__ Tree S;
   const int64_t e = blockIdx.x;
   const Entry E = entry_of(p, e, intf);
-  fold_records(rec, 0, nblocks, p, E, status, S);
+  if constexpr (RUN) fold_runs(rec, nblocks, p, E, status, S, run);
+  else fold_records(rec, 0, nblocks, p, E, status, S);
   if (threadIdx.x == 0) {
     const Chan add = {S.n[0], S.mi[0], S.mj[0], S.m2[0]};
     const uint64_t w[2] = {S.lo[0], S.hi[0]};
@@ -566,14 +640,19 @@ int64_t merge_slice_words(int64_t nblocks, int p) {
 
 void launch_merge_records(const uint64_t* rec, int64_t nblocks, int p, const uint8_t* intf,
                           const uint64_t* cur, uint64_t* next, DevStatus* status, hipStream_t s,
-                          uint64_t* part) {
+                          uint64_t* part, int run) {
   const Layout L = Layout::make(p);
   const int64_t E = p + L.T;
   const MergePlan m = merge_plan(nblocks, E);
   const int64_t g = m.g;
+  if (run > 1) {
+    hipLaunchKernelGGL(k_merge_tree<true>, dim3((unsigned)E), dim3(kTreeThreads), 0, s, rec, nblocks, p,
+                       intf, cur, next, status, run);
+    return;
+  }
   if (part == nullptr || g <= 1) {
-    hipLaunchKernelGGL(k_merge_tree, dim3((unsigned)E), dim3(kTreeThreads), 0, s, rec, nblocks, p,
-                       intf, cur, next, status);
+    hipLaunchKernelGGL(k_merge_tree<false>, dim3((unsigned)E), dim3(kTreeThreads), 0, s, rec, nblocks, p,
+                       intf, cur, next, status, 1);
     return;
   }
   const int64_t per = (nblocks + g - 1) / g;

@@ -94,7 +94,7 @@ extern "C" int stats_accumulate_noalloc(stats_ctx* h, const void* const* planes,
     if (e != hipSuccess) return hip_fail(h, e, "accumulate kernel launch");
     // reads the records before the next launch (same stream) overwrites them
     launch_merge_records(rec, nblocks, p, h->intf_dev, h->state[h->cur], h->state[h->cur ^ 1],
-                         h->status_dev, h->stream);
+                         h->status_dev, h->stream, nullptr, shift_run(h, R));
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "merge kernel launch");
     h->cur ^= 1;

@@ -114,6 +114,7 @@ void launch_pairwise_merge_states(const uint64_t* a, const uint64_t* b, uint64_t
 AccumLaunch accum_launch_of(const stats_ctx* h, const void* const* planes);
 int64_t block_rows_for(const stats_ctx* h, int64_t nrows, bool lane = false);
 int64_t shift_low_for(const stats_ctx* h, int64_t R);
+int shift_run(const stats_ctx* h, int64_t R);
 int raw_of_state(stats_ctx* h, const uint64_t* state_dev, int64_t* n, stats_i128* s_int,
                  double* s_f64, stats_i128* C_int, double* C_f64, uint8_t* exact_mask);
 int selection(const stats_ctx* h, const stats_finalize_opts* o, std::vector<int32_t>* sel);
