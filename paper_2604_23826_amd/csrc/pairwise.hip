@@ -5,8 +5,9 @@
 // "Limitations and Future Work").  Covariance and correlation of a pair use
 // only its complete rows (pairwise deletion).
 //
-// Per block of rows, with K_i the first present value of column i in the
-// block (shift) and, per row, d_i = x_i - K_i and v_i = 1 where x_i is present
+// Per block of rows, with K_i the first present value of column i from the
+// block's shift row on (its own first row; blocks of less than 4096 rows: the first
+// of their 4096) and, per row, d_i = x_i - K_i and v_i = 1 where x_i is present
 // (d_i = v_i = 0 where it is NaN), four matrix products over the block's rows
 // hold everything:
 //     N = V^T V          n_ij
@@ -37,7 +38,7 @@ typedef int i4 __attribute__((ext_vector_type(4)));
 
 constexpr int kThreads = 256;
 constexpr int kMaxP = 16;
-constexpr int kScan = 256;  // rows searched for a block's shift
+constexpr int kScan = 256;  // rows searched for a block's shift, from its shift row
 
 // Block record: n (rows), K[16], then the four 16 x 16 tiles N, S, Q, C.
 constexpr int kRecWords = 1 + kMaxP + 4 * 256;
@@ -48,6 +49,7 @@ struct Args {
   int32_t dtype[kMaxP];  // STATS_F32 / STATS_F64
   int p;
   int64_t nrows, R;
+  int64_t shift_low;  // see shift_row
   double* rec;
 };
 
@@ -87,17 +89,18 @@ __global__ __launch_bounds__(kThreads) void k_pairwise(Args a) {
   const int64_t r0 = (int64_t)blockIdx.x * a.R, r1 = min(r0 + a.R, a.nrows);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, q16 = lane & 15;
   const int p = a.p;
-  // shift: the first present value of each column among the block's first rows
+  // shift: the first present value of each column among the first rows
+  const int64_t rk = shift_row(r0, a.shift_low);
   {
     const int c = tid & 15, cc = c < p ? c : 0;
     const bool f32 = a.dtype[cc] == STATS_F32;
-    const int lim = (int)min((int64_t)kScan, r1 - r0);
+    const int lim = (int)min((int64_t)kScan, (a.shift_low ? a.nrows : r1) - rk);
     if (tid < kMaxP) s_first[tid] = INT32_MAX;
     __syncthreads();
     for (int k = tid >> 4; k - (tid >> 4) < lim; k += 16) {
       bool found = c >= p;
       if (!found && k < lim) {
-        const double x = value<KIND>(load_raw<KIND>(a.colbase[cc] + (r0 + k) * a.colstride[cc], f32), f32);
+        const double x = value<KIND>(load_raw<KIND>(a.colbase[cc] + (rk + k) * a.colstride[cc], f32), f32);
         if (x == x) atomicMin(&s_first[c], k);
       }
       __syncthreads();
@@ -107,7 +110,7 @@ __global__ __launch_bounds__(kThreads) void k_pairwise(Args a) {
     if (tid < kMaxP) {
       double K = 0.0;
       if (tid < p && s_first[tid] != INT32_MAX)
-        K = value<KIND>(load_raw<KIND>(a.colbase[tid] + (r0 + s_first[tid]) * a.colstride[tid], f32), f32);
+        K = value<KIND>(load_raw<KIND>(a.colbase[tid] + (rk + s_first[tid]) * a.colstride[tid], f32), f32);
       sK[tid] = K;
     }
     __syncthreads();
@@ -248,22 +251,26 @@ __device__ inline Pair combine(const Pair& a, const Pair& b) {
   return r;
 }
 
-// Pair (i, j) of block record rec (shifted sums -> centred form).
-__device__ inline Pair from_record(const double* rec, int i, int j) {
-  const double* K = rec + 1;
+// Pair (i, j) of block record rec: n, S_i, S_j, Q_i, Q_j, C.
+__device__ inline Pair sums_of(const double* rec, int i, int j) {
   const double* N = rec + 1 + kMaxP;
   const double* S = N + 256;
   const double* Q = S + 256;
   const double* C = Q + 256;
+  return Pair{N[16 * i + j], S[16 * i + j], S[16 * j + i], Q[16 * i + j], Q[16 * j + i], C[16 * i + j]};
+}
+
+// Shifted sums -> centred form, with the shifts of record rec.
+__device__ inline Pair centred(const Pair& s, const double* rec, int i, int j) {
+  const double* K = rec + 1;
+  if (s.n == 0.0) return Pair{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   Pair r;
-  r.n = N[16 * i + j];
-  if (r.n == 0.0) return Pair{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  const double si = S[16 * i + j], sj = S[16 * j + i];
-  r.mi = K[i] + si / r.n;
-  r.mj = K[j] + sj / r.n;
-  r.m2i = Q[16 * i + j] - si * (si / r.n);
-  r.m2j = Q[16 * j + i] - sj * (sj / r.n);
-  r.c = C[16 * i + j] - si * (sj / r.n);
+  r.n = s.n;
+  r.mi = K[i] + s.mi / s.n;
+  r.mj = K[j] + s.mj / s.n;
+  r.m2i = s.m2i - s.mi * (s.mi / s.n);
+  r.m2j = s.m2j - s.mj * (s.mj / s.n);
+  r.c = s.c - s.mi * (s.mj / s.n);
   return r;
 }
 
@@ -281,17 +288,43 @@ constexpr int kMergeThreads = 256;
 
 // One workgroup per pair: thread k combines a contiguous range of blocks,
 // then a fixed binary tree over the threads; the result is combined with the
-// incoming state (cur) into next.
+// incoming state (cur) into next.  run > 1 (a power of two up to 16; at most 256
+// records): thread b holds record b, `run` of which share their shifts and are
+// added up, as the one block of 4096 rows that they were cut from, before they
+// are centred (see fold_runs of the complete-data merge); the result goes to the
+// thread that would have it from such blocks.
 __global__ __launch_bounds__(kMergeThreads) void k_pw_merge(const double* rec, int64_t nblocks, int p,
-                                                           const double* cur, double* next) {
+                                                           const double* cur, double* next, int run) {
   __shared__ Pair part[kMergeThreads];
   const int t = blockIdx.x;
   int i, j;
   pair_of(p, t, i, j);
-  const int64_t a0 = nblocks * threadIdx.x / kMergeThreads, a1 = nblocks * (threadIdx.x + 1) / kMergeThreads;
   Pair acc{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int64_t b = a0; b < a1; ++b) acc = combine(acc, from_record(rec + b * kRecWords, i, j));
-  part[threadIdx.x] = acc;
+  if (run > 1) {
+    const int b = threadIdx.x;
+    const double* r = rec + (b < nblocks ? b : 0) * kRecWords;
+    Pair s = sums_of(r, i, j);
+    if (b >= nblocks) s = Pair{0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int d = 1; d < run && d < nblocks; d <<= 1) {
+      s.n += __shfl_xor(s.n, d, 64);
+      s.mi += __shfl_xor(s.mi, d, 64);
+      s.mj += __shfl_xor(s.mj, d, 64);
+      s.m2i += __shfl_xor(s.m2i, d, 64);
+      s.m2j += __shfl_xor(s.m2j, d, 64);
+      s.c += __shfl_xor(s.c, d, 64);
+    }
+    part[b] = acc;
+    __syncthreads();
+    const int nr = (int)(nblocks + run - 1) / run, k = b / run;
+    if (b % run == 0 && k < nr) part[(kMergeThreads * (k + 1) + nr - 1) / nr - 1] = centred(s, r, i, j);
+  } else {
+    const int64_t a0 = nblocks * threadIdx.x / kMergeThreads, a1 = nblocks * (threadIdx.x + 1) / kMergeThreads;
+    for (int64_t b = a0; b < a1; ++b) {
+      const double* r = rec + b * kRecWords;
+      acc = combine(acc, centred(sums_of(r, i, j), r, i, j));
+    }
+    part[threadIdx.x] = acc;
+  }
   __syncthreads();
   for (int s = kMergeThreads / 2; s >= 1; s >>= 1) {
     if ((int)threadIdx.x < s) part[threadIdx.x] = combine(part[threadIdx.x], part[threadIdx.x + s]);
@@ -396,6 +429,7 @@ int accumulate_pairwise(stats_ctx* h, const void* const* planes, int64_t nrows) 
     for (int c = 0; c < p; ++c) b.colbase[c] = a.colbase[c] + done * a.colstride[c];
     b.nrows = rows;
     b.R = R;
+    b.shift_low = shift_low_for(h, R);
     b.rec = (double*)h->rec;
     {
       Timer t;
@@ -410,7 +444,7 @@ int accumulate_pairwise(stats_ctx* h, const void* const* planes, int64_t nrows) 
       t.begin(h, STATS_K_MERGE);
       hipLaunchKernelGGL(pw::k_pw_merge, dim3((unsigned)T), dim3(pw::kMergeThreads), 0, h->stream,
                          (const double*)h->rec, nblocks, p, (const double*)h->state[h->cur],
-                         (double*)h->state[h->cur ^ 1]);
+                         (double*)h->state[h->cur ^ 1], shift_run(h, R));
       t.end();
     }
     e = hipGetLastError();

@@ -93,3 +93,48 @@ def test_one_infinity(kind, p):
     assert got["mean"][0] == -np.inf
     if p > 1:
         assert np.max(np.abs(got["mean"][1:] - x[:, 1:].mean(0, dtype=np.longdouble))) <= 4 * U * 1e12
+
+
+def _pairwise(x):
+    import torch
+    L = lib()
+    n, p = x.shape
+    h = L.stats_open(L.make_config([(L.STATS_F64, 0, 8 * c, 0) for c in range(p)], [8 * p],
+                                   stream=current_stream(), pairwise=True))
+    planes = [to_dev(x)]
+    torch.cuda.synchronize()
+    try:
+        L.stats_accumulate(h, planes, n)
+        return L.stats_finalize_pairwise(h, p)
+    finally:
+        L.stats_close(h)
+
+
+# the three packings of the pairwise kernel
+@pytest.mark.parametrize("p", [1, 4, 7, 13])
+@pytest.mark.parametrize("n", [300, 1025, 4096])
+def test_pairwise_far_from_zero(p, n):
+    print(f"short blocks, pairwise p={p} n={n}", flush=True)
+    x = _values(n, p)
+    got = _pairwise(x)
+    assert np.all(got["n"] == n)
+    _check_moments(x, got["mean"], got["cov"])
+
+
+@pytest.mark.parametrize("p", [4, 7, 13])
+@pytest.mark.parametrize("n,rows", [(3000, 700), (200_000, 1500)])
+def test_pairwise_missing_and_infinity(p, n, rows):
+    """Column 1 is missing beyond its first rows, so whole blocks hold none of it: its
+    moments and the pair's are those of the first rows alone.  Column 2's infinity
+    gives an infinite mean."""
+    print(f"short blocks, pairwise with missing values p={p} n={n}", flush=True)
+    x = _values(n, p)
+    x[rows:, 1] = np.nan
+    x[rows + 100, 2] = np.inf
+    got = _pairwise(x)
+    assert got["n"][0, 1] == rows and got["n"][0, 0] == n
+    if n <= 4096:
+        assert got["mean"][2] == np.inf
+    y = x[:rows, :2]  # column 0's own mean and variance are over all rows: y's instead
+    _check_moments(y, np.array([(y[:, 0] - 1e12).mean() + 1e12, got["mean"][1]]),
+                   np.array([[np.var(y[:, 0] - 1e12, ddof=1), got["cov"][0, 1]], got["cov"][1, :2]]))
