@@ -410,7 +410,10 @@ __device__ inline T load_global(const char* p) {
 // Chunks of at most this many interleaved rows take the column-per-lane kernel
 // (rows_mfma.hip) whatever their layout: its short code and early loads start
 // faster than the LDS-DMA kernels, which overtake it where bandwidth counts
-// (80-byte rows, 250,000: 10 against 13 us; 1,000,000: 22 against 21 us).
+// (80-byte rows, 250,000: 10 against 13 us; 1,000,000: 22 against 21 us).  FP64 rows,
+// 262,144 and 65,536 of them: 2 columns 7.6 against 6.6 us; 3, 5 and 13 within 2 %;
+// 10 columns 10.5 against 12.7 and 7.1 against 11.3; 16 columns 11.6 against 22.8 and
+// 7.2 against 22.9.
 constexpr int64_t kLaneRows = (int64_t)1 << 18;
 
 // A block's shift is a row of its chunk: its own first row, or, where a small chunk

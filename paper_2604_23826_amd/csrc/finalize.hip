@@ -75,7 +75,8 @@ __device__ inline bool converged(const double* A, int q, int tid, int nth, int* 
 // bounds it is the chain of one rotation (about 1.2 q^2 of them), one
 // reciprocal square root and a dozen dependent FMAs (360 cycles in all), where a
 // Jacobi round (about 5 q of them) is three divisions, three square roots and
-// two barriers.  Whole kernel, 9 x 9: 89 -> 38 us; 15 x 15: 168 -> 72 us.
+// two barriers.  Whole kernel with the refinement below (3 and 4 us),
+// 9 x 9: 89 -> 39 us; 15 x 15: 168 -> 76 us.
 constexpr int kQlThreads = 256;
 
 // Tridiagonal form of the symmetric matrix M (q x q, global or LDS) and the

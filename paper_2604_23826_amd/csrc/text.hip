@@ -17,8 +17,8 @@
 // integer field and some 300 a 17-digit decimal one, at two to three waves per
 // SIMD (the text and the parsed rows fill LDS).  8 million ten-column Table-1
 // lines (458 MB): 1050 us in the kernel with the fields unrolled (78 KiB of
-// code) and a corrected FP64 division per decimal field, 515 us as it is;
-// conversion of 2 million lines of eight decimals: 474 and 210 us.
+// code) and a corrected FP64 division per decimal field, 525 us as it is;
+// conversion of 2 million lines of eight decimals: 474 and 214 us.
 //
 // Fields: integer columns are decimal integers (optional sign, at most 18
 // digits), parsed exactly; other columns are decimal numbers (optional sign,
